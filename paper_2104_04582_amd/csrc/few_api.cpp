@@ -488,6 +488,7 @@ PrepJob prep_job(const HostReq &r, ReqBase base, double theta, double phi, doubl
     j.mrows = at_up<const int2>(r, base, r.L.off_mrows);
     j.mtab = r.mfma ? at_dev<char>(r, base, r.L.off_mtab) : nullptr;
     j.mscale = r.mfma ? at_dev<float>(r, base, r.L.off_mscale) : nullptr;
+    j.mcls = r.mfma ? at_dev<unsigned long long>(r, base, r.L.off_mcls) : nullptr;
     j.n_mrows = r.terms.n_mrows;
     j.n_min = r.terms.n_min;
     j.n_segs = r.terms.n_segs;
@@ -521,6 +522,7 @@ SumJob sum_job(const HostReq &r, ReqBase base, double t_start, double dt, int64_
     j.split = tl.split ? 1 : 0;
     j.mtab = r.mfma ? at_dev<const char>(r, base, r.L.off_mtab) : nullptr;
     j.mscale = r.mfma ? at_dev<const float>(r, base, r.L.off_mscale) : nullptr;
+    j.mcls = r.mfma ? at_dev<const unsigned long long>(r, base, r.L.off_mcls) : nullptr;
     j.mrows = at_up<const int2>(r, base, r.L.off_mrows);
     j.n_mrows = r.terms.n_mrows;
     j.n_min = r.terms.n_min;

@@ -96,7 +96,7 @@ inline int split_tile_samples() { return kWave * kSamplesPerLaneF32; }
 // samples per wave, kMfWaves waves per workgroup.  A request takes this
 // path when its term layout fits the shape and is long enough to repay it.
 #ifndef FEW_MF_NT
-#define FEW_MF_NT 3
+#define FEW_MF_NT 4
 #endif
 #ifndef FEW_MF_WAVES
 #define FEW_MF_WAVES 12
@@ -108,7 +108,7 @@ constexpr int kMfWaves = FEW_MF_WAVES;
 constexpr int kMfRows = 8 * kMfMT;          // signed m values per request
 constexpr int kMfA = 16 * kMfT;             // |n| < kMfA
 constexpr int kMfRound = kMfWaves * kMfNT * 16;   // samples per workgroup round
-// fp16 values of one interval: [p 4][mt][t][hi, lo][lane 64][8]
+// fp16 values of one interval: [mt][p 4][t][hi, lo][lane 64][8]
 constexpr size_t kMfIntervalHalves = (size_t)4 * kMfMT * kMfT * 2 * 64 * 8;
 constexpr int kMfMinTerms = 480;            // below this the vector kernel is cheaper
 
@@ -174,6 +174,7 @@ struct PrepJob {
     const int2 *mrows;      // [n_mrows + 1]: (m, first segment) per row, sentinel (0, n_segs)
     void *mtab;             // [K-1][kMfIntervalHalves] fp16
     float *mscale;          // [K-1][kMfRows]: 2^E with row values scaled by 2^-E
+    unsigned long long *mcls;   // [K-1]: fragment classes, 16 bits per row tile
     int n_mrows, n_min, n_segs;
     int l_max;              // largest listed l
 };
@@ -212,6 +213,7 @@ struct SumJob {
     // matrix-core path
     const void *mtab;       // [K-1][kMfIntervalHalves] fp16 operand table
     const float *mscale;    // [K-1][kMfRows]
+    const unsigned long long *mcls;     // [K-1]
     const int2 *mrows;      // [n_mrows + 1]
     int n_mrows, n_min;
     long long sample_base;  // first sample of this job in a batched launch's range
@@ -334,7 +336,7 @@ struct ReqLayout {
     size_t off_t, off_segs, off_term_ptr, off_term_src, off_chunks, off_mrows,
         upload_end;   // host-staged
     size_t off_pcoef, off_acoef, off_ybuf, off_table, off_starts, off_tile_pref, off_mtab,
-        off_mscale, total;
+        off_mscale, off_mcls, total;
     size_t dev_begin;       // first device-produced offset (== off_pcoef)
 };
 // mfma: binary32 request on the matrix-core path (binary64 fold table, fp16

@@ -291,6 +291,7 @@ ReqLayout request_layout(bool fp32, int K, int M, int n_segs, int n_terms, int n
     L.off_tile_pref = take(sizeof(int) * kParts * (size_t)K);
     L.off_mtab = take(mfma ? sizeof(uint16_t) * kMfIntervalHalves * (size_t)(K - 1) : 0);
     L.off_mscale = take(mfma ? sizeof(float) * kMfRows * (size_t)(K - 1) : 0);
+    L.off_mcls = take(mfma ? sizeof(unsigned long long) * (size_t)(K - 1) : 0);
     L.total = o;
     return L;
 }

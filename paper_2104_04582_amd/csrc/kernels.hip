@@ -1826,7 +1826,7 @@ typedef float mf_float4 __attribute__((ext_vector_type(4)));
 // Fold (Eqs. (9)-(10) for fixed viewing angles, Sec. IV): every term (m_r, n)
 // is C = scale sum_contributors w A, with w = -2Y_{l, m_r} for a listed mode
 // and (-1)^l -2Y_{l, m_r} for the mirror of a listed mode (m_r = -m, the
-// amplitude conjugated), and coefficient p rescaled to u = x / h_i by h_i^p.
+// amplitude conjugated), and the cubic written in v = 2 x / h_i - 1.
 // The weights depend on (l, m_r) only, so the workgroup forms them once per
 // row and l.  The folded values stay in LDS.
 //
@@ -1842,10 +1842,20 @@ typedef float mf_float4 __attribute__((ext_vector_type(4)));
 // 2^-E, E the exponent of the pair's largest |coefficient| on the interval
 // (so scaled values stay below 2), and split into hi = fp16(v) and
 // lo = fp16(v - hi), both from binary64.  Table layout, per interval:
-// [3 - p][mt][t][hi, lo][lane 64][8 values] (p descending, the order of the
+// [mt][3 - p][t][hi, lo][lane 64][8 values] (p descending, the order of the
 // Horner recurrence that reads it), lane l's operand fragment of
 // v_mfma_f32_16x16x32_f16: matrix row l % 16 of the tile, columns
 // a = 16 t + 4 (l / 16) + i / 2 and c = i % 2 for value i.
+// Class of a fragment (row tile, power p, step t), two bits: bit 0 set if it
+// holds a nonzero value, bit 1 if some |value| reaches kMfSmall = 2^-12 (of the
+// row pair's scale), when all three hi/lo products are formed.  Below it, only
+// hi * hi is: there hi = fp16(v) alone resolves v to 2^-24 of the scale, the
+// resolution that hi + lo gives values near the scale, and the lo part of the
+// harmonics (below 2^-12 of their modulus 1) would add less than 2^-24 too,
+// the size of the lo * lo products that are left out everywhere.  A spline's
+// higher powers are small on smooth data: at 100 knots over a year p = 2, 3
+// take one product, so 8 products are formed instead of 12.
+constexpr double kMfSmall = 0x1p-12;
 constexpr int kFoldSegs = 64;                       // segments of a row tile kept in LDS
 
 __device__ void fold_pack_body(const PrepJob &jb, int b) {
@@ -1868,6 +1878,7 @@ __device__ void fold_pack_body(const PrepJob &jb, int b) {
     __shared__ int rowmv[8];                        // m_r of the tile's rows
     __shared__ double2 trig[9];                     // (cos, sin) of theta / 2 and of m_r phi
     __shared__ int2 segv[kFoldSegs];
+    __shared__ int fcls[4 * kMfT];
     const int tid = threadIdx.x;
     const int r0 = 8 * mt;
     // the tile's segments [g0, g1); its terms are one contiguous run [t0, t1)
@@ -1988,14 +1999,25 @@ __device__ void fold_pack_body(const PrepJob &jb, int b) {
 #pragma unroll
             for (int j = 0; j < 3; ++j) src[j] = nsrc[j];
         }
-        double f = jb.scale, fi = jb.scale_im;
+        // overall factor; coefficients of v = 2 x / h - 1 in [-1, 1]
         double *dst = cf[k][n + kMfA - 1];
+        const double hh = 0.5 * h;
+        double f = jb.scale, fi = jb.scale_im;
+        double b[8];
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
-            dst[2 * q] = acc[2 * q] * f - acc[2 * q + 1] * fi;
-            dst[2 * q + 1] = acc[2 * q] * fi + acc[2 * q + 1] * f;
-            f *= h;
-            fi *= h;
+            b[2 * q] = acc[2 * q] * f - acc[2 * q + 1] * fi;
+            b[2 * q + 1] = acc[2 * q] * fi + acc[2 * q + 1] * f;
+            f *= hh;
+            fi *= hh;
+        }
+#pragma unroll
+        for (int c = 0; c < 2; ++c) {               // (v + 1)^q expanded
+            const double b1 = b[2 + c], b2 = b[4 + c], b3 = b[6 + c];
+            dst[c] = b[c] + (b1 + (b2 + b3));
+            dst[2 + c] = b1 + (2.0 * b2 + 3.0 * b3);
+            dst[4 + c] = b2 + 3.0 * b3;
+            dst[6 + c] = b3;
         }
     }
     __syncthreads();
@@ -2024,10 +2046,11 @@ __device__ void fold_pack_body(const PrepJob &jb, int b) {
     __syncthreads();
     _Float16 *dst = (_Float16 *)jb.mtab + (size_t)iv * kMfIntervalHalves;
     for (int it = tid; it < 4 * kMfT * 64; it += blockDim.x) {
-        const int ln = it & 63, t = (it >> 6) % kMfT, p = (it >> 6) / kMfT;
+        const int ln = it & 63, t = (it >> 6) % kMfT, p = (it >> 6) / kMfT;   // one wave: one (p, t)
         const int kk = (ln & 15) >> 1, comp = ln & 1, g = ln >> 4;
         const double sc = rsc[kk];
         mf_half8 hi, lo;
+        bool any = false, big = false;
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
             const int a = 16 * t + 4 * g + j;
@@ -2045,6 +2068,8 @@ __device__ void fold_pack_body(const PrepJob &jb, int b) {
                 else
                     v = c == 0 ? pi + qi : pr - qr;
                 v = v * sc;
+                any = any || v != 0.0;
+                big = big || !(fabs(v) < kMfSmall);
                 // through binary32 (one instruction each way; the pair still
                 // carries about 22 bits: lo takes the exact binary64 residual)
                 const _Float16 hv = (_Float16)(float)v;
@@ -2053,9 +2078,17 @@ __device__ void fold_pack_body(const PrepJob &jb, int b) {
             }
         }
         const size_t at =
-            ((((size_t)(3 - p) * kMfMT + mt) * kMfT + t) * 2) * 512 + (size_t)ln * 8;
+            ((((size_t)mt * 4 + (3 - p)) * kMfT + t) * 2) * 512 + (size_t)ln * 8;
         *(mf_half8 *)(dst + at) = hi;
         *(mf_half8 *)(dst + at + 512) = lo;
+        const int fc = (__ballot(any) ? 1 : 0) | (__ballot(big) ? 2 : 0);
+        if (ln == 0) fcls[p * kMfT + t] = fc;
+    }
+    __syncthreads();
+    if (tid == 0) {
+        unsigned w = 0;
+        for (int f = 0; f < 4 * kMfT; ++f) w |= (unsigned)fcls[f] << (2 * f);
+        ((unsigned short *)jb.mcls)[(size_t)iv * 4 + mt] = (unsigned short)w;
     }
 }
 
@@ -2137,100 +2170,111 @@ __device__ __forceinline__ void split_pair(float a0, float a1, unsigned &hi, uns
 }
 
 
-// The value v of the lane whose byte address (4 x lane index) is addr.
-__device__ __forceinline__ float lane_xchg(int addr, float v) {
-    return __builtin_bit_cast(float, __builtin_amdgcn_ds_bpermute(addr, __builtin_bit_cast(int, v)));
-}
-
-// Per-wave LDS area of the per-sample values of one round (SoA, SPW samples):
-// f, f^16, f^{4g} (g = 0..3), e^{-i Phi_phi}, its 8th power, the row
-// harmonic z_0 e^{-2ig Phi_phi} (g = 0..3), u, and the reduced Phi_phi.
+// Per-wave LDS area of the per-sample values of one round (64 samples, one per
+// lane): f = e^{-i Phi_r} and its powers f^2, f^3 (steps inside a lane group's
+// four columns), f^{4g} (g = 0..3, the group's first column; g = 0 stays 1),
+// f^16; E = e^{-i Phi_phi}, E^4 and E^8; the interval coordinate v in [-1, 1];
+// Phi_phi itself (rows of arbitrary m).
 constexpr int kMfSPW = kMfNT * 16;                  // samples per wave and round
-static_assert(kMfNT <= 4, "one sample tile per lane group in the epilogue");
+static_assert(kMfNT == 4, "one sample per lane");
 struct MfSampleArea {
-    float2 f[kMfSPW], f16[kMfSPW], c[kMfSPW][4];
-    float2 e[kMfSPW], e8[kMfSPW], zg[kMfSPW][4];
-    float u[kMfSPW];
+    float2 f[kMfSPW], f2[kMfSPW], f3[kMfSPW], f16[kMfSPW], c[4][kMfSPW];
+    float2 e[kMfSPW], e4[kMfSPW], e8[kMfSPW];
+    float v[kMfSPW];
     double pf[kMfSPW];
 };
 
-// One round of a workgroup: wave w takes the kMfNT * 16 samples
-// base + w kMfNT 16 + s, s = 16 nt + c (tiles nt of 16, valid below e).  The
-// lanes first form the per-sample values of sample s = lane + 64 k (phases,
+// Exchange of the upper 32 lanes of a with the lower 32 of b, and of the odd
+// 16-lane rows of a with the even ones of b.
+__device__ __forceinline__ void lane_swap32(float &a, float &b) {
+    const auto r = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(unsigned, a),
+                                                    __builtin_bit_cast(unsigned, b), false, false);
+    a = __builtin_bit_cast(float, (unsigned)r[0]);
+    b = __builtin_bit_cast(float, (unsigned)r[1]);
+}
+__device__ __forceinline__ void lane_swap16(float &a, float &b) {
+    const auto r = __builtin_amdgcn_permlane16_swap(__builtin_bit_cast(unsigned, a),
+                                                    __builtin_bit_cast(unsigned, b), false, false);
+    a = __builtin_bit_cast(float, (unsigned)r[0]);
+    b = __builtin_bit_cast(float, (unsigned)r[1]);
+}
+
+// One wave-round: the 64 samples wbase + s (s = lane, valid below e) in four
+// tiles of 16.  Every lane first forms the values of its own sample (phases,
 // harmonics and their powers) into the wave's LDS area; in tile nt the four
 // lane groups g = l / 16 of column c read what they need of sample 16 nt + c
 // from there.  Group g holds the operand columns |n| = 16 t + 4 g + j, j < 4,
 // of step t: f^{16 t + 4 g} times f^j (the same fragment serves n and -n).
-// The accumulators run a Horner recurrence in u over p = 3 .. 0.  Returns this
-// lane's binary64 inner-product sums (INNER) or stores h.  The LDS accesses of
-// one wave complete in order, so its area needs no barrier.
+// The row tiles are taken one after the other, the highest first: the
+// accumulators of a tile (16 registers) run a Horner recurrence in v over
+// p = 3 .. 0, then the lane's two rows are combined and added into its
+// running value by a Horner recurrence in E^8.  cls: two bits per (tile,
+// power, step) fragment of the operand table, see fold_pack_body.  The four
+// lane groups of a column are joined by swapping lanes between tiles (two
+// tiles at a time, so that each instruction combines two tiles), after which
+// lane l holds sample l.  Returns this lane's binary64 inner-product sums
+// (INNER) or stores h.  The LDS accesses of one wave complete in order, so its
+// area needs no barrier.
 template <bool INNER>
-__device__ __forceinline__ double2 mf_round(const SumJob &jb, int iv, double ti, double inv_h,
-                                            long long base, long long e, const float4 *lds,
-                                            const float *msc, const int *mm, bool consec,
+__device__ __forceinline__ double2 mf_round(const SumJob &jb, int iv, double ti, double inv_h2,
+                                            long long wbase, long long e, const float4 *lds,
+                                            const float *msc, const int *mm,
+                                            unsigned long long cls, bool consec,
                                             MfSampleArea *sa) {
-    constexpr int SPW = kMfSPW;
-    constexpr int OWN = (SPW + kWave - 1) / kWave;  // samples formed per lane
-    const int lane = threadIdx.x & (kWave - 1), w = threadIdx.x / kWave;
+    const int lane = threadIdx.x & (kWave - 1);
     const int g = lane >> 4, col = lane & 15;
     const FEW_AS4 double *pc = cptr(jb.pcoef) + (size_t)iv * 16;
-    const long long wbase = base + (long long)w * SPW;
     const int m0 = mm[0], am0 = m0 < 0 ? -m0 : m0;
-    // After the row combination every lane holds h of its column's sample in
-    // each tile; lane group g < kMfNT then stores (or takes into the inner
-    // products) the sample of tile g, so a wave issues one store per round.
-    const long long jo = wbase + 16 * g + col;
-    const bool own = g < kMfNT && jo < e;
-    // INNER: that sample's data, requested first so that its latency passes
+    const long long jo = wbase + lane;
+    const bool own = jo < e;
+    // INNER: the sample's data, requested first so that its latency passes
     // under the round's products
     // (every lane loads, at a clamped index, so that the load is not under a
     // branch, which would make the compiler wait for it at the join)
     float2 dv = make_float2(0.0f, 0.0f);
     if constexpr (INNER) dv = ((const float2 *)jb.data)[min(jo, e - 1)];
-    // this lane's samples -> the wave's area
-#pragma unroll
-    for (int k = 0; k < OWN; ++k) {
-        const int sl = lane + kWave * k;
-        if (sl >= SPW) break;
-        long long j = wbase + sl;
-        if (j >= e) j = e - 1;
-        const double tj = dev_sample_time(jb.t_start, jb.dt, j);
-        const dd x = two_sum(tj, -ti);
-        const double pf = phase_raw(pc, x.hi);
-        const double pr = phase_raw(pc + 8, x.hi);
+    // this lane's sample -> the wave's area.  z0 = e^{-i m_0 Phi_phi} and E^2
+    // stay in registers: the same lane holds the sample at the end.
+    float z0r = 1.0f, z0i = 0.0f, e2r = 1.0f, e2i = 0.0f;
+    {
+        const double tj = dev_sample_time(jb.t_start, jb.dt, min(jo, e - 1));
+        const double x = tj - ti;
+        const double pf = phase_raw(pc, x);
+        const double pr = phase_raw(pc + 8, x);
         float er, ei, fr, fi;
         phasor_f32(pf, &er, &ei);
         phasor_f32(pr, &fr, &fi);
-        float f2r, f2i, f4r, f4i, f8r, f8i, f12r, f12i, f16r, f16i;
+        float f2r, f2i, f3r, f3i, f4r, f4i, f8r, f8i, f12r, f12i, f16r, f16i;
         cmulf(fr, fi, fr, fi, &f2r, &f2i);
+        cmulf(f2r, f2i, fr, fi, &f3r, &f3i);
         cmulf(f2r, f2i, f2r, f2i, &f4r, &f4i);
         cmulf(f4r, f4i, f4r, f4i, &f8r, &f8i);
         cmulf(f8r, f8i, f4r, f4i, &f12r, &f12i);
         cmulf(f8r, f8i, f8r, f8i, &f16r, &f16i);
-        sa->u[sl] = (float)(x.hi * inv_h);
-        sa->f[sl] = make_float2(fr, fi);
-        sa->f16[sl] = make_float2(f16r, f16i);
-        sa->c[sl][0] = make_float2(1.0f, 0.0f);
-        sa->c[sl][1] = make_float2(f4r, f4i);
-        sa->c[sl][2] = make_float2(f8r, f8i);
-        sa->c[sl][3] = make_float2(f12r, f12i);
-        sa->e[sl] = make_float2(er, ei);
+        sa->v[lane] = (float)fma(x, inv_h2, -1.0);
+        sa->f[lane] = make_float2(fr, fi);
+        sa->f2[lane] = make_float2(f2r, f2i);
+        sa->f3[lane] = make_float2(f3r, f3i);
+        sa->f16[lane] = make_float2(f16r, f16i);
+        sa->c[1][lane] = make_float2(f4r, f4i);
+        sa->c[2][lane] = make_float2(f8r, f8i);
+        sa->c[3][lane] = make_float2(f12r, f12i);
+        sa->e[lane] = make_float2(er, ei);
         if (consec) {
             // Rows of consecutive m (m_r = m_0 + r): every z_r is a power of
             // E = e^{-i Phi_phi}.  z_0 = E^{m_0} by binary powering (E^{-1} =
             // conj E), so each z_r carries m_r times the phase error of E, at
-            // most max |m| of it.  Lane group g starts from z_0 E^{2g}.
-            float e2r, e2i, e4r, e4i, e6r, e6i, e8r, e8i;
+            // most max |m| of it.
+            float e4r, e4i, e8r, e8i;
             cmulf(er, ei, er, ei, &e2r, &e2i);
             cmulf(e2r, e2i, e2r, e2i, &e4r, &e4i);
-            cmulf(e4r, e4i, e2r, e2i, &e6r, &e6i);
             cmulf(e4r, e4i, e4r, e4i, &e8r, &e8i);
-            float zr = 1.0f, zi = 0.0f, br = e8r, bi = e8i;
+            float br = e8r, bi = e8i;
             auto take = [&](float qr, float qi) {
                 float nr, ni;
-                cmulf(zr, zi, qr, qi, &nr, &ni);
-                zr = nr;
-                zi = ni;
+                cmulf(z0r, z0i, qr, qi, &nr, &ni);
+                z0r = nr;
+                z0i = ni;
             };
             if (am0 & 1) take(er, ei);
             if (am0 & 2) take(e2r, e2i);
@@ -2242,67 +2286,65 @@ __device__ __forceinline__ double2 mf_round(const SumJob &jb, int iv, double ti,
                 br = nr;
                 bi = ni;
             }
-            if (m0 < 0) zi = -zi;
-            sa->e8[sl] = make_float2(e8r, e8i);
-            sa->zg[sl][0] = make_float2(zr, zi);
-            float qr, qi;
-            cmulf(zr, zi, e2r, e2i, &qr, &qi);
-            sa->zg[sl][1] = make_float2(qr, qi);
-            cmulf(zr, zi, e4r, e4i, &qr, &qi);
-            sa->zg[sl][2] = make_float2(qr, qi);
-            cmulf(zr, zi, e6r, e6i, &qr, &qi);
-            sa->zg[sl][3] = make_float2(qr, qi);
+            if (m0 < 0) z0i = -z0i;
+            sa->e4[lane] = make_float2(e4r, e4i);
+            sa->e8[lane] = make_float2(e8r, e8i);
         } else {
-            sa->pf[sl] = d_reduce_2pi(pf);
+            // rows of arbitrary m carry their whole phase themselves
+            sa->e4[lane] = make_float2(1.0f, 0.0f);
+            sa->pf[lane] = d_reduce_2pi(pf);
         }
     }
     __builtin_amdgcn_wave_barrier();
     // operands: powers of f for every tile and step (fp16 pairs per word)
     mf_u4 bh[kMfNT][kMfT], bl[kMfNT][kMfT];
-    float uu[kMfNT];
+    float vv[kMfNT];
 #pragma unroll
     for (int nt = 0; nt < kMfNT; ++nt) {
         const int sl = 16 * nt + col;
-        uu[nt] = sa->u[sl];
-        const float2 fa = sa->f[sl], fs = sa->f16[sl], c0 = sa->c[sl][g];
-        const float ar = fa.x, ai = fa.y, sr = fs.x, si = fs.y;
-        float cr = c0.x, ci = c0.y;
+        vv[nt] = sa->v[sl];
+        const float2 f1 = sa->f[sl], f2 = sa->f2[sl], f3 = sa->f3[sl], fs = sa->f16[sl];
+        const float2 c0 = sa->c[g][sl];
+        float w[8];
+        w[0] = c0.x;
+        w[1] = c0.y;
+        cmulf(c0.x, c0.y, f1.x, f1.y, &w[2], &w[3]);
+        cmulf(c0.x, c0.y, f2.x, f2.y, &w[4], &w[5]);
+        cmulf(c0.x, c0.y, f3.x, f3.y, &w[6], &w[7]);
 #pragma unroll
         for (int t = 0; t < kMfT; ++t) {
-            float v[8];
-            v[0] = cr;
-            v[1] = ci;
-            cmulf(v[0], v[1], ar, ai, &v[2], &v[3]);
-            cmulf(v[2], v[3], ar, ai, &v[4], &v[5]);
-            cmulf(v[4], v[5], ar, ai, &v[6], &v[7]);
+            if (t > 0) {
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    float nr, ni;
+                    cmulf(w[2 * i], w[2 * i + 1], fs.x, fs.y, &nr, &ni);
+                    w[2 * i] = nr;
+                    w[2 * i + 1] = ni;
+                }
+            }
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
                 unsigned h, l;
-                split_pair(v[2 * i], v[2 * i + 1], h, l);
+                split_pair(w[2 * i], w[2 * i + 1], h, l);
                 bh[nt][t][i] = h;
                 bl[nt][t][i] = l;
             }
-            if (t + 1 < kMfT) {
-                float nr, ni;
-                cmulf(cr, ci, sr, si, &nr, &ni);
-                cr = nr;
-                ci = ni;
-            }
         }
     }
-    mf_float4 acc[kMfMT][kMfNT];
-    // the products of power p, (mt, t) in order, each fragment read one
-    // fragment ahead of its products (constant offsets from fp).  FIRST: the
-    // first power, whose first product of each (mt, t = 0) starts from zero
-    // (no accumulator to clear).
-    auto power = [&](int p, auto first) {
-        constexpr bool FIRST = decltype(first)::value;
-        const float4 *fp = lds + (size_t)(3 - p) * kMfMT * kMfT * 2 * 64 + lane;
-        constexpr int NF = kMfMT * kMfT;
+    float qr[kMfNT], qi[kMfNT];
+#pragma unroll
+    for (int mt = kMfMT - 1; mt >= 0; --mt) {
+        const float4 *fp = lds + (size_t)mt * 4 * kMfT * 2 * 64 + lane;
+        // (opaque here, so that the compiler does not keep a condition per
+        // fragment in scalar registers across the whole loop over rounds)
+        unsigned ct = (unsigned)(cls >> (16 * mt));
+        asm volatile("" : "+s"(ct));
+        mf_float4 acc[kMfNT];
+        constexpr int NF = 4 * kMfT;                // fragments of the tile, p descending
         float4 ch = fp[0], cl = fp[64];
 #pragma unroll
         for (int k = 0; k < NF; ++k) {
-            const int t = k % kMfT, mt = k / kMfT;
+            const int t = k % kMfT, p = 3 - k / kMfT;
             float4 nh = ch, nl = cl;
             if (k + 1 < NF) {
                 nh = fp[((k + 1) * 2) * 64];
@@ -2312,124 +2354,125 @@ __device__ __forceinline__ double2 mf_round(const SumJob &jb, int iv, double ti,
             __builtin_amdgcn_sched_barrier(0);
             const mf_half8 ah = __builtin_bit_cast(mf_half8, ch);
             const mf_half8 al = __builtin_bit_cast(mf_half8, cl);
+            const unsigned cc = ct >> (2 * (p * kMfT + t));
+            if (t == 0 && p < 3) {
+                // Horner step: every accumulator element of tile nt times v
 #pragma unroll
-            for (int nt = 0; nt < kMfNT; ++nt)
-                acc[mt][nt] = __builtin_amdgcn_mfma_f32_16x16x32_f16(
-                    al, __builtin_bit_cast(mf_half8, bh[nt][t]),
-                    (FIRST && t == 0) ? mf_float4{0.0f, 0.0f, 0.0f, 0.0f} : acc[mt][nt], 0, 0, 0);
+                for (int nt = 0; nt < kMfNT; ++nt)
 #pragma unroll
-            for (int nt = 0; nt < kMfNT; ++nt)
-                acc[mt][nt] = __builtin_amdgcn_mfma_f32_16x16x32_f16(
-                    ah, __builtin_bit_cast(mf_half8, bl[nt][t]), acc[mt][nt], 0, 0, 0);
+                    for (int i = 0; i < 4; ++i) acc[nt][i] = acc[nt][i] * vv[nt];
+            }
+            if (k == 0) {
+                // the first product starts from zero (no accumulator to clear)
 #pragma unroll
-            for (int nt = 0; nt < kMfNT; ++nt)
-                acc[mt][nt] = __builtin_amdgcn_mfma_f32_16x16x32_f16(
-                    ah, __builtin_bit_cast(mf_half8, bh[nt][t]), acc[mt][nt], 0, 0, 0);
+                for (int nt = 0; nt < kMfNT; ++nt)
+                    acc[nt] = __builtin_amdgcn_mfma_f32_16x16x32_f16(
+                        ah, __builtin_bit_cast(mf_half8, bh[nt][t]),
+                        mf_float4{0.0f, 0.0f, 0.0f, 0.0f}, 0, 0, 0);
+            }
+            if (cc & 2) {
+#pragma unroll
+                for (int nt = 0; nt < kMfNT; ++nt)
+                    acc[nt] = __builtin_amdgcn_mfma_f32_16x16x32_f16(
+                        al, __builtin_bit_cast(mf_half8, bh[nt][t]), acc[nt], 0, 0, 0);
+#pragma unroll
+                for (int nt = 0; nt < kMfNT; ++nt)
+                    acc[nt] = __builtin_amdgcn_mfma_f32_16x16x32_f16(
+                        ah, __builtin_bit_cast(mf_half8, bl[nt][t]), acc[nt], 0, 0, 0);
+            }
+            if (k != 0 && (cc & 1)) {
+#pragma unroll
+                for (int nt = 0; nt < kMfNT; ++nt)
+                    acc[nt] = __builtin_amdgcn_mfma_f32_16x16x32_f16(
+                        ah, __builtin_bit_cast(mf_half8, bh[nt][t]), acc[nt], 0, 0, 0);
+            }
             __builtin_amdgcn_sched_barrier(0);
             ch = nh;
             cl = nl;
         }
-    };
-    power(3, std::true_type{});
-#pragma unroll 1
-    for (int p = 2; p >= 0; --p) {
-        // Horner step: every accumulator element of column nt times u
-#pragma unroll
-        for (int mt = 0; mt < kMfMT; ++mt)
-#pragma unroll
-            for (int nt = 0; nt < kMfNT; ++nt)
-#pragma unroll
-                for (int i = 0; i < 4; ++i) acc[mt][nt][i] = acc[mt][nt][i] * uu[nt];
-        power(p, std::false_type{});
-    }
-    // Rows -> h.  The lane holds rows r = 8 mt + 2g (a0 + i b0) and r + 1
-    // (a1 + i b1) of tile mt, each to be scaled by 2^{E_r} and multiplied by
-    // its harmonic z_r = e^{-i m_r Phi_phi}.
-    float se[kMfMT], so[kMfMT];
-    int me[kMfMT], mo[kMfMT];
-#pragma unroll
-    for (int mt = 0; mt < kMfMT; ++mt) {
+        // Rows -> the lane's value.  The lane holds rows r = 8 mt + 2g
+        // (a0 + i b0) and r + 1 (a1 + i b1), which share one scale.
         const int r0 = 8 * mt + 2 * g;
-        se[mt] = msc[r0];
-        so[mt] = msc[r0 + 1];
-        me[mt] = mm[r0];
-        mo[mt] = mm[r0 + 1];
-    }
-    double dh = 0.0, hh = 0.0;
-    float hro = 0.0f, hqo = 0.0f;                   // h of this lane group's sample
-    // byte addresses of lanes l ^ 16 and l ^ 32 for ds_bpermute
-    const int bp16 = (lane ^ 16) << 2, bp32 = (lane ^ 32) << 2;
+        const float se = msc[r0];
+        const int me = mm[r0], mo = mm[r0 + 1];
 #pragma unroll
-    for (int nt = 0; nt < kMfNT; ++nt) {
-        const int sl = 16 * nt + col;
-        const float2 E = sa->e[sl];
-        float hr, hq;
-        if (consec) {
-            // z_r = z_0 E^{2g} E^{8 mt} (E for the odd row): Horner in E^8
-            // over the tiles of W_mt = s (a0 + i b0 + E (a1 + i b1)), s the
-            // scale the two rows share
-            const float2 E8 = sa->e8[sl], Z = sa->zg[sl][g];
-            float qr = 0.0f, qi = 0.0f;
-#pragma unroll
-            for (int mt = kMfMT - 1; mt >= 0; --mt) {
-                // the two rows share their scale (fold_pack_body)
-                const float a0 = acc[mt][nt][0], b0 = acc[mt][nt][1];
-                const float a1 = acc[mt][nt][2], b1 = acc[mt][nt][3];
-                const float wr = se[mt] * __builtin_fmaf(E.x, a1, __builtin_fmaf(-E.y, b1, a0));
-                const float wi = se[mt] * __builtin_fmaf(E.x, b1, __builtin_fmaf(E.y, a1, b0));
+        for (int nt = 0; nt < kMfNT; ++nt) {
+            const int sl = 16 * nt + col;
+            const float2 E = sa->e[sl];
+            const float a0 = acc[nt][0], b0 = acc[nt][1];
+            const float a1 = acc[nt][2], b1 = acc[nt][3];
+            if (consec) {
+                // z_r = z_0 E^{2g} E^{8 mt} (E for the odd row): Horner in E^8
+                // over the tiles of s (a0 + i b0 + E (a1 + i b1))
+                const float wr = se * __builtin_fmaf(E.x, a1, __builtin_fmaf(-E.y, b1, a0));
+                const float wi = se * __builtin_fmaf(E.x, b1, __builtin_fmaf(E.y, a1, b0));
                 if (mt == kMfMT - 1) {
-                    qr = wr;
-                    qi = wi;
+                    qr[nt] = wr;
+                    qi[nt] = wi;
                 } else {
-                    const float nr = __builtin_fmaf(qr, E8.x, __builtin_fmaf(-qi, E8.y, wr));
-                    const float ni = __builtin_fmaf(qr, E8.y, __builtin_fmaf(qi, E8.x, wi));
-                    qr = nr;
-                    qi = ni;
+                    const float2 E8 = sa->e8[sl];
+                    const float nr = __builtin_fmaf(qr[nt], E8.x, __builtin_fmaf(-qi[nt], E8.y, wr));
+                    const float ni = __builtin_fmaf(qr[nt], E8.y, __builtin_fmaf(qi[nt], E8.x, wi));
+                    qr[nt] = nr;
+                    qi[nt] = ni;
                 }
-            }
-            cmulf(qr, qi, Z.x, Z.y, &hr, &hq);
-        } else {
-            // rows of arbitrary m: one phasor per row (the odd row from the
-            // even one when its m is the next integer)
-            const double spf = sa->pf[sl];
-            hr = 0.0f;
-            hq = 0.0f;
-#pragma unroll
-            for (int mt = 0; mt < kMfMT; ++mt) {
+            } else {
+                // rows of arbitrary m: one phasor per row (the odd row from the
+                // even one when its m is the next integer)
+                const double spf = sa->pf[sl];
                 float zr, zi, yr, yi;
-                phasor_f32((double)me[mt] * spf, &zr, &zi);
-                if (mo[mt] == me[mt] + 1)
+                phasor_f32((double)me * spf, &zr, &zi);
+                if (mo == me + 1)
                     cmulf(zr, zi, E.x, E.y, &yr, &yi);
                 else
-                    phasor_f32((double)mo[mt] * spf, &yr, &yi);
-                const float zsr = zr * se[mt], zsi = zi * se[mt];
-                const float ysr = yr * so[mt], ysi = yi * so[mt];
-                const float a0 = acc[mt][nt][0], b0 = acc[mt][nt][1];
-                const float a1 = acc[mt][nt][2], b1 = acc[mt][nt][3];
-                hr = __builtin_fmaf(zsr, a0, __builtin_fmaf(-zsi, b0, hr));
-                hq = __builtin_fmaf(zsr, b0, __builtin_fmaf(zsi, a0, hq));
-                hr = __builtin_fmaf(ysr, a1, __builtin_fmaf(-ysi, b1, hr));
-                hq = __builtin_fmaf(ysr, b1, __builtin_fmaf(ysi, a1, hq));
+                    phasor_f32((double)mo * spf, &yr, &yi);
+                float hr = 0.0f, hq = 0.0f;
+                if (mt != kMfMT - 1) {
+                    hr = qr[nt];
+                    hq = qi[nt];
+                }
+                zr = zr * se;
+                zi = zi * se;
+                yr = yr * se;
+                yi = yi * se;
+                hr = __builtin_fmaf(zr, a0, __builtin_fmaf(-zi, b0, hr));
+                hq = __builtin_fmaf(zr, b0, __builtin_fmaf(zi, a0, hq));
+                qr[nt] = __builtin_fmaf(yr, a1, __builtin_fmaf(-yi, b1, hr));
+                qi[nt] = __builtin_fmaf(yr, b1, __builtin_fmaf(yi, a1, hq));
             }
         }
-        // the four lane groups hold the other rows of the same sample
-        hr = hr + lane_xchg(bp16, hr);
-        hq = hq + lane_xchg(bp16, hq);
-        hr = hr + lane_xchg(bp32, hr);
-        hq = hq + lane_xchg(bp32, hq);
-        if (g == nt) {
-            hro = hr;
-            hqo = hq;
-        }
     }
+    // Join the lane groups, h = z_0 ((q_0 + E^4 q_2) + E^2 (q_1 + E^4 q_3)).
+    // Swapping halves between tiles P and Q leaves (P: g 0, 1; Q: g 0, 1) in
+    // one register and (P: g 2, 3; Q: g 2, 3) in the other; swapping rows
+    // between the pairs (0, 2) and (1, 3) then leaves lane l with sample l.
+    float hr, hq;
+    {
+        auto join4 = [&](int a, int b, float *yr, float *yi) {
+            float pr = qr[a], pi = qi[a], ur = qr[b], ui = qi[b];
+            lane_swap32(pr, ur);
+            lane_swap32(pi, ui);
+            const float2 E4 = sa->e4[16 * (lane < 32 ? a : b) + col];
+            *yr = __builtin_fmaf(E4.x, ur, __builtin_fmaf(-E4.y, ui, pr));
+            *yi = __builtin_fmaf(E4.x, ui, __builtin_fmaf(E4.y, ur, pi));
+        };
+        float xr, xi, yr, yi;
+        join4(0, 2, &xr, &xi);
+        join4(1, 3, &yr, &yi);
+        lane_swap16(xr, yr);
+        lane_swap16(xi, yi);
+        const float sr = __builtin_fmaf(e2r, yr, __builtin_fmaf(-e2i, yi, xr));
+        const float si = __builtin_fmaf(e2r, yi, __builtin_fmaf(e2i, yr, xi));
+        cmulf(sr, si, z0r, z0i, &hr, &hq);
+    }
+    double dh = 0.0, hh = 0.0;
     if (own) {
         if constexpr (INNER) {
-            const double xr = hro, xi = hqo, dr = dv.x, di = dv.y;
+            const double xr = hr, xi = hq, dr = dv.x, di = dv.y;
             dh = dr * xr + di * xi;
             hh = xr * xr + xi * xi;
         } else {
-            float2 *o = (float2 *)jb.out + jo;
-            *o = make_float2(hro, hqo);
+            ((float2 *)jb.out)[jo] = make_float2(hr, hq);
         }
     }
     // the area is rewritten by the next round only after these reads
@@ -2449,6 +2492,7 @@ __device__ void mf_range(const SumJob &jb, long long lo, long long hi, float4 *l
     // the waves' sample areas follow the operand table in LDS
     MfSampleArea *sa = (MfSampleArea *)((char *)lds + kMfIntervalHalves * sizeof(_Float16)) +
                        threadIdx.x / kWave;
+    sa->c[0][threadIdx.x & (kWave - 1)] = make_float2(1.0f, 0.0f);
     __syncthreads();                                // rows of a previous job no longer read
     if ((int)threadIdx.x < kMfRows) {
         const int r = threadIdx.x;
@@ -2477,15 +2521,15 @@ __device__ void mf_range(const SumJob &jb, long long lo, long long hi, float4 *l
         for (int v = threadIdx.x; v < n4; v += blockDim.x) lds[v] = src[v];
         if ((int)threadIdx.x < kMfRows)
             msc[threadIdx.x] = jb.mscale[(size_t)iv * kMfRows + threadIdx.x];
+        const unsigned long long cls = cptr(jb.mcls)[iv];
         __syncthreads();
         // a wave whose samples of a round all lie past the interval's end (the
         // last round of an interval) skips that round
-        const long long wfirst = (long long)(threadIdx.x / kWave) * kMfSPW;
-        const double ti = jb.t[iv], inv_h = 1.0 / (jb.t[iv + 1] - ti);
-        for (long long base = lo; base < e; base += kMfRound) {
-            if (base + wfirst >= e) continue;           // uniform per wave
+        const double ti = jb.t[iv], inv_h2 = 2.0 / (jb.t[iv + 1] - ti);
+        for (long long base = lo + (long long)(threadIdx.x / kWave) * kMfSPW; base < e;
+             base += kMfRound) {                    // uniform per wave
             const double2 v =
-                mf_round<INNER>(jb, iv, ti, inv_h, base, e, lds, msc, mm, consec, sa);
+                mf_round<INNER>(jb, iv, ti, inv_h2, base, e, lds, msc, mm, cls, consec, sa);
             if constexpr (INNER) {
                 double2 a = iacc[threadIdx.x];
                 a.x = a.x + v.x;
