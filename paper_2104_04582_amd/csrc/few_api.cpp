@@ -363,6 +363,7 @@ class LayoutCache {
         b->n_max = a.n_max;
         b->l_max = a.l_max;
         b->mfma = a.mfma;
+        b->consec = a.consec;
         b->mrows = (int *)std::malloc(sizeof(int) * 2 * (size_t)(a.n_mrows + 1));
         b->segs = (int *)std::malloc(sizeof(int) * 4 * (size_t)a.n_segs);
         b->term_ptr = (int *)std::malloc(sizeof(int) * (size_t)(a.n_terms + 1));
@@ -486,9 +487,8 @@ PrepJob prep_job(const HostReq &r, ReqBase base, double theta, double phi, doubl
     j.fold_blocks = (r.terms.n_terms + j.fold_terms - 1) / j.fold_terms;
     j.segs = at_up<const int4>(r, base, r.L.off_segs);
     j.mrows = at_up<const int2>(r, base, r.L.off_mrows);
-    j.mtab = r.mfma ? at_dev<char>(r, base, r.L.off_mtab) : nullptr;
-    j.mscale = r.mfma ? at_dev<float>(r, base, r.L.off_mscale) : nullptr;
-    j.mcls = r.mfma ? at_dev<unsigned long long>(r, base, r.L.off_mcls) : nullptr;
+    j.mtab = r.mfma ? at_dev<float>(r, base, r.L.off_mtab) : nullptr;
+    j.minfo = r.mfma ? at_dev<MfInfo>(r, base, r.L.off_minfo) : nullptr;
     j.n_mrows = r.terms.n_mrows;
     j.n_min = r.terms.n_min;
     j.n_segs = r.terms.n_segs;
@@ -520,12 +520,12 @@ SumJob sum_job(const HostReq &r, ReqBase base, double t_start, double dt, int64_
     j.wave_base = 0;
     for (int q = 0; q < kTermGroups - 1; ++q) j.grp[q] = r.terms.grp[q];
     j.split = tl.split ? 1 : 0;
-    j.mtab = r.mfma ? at_dev<const char>(r, base, r.L.off_mtab) : nullptr;
-    j.mscale = r.mfma ? at_dev<const float>(r, base, r.L.off_mscale) : nullptr;
-    j.mcls = r.mfma ? at_dev<const unsigned long long>(r, base, r.L.off_mcls) : nullptr;
+    j.mtab = r.mfma ? at_dev<const float>(r, base, r.L.off_mtab) : nullptr;
+    j.minfo = r.mfma ? at_dev<const MfInfo>(r, base, r.L.off_minfo) : nullptr;
     j.mrows = at_up<const int2>(r, base, r.L.off_mrows);
     j.n_mrows = r.terms.n_mrows;
     j.n_min = r.terms.n_min;
+    j.mf_consec = r.terms.consec ? 1 : 0;
     j.sample_base = 0;
     return j;
 }
@@ -1104,7 +1104,7 @@ int sum_impl(few_plan p, few_spline s, double theta, double phi, double scale, d
         const bool mf = s->h.mfma;
         const long long need =
             !inner ? 0 : mf ? (long long)p->mf_wg : inner_slots(tl.parts, (int)slots, p->fp32);
-        // matrix-core requests fold straight into the fp16 operand table
+        // matrix-core requests fold straight into the operand table
         auto prep = [&]() -> hipError_t {
             return mf ? launch_fold_pack(pj, p->stream) : launch_prepare(pj, p->fp32, p->stream);
         };
@@ -1468,25 +1468,29 @@ int launch_batch(few_plan p, Batch *b, hipStream_t s, unsigned *counter) {
         return FEW_OK;
     }
     // vector-path jobs first in the prepare and sum job arrays, then the
-    // matrix-core ones (each set has its own launches)
-    int nv = 0;
-    for (ServedReq *r : b->reqs) nv += r->h.mfma ? 0 : 1;
+    // matrix-core ones, those with rows of consecutive m before the others
+    // (each set has its own summation launch)
+    auto set_of = [](const ServedReq *r) { return !r->h.mfma ? 0 : r->h.terms.consec ? 1 : 2; };
+    int first[4] = {0, 0, 0, 0}, next[3];
+    for (ServedReq *r : b->reqs) ++first[set_of(r) + 1];
+    for (int q = 0; q < 3; ++q) first[q + 1] += first[q];
+    std::copy(first, first + 3, next);
+    const int nv = first[1];
     int max_amp_blocks = 0, max_K = 4, max_fold_blocks = 0, max_K_mf = 4;
-    long long waves = 0, mf_total = 0;
-    int kv = 0, km = nv;
+    long long waves = 0, mf_total[3] = {0, 0, 0};
     for (int i = 0; i < n; ++i) {
         ServedReq *r = b->reqs[i];
         const ReqBase rb{dev + up_off[i], dev + dev_off[i]};
         stage_upload(r->h, host + up_off[i]);
         fj[i] = fit_job(r->h, rb, r->r.phi_phi, r->r.phi_r, r->r.amp);
-        const int k = r->h.mfma ? km++ : kv++;
+        const int set = set_of(r), k = next[set]++;
         pj[k] = prep_job(r->h, rb, r->r.theta, r->r.phi, r->r.scale, r->r.t_start, r->r.dt,
                          r->r.n_samples, fp32, Tiling{1, 0});
         sj[k] = sum_job(r->h, rb, r->r.t_start, r->r.dt, r->r.n_samples, r->r.out,
                         Tiling{1, 0});
-        if (r->h.mfma) {
-            sj[k].sample_base = mf_total;
-            mf_total += r->r.n_samples;
+        if (set > 0) {
+            sj[k].sample_base = mf_total[set];
+            mf_total[set] += r->r.n_samples;
             max_K_mf = std::max(max_K_mf, r->h.K);
         } else {
             sj[k].wave_base = (int)waves;
@@ -1505,10 +1509,11 @@ int launch_batch(few_plan p, Batch *b, hipStream_t s, unsigned *counter) {
         HIP_TRY(launch_prepare_batch(pd, nv, max_fold_blocks, fp32, s));
         HIP_TRY(launch_sum_batch(sd, nv, (int)waves, fp32, true, counter, s));
     }
-    if (nv < n) {
-        HIP_TRY(launch_fold_pack_batch(pd + nv, n - nv, max_K_mf, s));
-        HIP_TRY(launch_sum_mfma_batch(sd + nv, n - nv, mf_total, p->mf_wg, s));
-    }
+    if (nv < n) HIP_TRY(launch_fold_pack_batch(pd + nv, n - nv, max_K_mf, s));
+    for (int set = 1; set < 3; ++set)
+        if (first[set + 1] > first[set])
+            HIP_TRY(launch_sum_mfma_batch(sd + first[set], first[set + 1] - first[set],
+                                          mf_total[set], set == 1, p->mf_wg, s));
     b->done = sync_event(p);
     if (!b->done) return fail(FEW_E_HIP, "event creation failed");
     HIP_TRY(hipEventRecord(b->done, s));

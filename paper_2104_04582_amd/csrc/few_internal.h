@@ -93,13 +93,17 @@ inline int split_tile_samples() { return kWave * kSamplesPerLaneF32; }
 // coefficient rows are added into one (the product is linear in them).
 // Fixed shape: kMfMT tiles of 16 matrix rows (8 signed m each), kMfT steps of
 // 32 columns (16 values of |n| each; |n| < 16 kMfT), kMfNT tiles of 16
-// samples per wave, kMfWaves waves per workgroup.  A request takes this
+// samples (one sample per lane) per wave and round, kMfWaves waves per
+// workgroup, one workgroup per compute unit: two waves per SIMD, so that a
+// wave can keep a block's operands (72 registers) and its sums in the 256
+// registers it then has (with 12 waves and 168 registers the block operands
+// spill: 426 against 388 us on 12.6 million samples).  A request takes this
 // path when its term layout fits the shape and is long enough to repay it.
 #ifndef FEW_MF_NT
 #define FEW_MF_NT 4
 #endif
 #ifndef FEW_MF_WAVES
-#define FEW_MF_WAVES 12
+#define FEW_MF_WAVES 8
 #endif
 constexpr int kMfMT = 3;
 constexpr int kMfT = 2;
@@ -107,9 +111,17 @@ constexpr int kMfNT = FEW_MF_NT;
 constexpr int kMfWaves = FEW_MF_WAVES;
 constexpr int kMfRows = 8 * kMfMT;          // signed m values per request
 constexpr int kMfA = 16 * kMfT;             // |n| < kMfA
-constexpr int kMfRound = kMfWaves * kMfNT * 16;   // samples per workgroup round
-// fp16 values of one interval: [mt][p 4][t][hi, lo][lane 64][8]
-constexpr size_t kMfIntervalHalves = (size_t)4 * kMfMT * kMfT * 2 * 64 * 8;
+constexpr int kMfRound = kMfWaves * kMfNT * 16;   // samples per workgroup round (static tables)
+// operand values of one interval, binary32: [mt][p 4][t][lane 64][8]
+constexpr size_t kMfIntervalFloats = (size_t)kMfMT * 4 * kMfT * 64 * 8;
+// What the summation needs to know of an interval's values: the scale of each
+// pair of signed m rows, and an upper bound of the largest |scaled value| of
+// every fragment (the leading 16 bits of a binary32 value, rounded up).
+struct MfInfo {
+    float scale[kMfRows / 2];
+    unsigned short top[kMfMT * 4 * kMfT];   // [mt][p][t]
+};
+static_assert(sizeof(MfInfo) == 96, "4-byte granularity, no padding");
 constexpr int kMfMinTerms = 480;            // below this the vector kernel is cheaper
 
 // ---------------------------------------------------------------------------
@@ -168,13 +180,11 @@ struct PrepJob {
     int short_tile;         // samples per short tile
     int fold_terms;         // consecutive terms folded by one workgroup
     int fold_blocks;        // term groups of the fold
-    // matrix-core path: the fold writes the fp16 operand table and the
-    // per-(interval, row) scales
+    // matrix-core path: the fold writes the operand table and its scales
     const int4 *segs;       // [n_segs]
     const int2 *mrows;      // [n_mrows + 1]: (m, first segment) per row, sentinel (0, n_segs)
-    void *mtab;             // [K-1][kMfIntervalHalves] fp16
-    float *mscale;          // [K-1][kMfRows]: 2^E with row values scaled by 2^-E
-    unsigned long long *mcls;   // [K-1]: fragment classes, 16 bits per row tile
+    float *mtab;            // [K-1][kMfIntervalFloats]: values of a row pair times 2^-E
+    MfInfo *minfo;          // [K-1]
     int n_mrows, n_min, n_segs;
     int l_max;              // largest listed l
 };
@@ -211,11 +221,11 @@ struct SumJob {
     int grp[kTermGroups - 1];   // first segment of term groups 1..3 (binary32)
     int split;              // short tiles are term-split tiles
     // matrix-core path
-    const void *mtab;       // [K-1][kMfIntervalHalves] fp16 operand table
-    const float *mscale;    // [K-1][kMfRows]
-    const unsigned long long *mcls;     // [K-1]
+    const float *mtab;      // [K-1][kMfIntervalFloats] operand values
+    const MfInfo *minfo;    // [K-1]
     const int2 *mrows;      // [n_mrows + 1]
     int n_mrows, n_min;
+    int mf_consec;          // rows of consecutive signed m
     long long sample_base;  // first sample of this job in a batched launch's range
     // matrix-core store launches: XCD split weights (all 0: equal split), and
     // where each workgroup reports (tag << kMfTagShift | its time), or nullptr
@@ -258,7 +268,7 @@ hipError_t launch_sum_batch(const SumJob *jobs_dev, int n_jobs, int total_wave_s
                             bool fp32, bool persistent, unsigned *counter_dev,
                             hipStream_t stream);
 hipError_t launch_zero_u32(unsigned *p, int n, hipStream_t stream);
-// Matrix-core path: the prepare step (interval starts, fold and the fp16
+// Matrix-core path: the prepare step (interval starts, fold and the
 // operand table, one request or n_jobs of them with max_K knots at most), and
 // the summation (every workgroup takes an equal contiguous share of the
 // samples; n_wg workgroups; with INNER each writes its partial sums to
@@ -271,7 +281,7 @@ hipError_t launch_sum_mfma(const SumJob &job, int n_wg, hipStream_t stream);
 hipError_t launch_sum_mfma_inner(const SumJob &job, int n_wg, double two_dt, double *out2,
                                  hipStream_t stream);
 hipError_t launch_sum_mfma_batch(const SumJob *jobs_dev, int n_jobs, long long total,
-                                 int n_wg, hipStream_t stream);
+                                 bool consec, int n_wg, hipStream_t stream);
 hipError_t launch_select(const double *amp, int K, int M, double eps, bool sorted, int *keep,
                          hipStream_t stream);
 constexpr int kMaxSelectModes = 4096;   // LDS: (binary64 key + int index) per padded mode
@@ -290,6 +300,7 @@ struct TermLayout {
     // matrix-core path: distinct signed m values (rows) and the n range
     int n_mrows = 0, n_min = 0, n_max = 0, l_max = 0;
     int *mrows = nullptr;      // 2 * (n_mrows + 1): (m, first segment), sentinel (0, n_segs)
+    bool consec = false;       // those m are consecutive
     bool mfma = false;         // layout fits the matrix-core shape (Schwarzschild terms)
 };
 
@@ -336,11 +347,11 @@ struct ReqLayout {
     size_t off_t, off_segs, off_term_ptr, off_term_src, off_chunks, off_mrows,
         upload_end;   // host-staged
     size_t off_pcoef, off_acoef, off_ybuf, off_table, off_starts, off_tile_pref, off_mtab,
-        off_mscale, off_mcls, total;
+        off_minfo, total;
     size_t dev_begin;       // first device-produced offset (== off_pcoef)
 };
-// mfma: binary32 request on the matrix-core path (binary64 fold table, fp16
-// operand table and row scales; n_mrows rows)
+// mfma: binary32 request on the matrix-core path (binary32 operand table in
+// place of the fold table; n_mrows rows)
 ReqLayout request_layout(bool fp32, int K, int M, int n_segs, int n_terms, int n_src,
                          int n_chunks, int n_ph, bool mfma = false, int n_mrows = 0);
 

@@ -194,6 +194,7 @@ int build_term_layout(int M, const int32_t *modes, int width, int max_gap, TermL
         mr.push_back(0);
         mr.push_back(n_seg);
         out->n_mrows = (int)mr.size() / 2 - 1;
+        out->consec = mr[2 * (out->n_mrows - 1)] - mr[0] == out->n_mrows - 1;
         int lm = 0;
         for (int k = 0; k < M; ++k) lm = std::max(lm, (int)modes[(size_t)width * k]);
         out->l_max = lm;
@@ -285,13 +286,12 @@ ReqLayout request_layout(bool fp32, int K, int M, int n_segs, int n_terms, int n
     L.off_acoef = take(sizeof(double) * 8 * (size_t)(K - 1) * M);
     L.off_ybuf = take(sizeof(double) * 2 * (size_t)std::max(n_src, 1));
     // fold table of the vector kernels (matrix-core requests fold straight
-    // into the fp16 operand table)
+    // into the operand table)
     L.off_table = take(mfma ? 0 : (fp32 ? 4 : 8) * 8 * (size_t)(K - 1) * n_terms);
     L.off_starts = take(sizeof(long long) * K);
     L.off_tile_pref = take(sizeof(int) * kParts * (size_t)K);
-    L.off_mtab = take(mfma ? sizeof(uint16_t) * kMfIntervalHalves * (size_t)(K - 1) : 0);
-    L.off_mscale = take(mfma ? sizeof(float) * kMfRows * (size_t)(K - 1) : 0);
-    L.off_mcls = take(mfma ? sizeof(unsigned long long) * (size_t)(K - 1) : 0);
+    L.off_mtab = take(mfma ? sizeof(float) * kMfIntervalFloats * (size_t)(K - 1) : 0);
+    L.off_minfo = take(mfma ? sizeof(MfInfo) * (size_t)(K - 1) : 0);
     L.total = o;
     return L;
 }

@@ -14,7 +14,7 @@
 //                  refinement step, scan solves).
 //  fold_pack_kernel  matrix-core requests: interval starts; per interval and
 //                  row tile, -2Y_lm, the fold of the l-sum, the row scales and
-//                  the fp16 hi/lo operand table.
+//                  the operand table of the products.
 //  prepare_kernel  vector-path requests: interval starts and tile prefixes;
 //                  -2Y_lm and the fold of the l-sum into one complex cubic per
 //                  signed (m, [k,] n) term.
@@ -1821,7 +1821,7 @@ typedef float mf_float4 __attribute__((ext_vector_type(4)));
 // Fold and pack for the matrix-core path: workgroup 0 computes the interval
 // starts and tile prefixes; each other workgroup folds one interval iv for
 // one row tile mt (rows 8 mt .. 8 mt + 7, the signed m values m_r; numbering
-// below) and writes its part of the fp16 operand table.
+// below) and writes its part of the operand table.
 //
 // Fold (Eqs. (9)-(10) for fixed viewing angles, Sec. IV): every term (m_r, n)
 // is C = scale sum_contributors w A, with w = -2Y_{l, m_r} for a listed mode
@@ -1840,22 +1840,17 @@ typedef float mf_float4 __attribute__((ext_vector_type(4)));
 // (Im P + Im Q, Re P - Re Q) (Q = 0 for a = 0).  Each pair of rows (signed m
 // rows 2j and 2j + 1, which one lane of the product holds) is scaled by
 // 2^-E, E the exponent of the pair's largest |coefficient| on the interval
-// (so scaled values stay below 2), and split into hi = fp16(v) and
-// lo = fp16(v - hi), both from binary64.  Table layout, per interval:
-// [mt][3 - p][t][hi, lo][lane 64][8 values] (p descending, the order of the
-// Horner recurrence that reads it), lane l's operand fragment of
+// (so scaled values stay below 2), and stored in binary32; the summation cuts
+// the values into fp16 hi and lo parts.  (One scale per interval would save
+// the sum's multiplies, but the lo parts of the small rows then fall into fp16
+// subnormals: error 5.1e-7 against 4.5e-7 on the one-year case.)  Layout, per
+// interval: [mt][p][t][lane 64][8 values], lane l's operand fragment of
 // v_mfma_f32_16x16x32_f16: matrix row l % 16 of the tile, columns
-// a = 16 t + 4 (l / 16) + i / 2 and c = i % 2 for value i.
-// Class of a fragment (row tile, power p, step t), two bits: bit 0 set if it
-// holds a nonzero value, bit 1 if some |value| reaches kMfSmall = 2^-12 (of the
-// row pair's scale), when all three hi/lo products are formed.  Below it, only
-// hi * hi is: there hi = fp16(v) alone resolves v to 2^-24 of the scale, the
-// resolution that hi + lo gives values near the scale, and the lo part of the
-// harmonics (below 2^-12 of their modulus 1) would add less than 2^-24 too,
-// the size of the lo * lo products that are left out everywhere.  A spline's
-// higher powers are small on smooth data: at 100 knots over a year p = 2, 3
-// take one product, so 8 products are formed instead of 12.
-constexpr double kMfSmall = 0x1p-12;
+// a = 16 t + 4 (l / 16) + i / 2 and c = i % 2 for value i.  MfInfo holds 2^E
+// and the largest |scaled value| of every fragment (mt, p, t), from which the
+// summation decides which products a fragment needs (found as bit patterns: a
+// NaN counts as the largest value, so it is never left out).
+constexpr int kFoldPackThreads = 512;
 constexpr int kFoldSegs = 64;                       // segments of a row tile kept in LDS
 
 __device__ void fold_pack_body(const PrepJob &jb, int b) {
@@ -1878,7 +1873,6 @@ __device__ void fold_pack_body(const PrepJob &jb, int b) {
     __shared__ int rowmv[8];                        // m_r of the tile's rows
     __shared__ double2 trig[9];                     // (cos, sin) of theta / 2 and of m_r phi
     __shared__ int2 segv[kFoldSegs];
-    __shared__ int fcls[4 * kMfT];
     const int tid = threadIdx.x;
     const int r0 = 8 * mt;
     // the tile's segments [g0, g1); its terms are one contiguous run [t0, t1)
@@ -2040,17 +2034,17 @@ __device__ void fold_pack_body(const PrepJob &jb, int b) {
                 ms = (float)ldexp(1.0, e);
             }
             rsc[k] = sc;
-            jb.mscale[(size_t)iv * kMfRows + r0 + k] = ms;
+            if ((k & 1) == 0) jb.minfo[iv].scale[(r0 + k) >> 1] = ms;
         }
     }
     __syncthreads();
-    _Float16 *dst = (_Float16 *)jb.mtab + (size_t)iv * kMfIntervalHalves;
+    float *dst = jb.mtab + ((size_t)iv * kMfMT + mt) * (4 * kMfT * 512);
     for (int it = tid; it < 4 * kMfT * 64; it += blockDim.x) {
         const int ln = it & 63, t = (it >> 6) % kMfT, p = (it >> 6) / kMfT;   // one wave: one (p, t)
         const int kk = (ln & 15) >> 1, comp = ln & 1, g = ln >> 4;
         const double sc = rsc[kk];
-        mf_half8 hi, lo;
-        bool any = false, big = false;
+        float o[8];
+        unsigned big = 0;
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
             const int a = 16 * t + 4 * g + j;
@@ -2060,35 +2054,18 @@ __device__ void fold_pack_body(const PrepJob &jb, int b) {
                 qr = cf[kk][-a + kMfA - 1][2 * p];
                 qi = cf[kk][-a + kMfA - 1][2 * p + 1];
             }
-#pragma unroll
-            for (int c = 0; c < 2; ++c) {
-                double v;
-                if (comp == 0)
-                    v = c == 0 ? pr + qr : qi - pi;
-                else
-                    v = c == 0 ? pi + qi : pr - qr;
-                v = v * sc;
-                any = any || v != 0.0;
-                big = big || !(fabs(v) < kMfSmall);
-                // through binary32 (one instruction each way; the pair still
-                // carries about 22 bits: lo takes the exact binary64 residual)
-                const _Float16 hv = (_Float16)(float)v;
-                hi[2 * j + c] = hv;
-                lo[2 * j + c] = (_Float16)(float)(v - (double)hv);
-            }
+            o[2 * j] = (float)((comp == 0 ? pr + qr : pi + qi) * sc);
+            o[2 * j + 1] = (float)((comp == 0 ? qi - pi : pr - qr) * sc);
+            big = max(big, max(__float_as_uint(o[2 * j]) & 0x7fffffffu,
+                               __float_as_uint(o[2 * j + 1]) & 0x7fffffffu));
         }
-        const size_t at =
-            ((((size_t)mt * 4 + (3 - p)) * kMfT + t) * 2) * 512 + (size_t)ln * 8;
-        *(mf_half8 *)(dst + at) = hi;
-        *(mf_half8 *)(dst + at + 512) = lo;
-        const int fc = (__ballot(any) ? 1 : 0) | (__ballot(big) ? 2 : 0);
-        if (ln == 0) fcls[p * kMfT + t] = fc;
-    }
-    __syncthreads();
-    if (tid == 0) {
-        unsigned w = 0;
-        for (int f = 0; f < 4 * kMfT; ++f) w |= (unsigned)fcls[f] << (2 * f);
-        ((unsigned short *)jb.mcls)[(size_t)iv * 4 + mt] = (unsigned short)w;
+        float4 *d = (float4 *)(dst + ((size_t)p * kMfT + t) * 512 + (size_t)ln * 8);
+        d[0] = make_float4(o[0], o[1], o[2], o[3]);
+        d[1] = make_float4(o[4], o[5], o[6], o[7]);
+        for (int off = kWave / 2; off > 0; off >>= 1) big = max(big, (unsigned)__shfl_xor((int)big, off));
+        if (ln == 0)
+            jb.minfo[iv].top[(mt * 4 + p) * kMfT + t] =
+                (unsigned short)min((big + 0xffffu) >> 16, 0x7fffu);
     }
 }
 
@@ -2096,7 +2073,6 @@ __device__ void fold_pack_body(const PrepJob &jb, int b) {
 // dominate), two operand items per lane in the pack; at most 128 registers,
 // so two workgroups fit a compute unit (the grid is slightly larger than the
 // number of compute units).
-constexpr int kFoldPackThreads = 512;
 
 __global__ __launch_bounds__(kFoldPackThreads) __attribute__((amdgpu_waves_per_eu(4)))
 void fold_pack_kernel(PrepJob jb) {
@@ -2149,39 +2125,41 @@ __device__ __forceinline__ void phasor_f32(double v, float *re, float *im) {
     *im = -sv;
 }
 
-// fp16 hi/lo parts of binary32 values, hi = fp16(a), lo = fp16(a - hi) (the
-// difference is exact in binary32): about 22 significant bits together.
-// Here for a pair, packed as two fp16 values per 32-bit word: both hi
-// parts by one packed conversion (round to nearest even), each lo part by one
-// mixed-precision multiply-add a * 1 - hi that reads hi as fp16 and writes its
-// fp16 result into one half of the lo word (written out because the compiler
-// otherwise forms each lo in binary32 and packs the pair again).
+// fp16 hi/lo parts of a pair of binary32 values, packed as two fp16 values per
+// 32-bit word: hi = fp16(a), lo = fp16(a - hi) (the difference is exact in
+// binary32), about 22 significant bits together.  The differences read the
+// packed hi halves directly (v_fma_mix_f32, written out because the compiler
+// unpacks them first).  Four instructions of 4.4 clocks per pair; forming lo
+// with v_fma_mixlo_f16 / mixhi takes one instruction less but those issue every
+// 8.4 clocks (rates measured with three waves per SIMD).
 typedef _Float16 mf_half2 __attribute__((ext_vector_type(2)));
 typedef float mf_f2 __attribute__((ext_vector_type(2)));
 typedef unsigned mf_u4 __attribute__((ext_vector_type(4)));
-__device__ __forceinline__ void split_pair(float a0, float a1, unsigned &hi, unsigned &lo) {
-    hi = __builtin_bit_cast(unsigned, __builtin_convertvector((mf_f2){a0, a1}, mf_half2));
-    unsigned l;
-    asm("v_fma_mixlo_f16 %0, %1, 1.0, -%2 op_sel_hi:[0,0,1]" : "=v"(l) : "v"(a0), "v"(hi));
-    asm("v_fma_mixhi_f16 %0, %1, 1.0, -%2 op_sel:[0,0,1] op_sel_hi:[0,0,1]"
-        : "+v"(l)
-        : "v"(a1), "v"(hi));
-    lo = l;
+__device__ __forceinline__ unsigned pack_half2(float a0, float a1) {
+    return __builtin_bit_cast(unsigned, __builtin_convertvector((mf_f2){a0, a1}, mf_half2));
 }
-
+__device__ __forceinline__ void split_pair(float a0, float a1, unsigned &hi, unsigned &lo) {
+    const unsigned h = pack_half2(a0, a1);
+    float l0, l1;
+    asm("v_fma_mix_f32 %0, %1, 1.0, -%2 op_sel_hi:[0,0,1]" : "=v"(l0) : "v"(a0), "v"(h));
+    asm("v_fma_mix_f32 %0, %1, 1.0, -%2 op_sel:[0,0,1] op_sel_hi:[0,0,1]"
+        : "=v"(l1)
+        : "v"(a1), "v"(h));
+    hi = h;
+    lo = pack_half2(l0, l1);
+}
 
 // Per-wave LDS area of the per-sample values of one round (64 samples, one per
 // lane): f = e^{-i Phi_r} and its powers f^2, f^3 (steps inside a lane group's
 // four columns), f^{4g} (g = 0..3, the group's first column; g = 0 stays 1),
-// f^16; E = e^{-i Phi_phi}, E^4 and E^8; the interval coordinate v in [-1, 1];
-// Phi_phi itself (rows of arbitrary m).
+// f^16; E = e^{-i Phi_phi}, E^4 and E^8 (for rows of arbitrary m the reduced
+// Phi_phi, binary64, in place of E^8); the coefficient variable v (or s).
 constexpr int kMfSPW = kMfNT * 16;                  // samples per wave and round
 static_assert(kMfNT == 4, "one sample per lane");
 struct MfSampleArea {
     float2 f[kMfSPW], f2[kMfSPW], f3[kMfSPW], f16[kMfSPW], c[4][kMfSPW];
     float2 e[kMfSPW], e4[kMfSPW], e8[kMfSPW];
     float v[kMfSPW];
-    double pf[kMfSPW];
 };
 
 // Exchange of the upper 32 lanes of a with the lower 32 of b, and of the odd
@@ -2199,147 +2177,383 @@ __device__ __forceinline__ void lane_swap16(float &a, float &b) {
     b = __builtin_bit_cast(float, (unsigned)r[1]);
 }
 
-// One wave-round: the 64 samples wbase + s (s = lane, valid below e) in four
-// tiles of 16.  Every lane first forms the values of its own sample (phases,
-// harmonics and their powers) into the wave's LDS area; in tile nt the four
-// lane groups g = l / 16 of column c read what they need of sample 16 nt + c
-// from there.  Group g holds the operand columns |n| = 16 t + 4 g + j, j < 4,
-// of step t: f^{16 t + 4 g} times f^j (the same fragment serves n and -n).
-// The row tiles are taken one after the other, the highest first: the
-// accumulators of a tile (16 registers) run a Horner recurrence in v over
-// p = 3 .. 0, then the lane's two rows are combined and added into its
-// running value by a Horner recurrence in E^8.  cls: two bits per (tile,
-// power, step) fragment of the operand table, see fold_pack_body.  The four
-// lane groups of a column are joined by swapping lanes between tiles (two
-// tiles at a time, so that each instruction combines two tiles), after which
-// lane l holds sample l.  Returns this lane's binary64 inner-product sums
-// (INNER) or stores h.  The LDS accesses of one wave complete in order, so its
-// area needs no barrier.
-template <bool INNER>
-__device__ __forceinline__ double2 mf_round(const SumJob &jb, int iv, double ti, double inv_h2,
-                                            long long wbase, long long e, const float4 *lds,
-                                            const float *msc, const int *mm,
-                                            unsigned long long cls, bool consec,
-                                            MfSampleArea *sa) {
-    const int lane = threadIdx.x & (kWave - 1);
-    const int g = lane >> 4, col = lane & 15;
-    const FEW_AS4 double *pc = cptr(jb.pcoef) + (size_t)iv * 16;
-    const int m0 = mm[0], am0 = m0 < 0 ? -m0 : m0;
-    const long long jo = wbase + lane;
-    const bool own = jo < e;
-    // INNER: the sample's data, requested first so that its latency passes
-    // under the round's products
-    // (every lane loads, at a clamped index, so that the load is not under a
-    // branch, which would make the compiler wait for it at the join)
-    float2 dv = make_float2(0.0f, 0.0f);
-    if constexpr (INNER) dv = ((const float2 *)jb.data)[min(jo, e - 1)];
-    // this lane's sample -> the wave's area.  z0 = e^{-i m_0 Phi_phi} and E^2
-    // stay in registers: the same lane holds the sample at the end.
-    float z0r = 1.0f, z0i = 0.0f, e2r = 1.0f, e2i = 0.0f;
-    {
-        const double tj = dev_sample_time(jb.t_start, jb.dt, min(jo, e - 1));
-        const double x = tj - ti;
-        const double pf = phase_raw(pc, x);
-        const double pr = phase_raw(pc + 8, x);
-        float er, ei, fr, fi;
-        phasor_f32(pf, &er, &ei);
-        phasor_f32(pr, &fr, &fi);
-        float f2r, f2i, f3r, f3i, f4r, f4i, f8r, f8i, f12r, f12i, f16r, f16i;
-        cmulf(fr, fi, fr, fi, &f2r, &f2i);
-        cmulf(f2r, f2i, fr, fi, &f3r, &f3i);
-        cmulf(f2r, f2i, f2r, f2i, &f4r, &f4i);
-        cmulf(f4r, f4i, f4r, f4i, &f8r, &f8i);
-        cmulf(f8r, f8i, f4r, f4i, &f12r, &f12i);
-        cmulf(f8r, f8i, f8r, f8i, &f16r, &f16i);
-        sa->v[lane] = (float)fma(x, inv_h2, -1.0);
-        sa->f[lane] = make_float2(fr, fi);
-        sa->f2[lane] = make_float2(f2r, f2i);
-        sa->f3[lane] = make_float2(f3r, f3i);
-        sa->f16[lane] = make_float2(f16r, f16i);
-        sa->c[1][lane] = make_float2(f4r, f4i);
-        sa->c[2][lane] = make_float2(f8r, f8i);
-        sa->c[3][lane] = make_float2(f12r, f12i);
-        sa->e[lane] = make_float2(er, ei);
-        if (consec) {
-            // Rows of consecutive m (m_r = m_0 + r): every z_r is a power of
-            // E = e^{-i Phi_phi}.  z_0 = E^{m_0} by binary powering (E^{-1} =
-            // conj E), so each z_r carries m_r times the phase error of E, at
-            // most max |m| of it.
-            float e4r, e4i, e8r, e8i;
-            cmulf(er, ei, er, ei, &e2r, &e2i);
-            cmulf(e2r, e2i, e2r, e2i, &e4r, &e4i);
-            cmulf(e4r, e4i, e4r, e4i, &e8r, &e8i);
-            float br = e8r, bi = e8i;
-            auto take = [&](float qr, float qi) {
-                float nr, ni;
-                cmulf(z0r, z0i, qr, qi, &nr, &ni);
-                z0r = nr;
-                z0i = ni;
-            };
-            if (am0 & 1) take(er, ei);
-            if (am0 & 2) take(e2r, e2i);
-            if (am0 & 4) take(e4r, e4i);
-            for (int bit = 8; bit <= am0; bit <<= 1) {
-                if (am0 & bit) take(br, bi);
-                float nr, ni;
-                cmulf(br, bi, br, bi, &nr, &ni);
-                br = nr;
-                bi = ni;
-            }
-            if (m0 < 0) z0i = -z0i;
-            sa->e4[lane] = make_float2(e4r, e4i);
-            sa->e8[lane] = make_float2(e8r, e8i);
-        } else {
-            // rows of arbitrary m carry their whole phase themselves
-            sa->e4[lane] = make_float2(1.0f, 0.0f);
-            sa->pf[lane] = d_reduce_2pi(pf);
-        }
+// A wave-uniform value in scalar registers.
+__device__ __forceinline__ float uniform_f32(float v) {
+    return __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, v)));
+}
+__device__ __forceinline__ double uniform_f64(double v) { return lane_value(v, 0); }
+
+// How the products of an interval are formed.
+//
+// Static tables.  A fragment (row tile mt, power p, step t) takes all three
+// hi/lo products if some |value| reaches kMfSmall = 2^-12 of its row pair's
+// scale S (the power of two above the pair's largest coefficient), else
+// hi * hi alone, and none if it holds only zeros.  Below 2^-12, hi = fp16(value)
+// alone resolves it to 2^-24 of the scale, the resolution that hi + lo gives
+// values near the scale, and the lo part of the harmonics (below 2^-12 of
+// their modulus 1) would add less than 2^-24 too, the size of the lo * lo
+// products that are left out everywhere.  A spline's higher powers are small
+// on smooth data: at 100 knots over a year p = 2 and 3 take one product each,
+// 8 in place of 12.
+//
+// Blocks.  Where the data allow it, the cubic is written about the centre v_0
+// of a block of consecutive samples, in s = (v - v_0) / w in [-1, 1], w the
+// block's half width in v:
+//   C(v) = T_0 + s T_1,  T_0 = b_0 + v_0 b_1 + (v_0^2 + w^2/2) b_2 + (v_0^3 + 3 w^2 v_0 / 2) b_3,
+//   T_1 = w (b_1 + 2 v_0 b_2 + (3 v_0^2 + 3 w^2 / 4) b_3)
+// (s^2 replaced by 1/2 and s^3 by 3 s / 4, their best constant and linear
+// approximations), which is off by at most (|b_2| + 3 |b_3|) w^2 / 2 + |b_3|
+// w^3 / 4.  Blocks are as long as keeps that below kMfBlockRest = 2^-25 S and
+// |T_1| below kMfBlockSlope = 2^-11 S in every fragment; T_1 then needs one
+// product (what is left out stays below 2^-23 S |s|), so a block takes 4
+// products and one Horner step in place of 8 to 12 and 3.  The launch is
+// limited by power, which goes with the products (one set of them cost 28.5 us
+// on 12.6 million samples, everything else 270 us).  The 72 registers of
+// T_0 (hi, lo) and T_1 stay in the wave, which forms them from the interval's
+// binary32 values (staged in LDS) whenever its samples enter another block:
+// about 400 vector instructions, against 560 for a round of 64 samples.  Sharing the tables
+// between waves through LDS instead, formed one block ahead, cost more in
+// barriers and reads than it saved (644 us against 515 with static tables).
+constexpr float kMfSmall = 0x1p-12f;
+constexpr float kMfBlockRest = 0x1p-25f;
+constexpr float kMfBlockSlope = 0x1p-11f;
+constexpr int kMfMinBlock = 2;          // shortest block, in rounds of 64 samples
+constexpr int kMfMaxBlock = 1 << 20;
+
+// Per-interval values.
+struct MfInterval {
+    double ti, inv_h2;      // knot time, 2 / h
+    unsigned any, big;      // static tables: bit (mt * 4 + p) * kMfT + t
+    int block;              // rounds per block, 0: static tables
+    long long first;        // first sample of the interval
+};
+
+// LDS: the static table, [mt][3 - p][t][hi, lo][lane 64][8 fp16], or the
+// interval's binary32 values, [mt][p][t][half of 4 values][lane 64].
+constexpr size_t kMfTableBytes = kMfIntervalFloats * sizeof(float);
+
+// The interval's binary32 values staged for the blocks.
+__device__ __forceinline__ void mf_stage(const float *tab, float4 *lds) {
+    for (int v = threadIdx.x; v < (int)(kMfIntervalFloats / 4); v += blockDim.x)
+        lds[(v & ~127) | (v & 1) << 6 | ((v >> 1) & 63)] = ((const float4 *)tab)[v];
+}
+
+// The static table of an interval (8 values of one fragment per lane and step).
+__device__ __forceinline__ void mf_build_static(const float *tab, float4 *lds) {
+    for (int it = threadIdx.x; it < kMfMT * 4 * kMfT * 64; it += blockDim.x) {
+        const int ln = it & 63, f = it >> 6, t = f % kMfT, p = (f / kMfT) & 3, mt = f / (4 * kMfT);
+        const float4 a = ((const float4 *)tab)[2 * it], b = ((const float4 *)tab)[2 * it + 1];
+        unsigned hi[4], lo[4];
+        split_pair(a.x, a.y, hi[0], lo[0]);
+        split_pair(a.z, a.w, hi[1], lo[1]);
+        split_pair(b.x, b.y, hi[2], lo[2]);
+        split_pair(b.z, b.w, hi[3], lo[3]);
+        uint4 *d = (uint4 *)lds + (size_t)(((mt * 4 + (3 - p)) * kMfT + t) * 2) * 64 + ln;
+        d[0] = make_uint4(hi[0], hi[1], hi[2], hi[3]);
+        d[64] = make_uint4(lo[0], lo[1], lo[2], lo[3]);
     }
-    __builtin_amdgcn_wave_barrier();
-    // operands: powers of f for every tile and step (fp16 pairs per word)
-    mf_u4 bh[kMfNT][kMfT], bl[kMfNT][kMfT];
-    float vv[kMfNT];
+}
+
+// The operand registers of a block: T_0 (hi, lo) and T_1 per row tile and step.
+struct MfBlock {
+    mf_u4 t1[kMfMT][kMfT], h0[kMfMT][kMfT], l0[kMfMT][kMfT];
+};
+
+// Form them for block centre v0 and half width w from the staged values.
+__device__ __forceinline__ void mf_block_form(const float4 *lds, double v0, double w, MfBlock &B) {
+    const int lane = threadIdx.x & (kWave - 1);
+    const double vv = v0 * v0, ww = w * w;
+    const float k1 = uniform_f32((float)v0), k2 = uniform_f32((float)fma(0.5, ww, vv)),
+                k3 = uniform_f32((float)(v0 * fma(1.5, ww, vv)));
+    const float q1 = uniform_f32((float)w), q2 = uniform_f32((float)(w * 2.0 * v0)),
+                q3 = uniform_f32((float)(w * fma(0.75, ww, 3.0 * vv)));
+    const float4 *src = lds + lane;
 #pragma unroll
-    for (int nt = 0; nt < kMfNT; ++nt) {
-        const int sl = 16 * nt + col;
-        vv[nt] = sa->v[sl];
-        const float2 f1 = sa->f[sl], f2 = sa->f2[sl], f3 = sa->f3[sl], fs = sa->f16[sl];
-        const float2 c0 = sa->c[g][sl];
-        float w[8];
-        w[0] = c0.x;
-        w[1] = c0.y;
-        cmulf(c0.x, c0.y, f1.x, f1.y, &w[2], &w[3]);
-        cmulf(c0.x, c0.y, f2.x, f2.y, &w[4], &w[5]);
-        cmulf(c0.x, c0.y, f3.x, f3.y, &w[6], &w[7]);
+    for (int mt = 0; mt < kMfMT; ++mt)
 #pragma unroll
         for (int t = 0; t < kMfT; ++t) {
-            if (t > 0) {
+            float4 b[4][2];
 #pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    float nr, ni;
-                    cmulf(w[2 * i], w[2 * i + 1], fs.x, fs.y, &nr, &ni);
-                    w[2 * i] = nr;
-                    w[2 * i + 1] = ni;
-                }
+            for (int p = 0; p < 4; ++p) {
+                const float4 *q = src + ((mt * 4 + p) * kMfT + t) * 128;
+                b[p][0] = q[0];
+                b[p][1] = q[64];
+            }
+            const float *b0 = (const float *)b[0], *b1 = (const float *)b[1];
+            const float *b2 = (const float *)b[2], *b3 = (const float *)b[3];
+            float T0[8], T1[8];
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                T0[i] = __builtin_fmaf(k3, b3[i], __builtin_fmaf(k2, b2[i], __builtin_fmaf(k1, b1[i], b0[i])));
+                T1[i] = __builtin_fmaf(q3, b3[i], __builtin_fmaf(q2, b2[i], q1 * b1[i]));
             }
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
                 unsigned h, l;
-                split_pair(w[2 * i], w[2 * i + 1], h, l);
-                bh[nt][t][i] = h;
-                bl[nt][t][i] = l;
+                split_pair(T0[2 * i], T0[2 * i + 1], h, l);
+                B.h0[mt][t][i] = h;
+                B.l0[mt][t][i] = l;
+                B.t1[mt][t][i] = pack_half2(T1[2 * i], T1[2 * i + 1]);
+            }
+            __builtin_amdgcn_sched_barrier(0);      // (one fragment's values at a time)
+        }
+}
+
+// What a lane keeps of its own sample until the end of the round.
+struct MfOwn {
+    float z0r, z0i, e2r, e2i;
+};
+
+// First part of a round: lane l forms the values of sample wbase + l (phases,
+// harmonics and their powers) into the wave's LDS area.  z0 = e^{-i m_0 Phi_phi}
+// and E^2 stay in registers: the same lane holds the sample at the end.
+template <bool CONSEC>
+__device__ __forceinline__ MfOwn mf_samples(const SumJob &jb, int iv, double ti, double vscale,
+                                            double vshift, long long wbase, long long e,
+                                            const int *mm, MfSampleArea *sa) {
+    const int lane = threadIdx.x & (kWave - 1);
+    const FEW_AS4 double *pc = cptr(jb.pcoef) + (size_t)iv * 16;
+    MfOwn own{1.0f, 0.0f, 1.0f, 0.0f};
+    // (wbase and e are whole numbers below 2^53: exact)
+    const double jd = fmin((double)wbase + (double)lane, (double)(e - 1));
+    const double tj = __dadd_rn(jb.t_start, __dmul_rn(jd, jb.dt));
+    const double x = tj - ti;
+    const double pf = phase_raw(pc, x);
+    const double pr = phase_raw(pc + 8, x);
+    float er, ei, fr, fi;
+    phasor_f32(pf, &er, &ei);
+    phasor_f32(pr, &fr, &fi);
+    float f2r, f2i, f3r, f3i, f4r, f4i, f8r, f8i, f12r, f12i, f16r, f16i;
+    cmulf(fr, fi, fr, fi, &f2r, &f2i);
+    cmulf(f2r, f2i, fr, fi, &f3r, &f3i);
+    cmulf(f2r, f2i, f2r, f2i, &f4r, &f4i);
+    cmulf(f4r, f4i, f4r, f4i, &f8r, &f8i);
+    cmulf(f8r, f8i, f4r, f4i, &f12r, &f12i);
+    cmulf(f8r, f8i, f8r, f8i, &f16r, &f16i);
+    sa->v[lane] = (float)fma(x, vscale, vshift);
+    sa->f[lane] = make_float2(fr, fi);
+    sa->f2[lane] = make_float2(f2r, f2i);
+    sa->f3[lane] = make_float2(f3r, f3i);
+    sa->f16[lane] = make_float2(f16r, f16i);
+    sa->c[1][lane] = make_float2(f4r, f4i);
+    sa->c[2][lane] = make_float2(f8r, f8i);
+    sa->c[3][lane] = make_float2(f12r, f12i);
+    sa->e[lane] = make_float2(er, ei);
+    if constexpr (CONSEC) {
+        const int m0 = mm[0], am0 = m0 < 0 ? -m0 : m0;
+        // Rows of consecutive m (m_r = m_0 + r): every z_r is a power of
+        // E = e^{-i Phi_phi}.  z_0 = E^{m_0} by binary powering (E^{-1} =
+        // conj E), so each z_r carries m_r times the phase error of E, at
+        // most max |m| of it.
+        float e4r, e4i, e8r, e8i;
+        cmulf(er, ei, er, ei, &own.e2r, &own.e2i);
+        cmulf(own.e2r, own.e2i, own.e2r, own.e2i, &e4r, &e4i);
+        cmulf(e4r, e4i, e4r, e4i, &e8r, &e8i);
+        float br = e8r, bi = e8i;
+        auto take = [&](float qr, float qi) {
+            float nr, ni;
+            cmulf(own.z0r, own.z0i, qr, qi, &nr, &ni);
+            own.z0r = nr;
+            own.z0i = ni;
+        };
+        if (am0 & 1) take(er, ei);
+        if (am0 & 2) take(own.e2r, own.e2i);
+        if (am0 & 4) take(e4r, e4i);
+        for (int bit = 8; bit <= am0; bit <<= 1) {
+            if (am0 & bit) take(br, bi);
+            float nr, ni;
+            cmulf(br, bi, br, bi, &nr, &ni);
+            br = nr;
+            bi = ni;
+        }
+        if (m0 < 0) own.z0i = -own.z0i;
+        sa->e4[lane] = make_float2(e4r, e4i);
+        sa->e8[lane] = make_float2(e8r, e8i);
+    } else {
+        // rows of arbitrary m carry their whole phase themselves
+        sa->e4[lane] = make_float2(1.0f, 0.0f);
+        ((double *)sa->e8)[lane] = d_reduce_2pi(pf);
+    }
+    __builtin_amdgcn_wave_barrier();
+    return own;
+}
+
+// The operand columns of sample tile nt: powers of f for every step, fp16 hi
+// and lo pairs.  Lane group g = l / 16 holds |n| = 16 t + 4 g + j, j < 4, of
+// step t: f^{16 t + 4 g} times f^j (the same fragment serves n and -n).
+__device__ __forceinline__ void mf_columns(const MfSampleArea *sa, int nt, mf_u4 (&bh)[kMfT],
+                                           mf_u4 (&bl)[kMfT]) {
+    const int lane = threadIdx.x & (kWave - 1);
+    const int g = lane >> 4, sl = 16 * nt + (lane & 15);
+    const float2 f1 = sa->f[sl], f2 = sa->f2[sl], f3 = sa->f3[sl], fs = sa->f16[sl];
+    const float2 c0 = sa->c[g][sl];
+    float w[8];
+    w[0] = c0.x;
+    w[1] = c0.y;
+    cmulf(c0.x, c0.y, f1.x, f1.y, &w[2], &w[3]);
+    cmulf(c0.x, c0.y, f2.x, f2.y, &w[4], &w[5]);
+    cmulf(c0.x, c0.y, f3.x, f3.y, &w[6], &w[7]);
+#pragma unroll
+    for (int t = 0; t < kMfT; ++t) {
+        if (t > 0) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                float nr, ni;
+                cmulf(w[2 * i], w[2 * i + 1], fs.x, fs.y, &nr, &ni);
+                w[2 * i] = nr;
+                w[2 * i + 1] = ni;
             }
         }
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            unsigned h, l;
+            split_pair(w[2 * i], w[2 * i + 1], h, l);
+            bh[t][i] = h;
+            bl[t][i] = l;
+        }
+    }
+}
+
+// Rows of tile mt -> the lane's value of its column in sample tile nt.  The
+// lane holds rows r = 8 mt + 2g (a0 + i b0) and r + 1 (a1 + i b1), which share
+// the scale se.
+template <bool CONSEC>
+__device__ __forceinline__ void mf_rows(const mf_float4 &acc, float se, int mt, int nt,
+                                        const int *mm, const MfSampleArea *sa, float &qr,
+                                        float &qi) {
+    const int lane = threadIdx.x & (kWave - 1);
+    const int g = lane >> 4, sl = 16 * nt + (lane & 15);
+    const float2 E = sa->e[sl];
+    const float a0 = acc[0], b0 = acc[1], a1 = acc[2], b1 = acc[3];
+    if constexpr (CONSEC) {
+        // z_r = z_0 E^{2g} E^{8 mt} (E for the odd row): Horner in E^8 over
+        // the tiles of s (a0 + i b0 + E (a1 + i b1))
+        const float wr = se * __builtin_fmaf(E.x, a1, __builtin_fmaf(-E.y, b1, a0));
+        const float wi = se * __builtin_fmaf(E.x, b1, __builtin_fmaf(E.y, a1, b0));
+        if (mt == kMfMT - 1) {
+            qr = wr;
+            qi = wi;
+        } else {
+            const float2 E8 = sa->e8[sl];
+            const float nr = __builtin_fmaf(qr, E8.x, __builtin_fmaf(-qi, E8.y, wr));
+            const float ni = __builtin_fmaf(qr, E8.y, __builtin_fmaf(qi, E8.x, wi));
+            qr = nr;
+            qi = ni;
+        }
+    } else {
+        // rows of arbitrary m: one phasor per row (the odd row from the even
+        // one when its m is the next integer)
+        const double spf = ((const double *)sa->e8)[sl];
+        const int me = mm[8 * mt + 2 * g], mo = mm[8 * mt + 2 * g + 1];
+        float zr, zi, yr, yi;
+        phasor_f32((double)me * spf, &zr, &zi);
+        if (mo == me + 1)
+            cmulf(zr, zi, E.x, E.y, &yr, &yi);
+        else
+            phasor_f32((double)mo * spf, &yr, &yi);
+        zr = zr * se;
+        zi = zi * se;
+        yr = yr * se;
+        yi = yi * se;
+        if (mt == kMfMT - 1) qr = qi = 0.0f;
+        qr = __builtin_fmaf(zr, a0, __builtin_fmaf(-zi, b0, qr));
+        qi = __builtin_fmaf(zr, b0, __builtin_fmaf(zi, a0, qi));
+        qr = __builtin_fmaf(yr, a1, __builtin_fmaf(-yi, b1, qr));
+        qi = __builtin_fmaf(yr, b1, __builtin_fmaf(yi, a1, qi));
+    }
+}
+
+// Last part of a round.  Join the lane groups, h = z_0 ((q_0 + E^4 q_2) +
+// E^2 (q_1 + E^4 q_3)): swapping halves between tiles P and Q leaves (P: g 0, 1;
+// Q: g 0, 1) in one register and (P: g 2, 3; Q: g 2, 3) in the other; swapping
+// rows between the pairs (0, 2) and (1, 3) then leaves lane l with sample l.
+// Stores h, or returns this lane's binary64 inner-product sums with the data
+// dv (INNER).
+template <bool INNER>
+__device__ __forceinline__ double2 mf_finish(const SumJob &jb, const float *qr, const float *qi,
+                                             const MfOwn &own, const MfSampleArea *sa,
+                                             long long jo, bool valid, float2 dv) {
+    const int lane = threadIdx.x & (kWave - 1), col = lane & 15;
+    auto join4 = [&](int a, int b, float *yr, float *yi) {
+        float pr = qr[a], pi = qi[a], ur = qr[b], ui = qi[b];
+        lane_swap32(pr, ur);
+        lane_swap32(pi, ui);
+        const float2 E4 = sa->e4[16 * (lane < 32 ? a : b) + col];
+        *yr = __builtin_fmaf(E4.x, ur, __builtin_fmaf(-E4.y, ui, pr));
+        *yi = __builtin_fmaf(E4.x, ui, __builtin_fmaf(E4.y, ur, pi));
+    };
+    float xr, xi, yr, yi, hr, hq;
+    join4(0, 2, &xr, &xi);
+    join4(1, 3, &yr, &yi);
+    lane_swap16(xr, yr);
+    lane_swap16(xi, yi);
+    const float sr = __builtin_fmaf(own.e2r, yr, __builtin_fmaf(-own.e2i, yi, xr));
+    const float si = __builtin_fmaf(own.e2r, yi, __builtin_fmaf(own.e2i, yr, xi));
+    cmulf(sr, si, own.z0r, own.z0i, &hr, &hq);
+    double dh = 0.0, hh = 0.0;
+    if (valid) {
+        if constexpr (INNER) {
+            const double vr = hr, vi = hq, dr = dv.x, di = dv.y;
+            dh = dr * vr + di * vi;
+            hh = vr * vr + vi * vi;
+        } else {
+            ((float2 *)jb.out)[jo] = make_float2(hr, hq);
+        }
+    }
+    // the area is rewritten by the next round only after these reads
+    __builtin_amdgcn_wave_barrier();
+    return make_double2(dh, hh);
+}
+
+// INNER: the lane's data sample, requested at the start of the round so that
+// its latency passes under the products (every lane loads, at a clamped index:
+// under a branch the compiler would wait for it at the join).
+template <bool INNER>
+__device__ __forceinline__ float2 mf_data(const SumJob &jb, long long jo, long long e) {
+    if constexpr (INNER) return ((const float2 *)jb.data)[min(jo, e - 1)];
+    return make_float2(0.0f, 0.0f);
+}
+
+// One round of a wave: the 64 samples wbase + l (valid below e) in four tiles
+// of 16, with the interval's static table in LDS.  The row tiles are taken one
+// after the other, the highest first: the accumulators of a tile (16
+// registers) run a Horner recurrence in v over p = 3 .. 0, then the lane's two
+// rows are combined and added into its running value.  The LDS accesses of
+// one wave complete in order, so its area needs no barrier.
+template <bool INNER, bool CONSEC>
+__device__ __forceinline__ double2 mf_round_static(const SumJob &jb, int iv, const MfInterval &I,
+                                                   long long wbase, long long e,
+                                                   const float4 *lds, const float *msc,
+                                                   const int *mm, MfSampleArea *sa) {
+    const int lane = threadIdx.x & (kWave - 1);
+    const long long jo = wbase + lane;
+    const float2 dv = mf_data<INNER>(jb, jo, e);
+    const MfOwn own = mf_samples<CONSEC>(jb, iv, I.ti, I.inv_h2, -1.0, wbase, e, mm, sa);
+    mf_u4 bh[kMfNT][kMfT], bl[kMfNT][kMfT];
+    float vv[kMfNT];
+#pragma unroll
+    for (int nt = 0; nt < kMfNT; ++nt) {
+        vv[nt] = sa->v[16 * nt + (lane & 15)];
+        mf_columns(sa, nt, bh[nt], bl[nt]);
     }
     float qr[kMfNT], qi[kMfNT];
 #pragma unroll
     for (int mt = kMfMT - 1; mt >= 0; --mt) {
+        mf_float4 acc[kMfNT];
+        // acc[nt] += A B_nt for the four sample tiles; the first product
+        // starts from zero (no accumulator to clear)
+        auto products = [&](float4 A, const mf_u4 (&B)[kMfNT][kMfT], int t, bool first) {
+#pragma unroll
+            for (int nt = 0; nt < kMfNT; ++nt)
+                acc[nt] = __builtin_amdgcn_mfma_f32_16x16x32_f16(
+                    __builtin_bit_cast(mf_half8, A), __builtin_bit_cast(mf_half8, B[nt][t]),
+                    first ? mf_float4{0.0f, 0.0f, 0.0f, 0.0f} : acc[nt], 0, 0, 0);
+        };
         const float4 *fp = lds + (size_t)mt * 4 * kMfT * 2 * 64 + lane;
         // (opaque here, so that the compiler does not keep a condition per
         // fragment in scalar registers across the whole loop over rounds)
-        unsigned ct = (unsigned)(cls >> (16 * mt));
-        asm volatile("" : "+s"(ct));
-        mf_float4 acc[kMfNT];
+        unsigned any = I.any >> (mt * 4 * kMfT), big = I.big >> (mt * 4 * kMfT);
+        asm volatile("" : "+s"(any), "+s"(big));
         constexpr int NF = 4 * kMfT;                // fragments of the tile, p descending
         float4 ch = fp[0], cl = fp[64];
 #pragma unroll
@@ -2352,146 +2566,155 @@ __device__ __forceinline__ double2 mf_round(const SumJob &jb, int iv, double ti,
             }
             // keep the next fragment's reads ahead of this fragment's products
             __builtin_amdgcn_sched_barrier(0);
-            const mf_half8 ah = __builtin_bit_cast(mf_half8, ch);
-            const mf_half8 al = __builtin_bit_cast(mf_half8, cl);
-            const unsigned cc = ct >> (2 * (p * kMfT + t));
-            if (t == 0 && p < 3) {
+            if (k == 0) {
+                products(ch, bh, t, true);
+            } else if (t == 0) {
                 // Horner step: every accumulator element of tile nt times v
 #pragma unroll
                 for (int nt = 0; nt < kMfNT; ++nt)
 #pragma unroll
                     for (int i = 0; i < 4; ++i) acc[nt][i] = acc[nt][i] * vv[nt];
             }
-            if (k == 0) {
-                // the first product starts from zero (no accumulator to clear)
-#pragma unroll
-                for (int nt = 0; nt < kMfNT; ++nt)
-                    acc[nt] = __builtin_amdgcn_mfma_f32_16x16x32_f16(
-                        ah, __builtin_bit_cast(mf_half8, bh[nt][t]),
-                        mf_float4{0.0f, 0.0f, 0.0f, 0.0f}, 0, 0, 0);
+            if ((big >> (p * kMfT + t)) & 1) {
+                products(cl, bh, t, false);
+                products(ch, bl, t, false);
             }
-            if (cc & 2) {
-#pragma unroll
-                for (int nt = 0; nt < kMfNT; ++nt)
-                    acc[nt] = __builtin_amdgcn_mfma_f32_16x16x32_f16(
-                        al, __builtin_bit_cast(mf_half8, bh[nt][t]), acc[nt], 0, 0, 0);
-#pragma unroll
-                for (int nt = 0; nt < kMfNT; ++nt)
-                    acc[nt] = __builtin_amdgcn_mfma_f32_16x16x32_f16(
-                        ah, __builtin_bit_cast(mf_half8, bl[nt][t]), acc[nt], 0, 0, 0);
-            }
-            if (k != 0 && (cc & 1)) {
-#pragma unroll
-                for (int nt = 0; nt < kMfNT; ++nt)
-                    acc[nt] = __builtin_amdgcn_mfma_f32_16x16x32_f16(
-                        ah, __builtin_bit_cast(mf_half8, bh[nt][t]), acc[nt], 0, 0, 0);
-            }
+            if (k != 0 && ((any >> (p * kMfT + t)) & 1)) products(ch, bh, t, false);
             __builtin_amdgcn_sched_barrier(0);
             ch = nh;
             cl = nl;
         }
-        // Rows -> the lane's value.  The lane holds rows r = 8 mt + 2g
-        // (a0 + i b0) and r + 1 (a1 + i b1), which share one scale.
-        const int r0 = 8 * mt + 2 * g;
-        const float se = msc[r0];
-        const int me = mm[r0], mo = mm[r0 + 1];
+        const float se = msc[4 * mt + (lane >> 4)];
 #pragma unroll
-        for (int nt = 0; nt < kMfNT; ++nt) {
-            const int sl = 16 * nt + col;
-            const float2 E = sa->e[sl];
-            const float a0 = acc[nt][0], b0 = acc[nt][1];
-            const float a1 = acc[nt][2], b1 = acc[nt][3];
-            if (consec) {
-                // z_r = z_0 E^{2g} E^{8 mt} (E for the odd row): Horner in E^8
-                // over the tiles of s (a0 + i b0 + E (a1 + i b1))
-                const float wr = se * __builtin_fmaf(E.x, a1, __builtin_fmaf(-E.y, b1, a0));
-                const float wi = se * __builtin_fmaf(E.x, b1, __builtin_fmaf(E.y, a1, b0));
-                if (mt == kMfMT - 1) {
-                    qr[nt] = wr;
-                    qi[nt] = wi;
-                } else {
-                    const float2 E8 = sa->e8[sl];
-                    const float nr = __builtin_fmaf(qr[nt], E8.x, __builtin_fmaf(-qi[nt], E8.y, wr));
-                    const float ni = __builtin_fmaf(qr[nt], E8.y, __builtin_fmaf(qi[nt], E8.x, wi));
-                    qr[nt] = nr;
-                    qi[nt] = ni;
-                }
-            } else {
-                // rows of arbitrary m: one phasor per row (the odd row from the
-                // even one when its m is the next integer)
-                const double spf = sa->pf[sl];
-                float zr, zi, yr, yi;
-                phasor_f32((double)me * spf, &zr, &zi);
-                if (mo == me + 1)
-                    cmulf(zr, zi, E.x, E.y, &yr, &yi);
-                else
-                    phasor_f32((double)mo * spf, &yr, &yi);
-                float hr = 0.0f, hq = 0.0f;
-                if (mt != kMfMT - 1) {
-                    hr = qr[nt];
-                    hq = qi[nt];
-                }
-                zr = zr * se;
-                zi = zi * se;
-                yr = yr * se;
-                yi = yi * se;
-                hr = __builtin_fmaf(zr, a0, __builtin_fmaf(-zi, b0, hr));
-                hq = __builtin_fmaf(zr, b0, __builtin_fmaf(zi, a0, hq));
-                qr[nt] = __builtin_fmaf(yr, a1, __builtin_fmaf(-yi, b1, hr));
-                qi[nt] = __builtin_fmaf(yr, b1, __builtin_fmaf(yi, a1, hq));
-            }
-        }
+        for (int nt = 0; nt < kMfNT; ++nt) mf_rows<CONSEC>(acc[nt], se, mt, nt, mm, sa, qr[nt], qi[nt]);
     }
-    // Join the lane groups, h = z_0 ((q_0 + E^4 q_2) + E^2 (q_1 + E^4 q_3)).
-    // Swapping halves between tiles P and Q leaves (P: g 0, 1; Q: g 0, 1) in
-    // one register and (P: g 2, 3; Q: g 2, 3) in the other; swapping rows
-    // between the pairs (0, 2) and (1, 3) then leaves lane l with sample l.
-    float hr, hq;
-    {
-        auto join4 = [&](int a, int b, float *yr, float *yi) {
-            float pr = qr[a], pi = qi[a], ur = qr[b], ui = qi[b];
-            lane_swap32(pr, ur);
-            lane_swap32(pi, ui);
-            const float2 E4 = sa->e4[16 * (lane < 32 ? a : b) + col];
-            *yr = __builtin_fmaf(E4.x, ur, __builtin_fmaf(-E4.y, ui, pr));
-            *yi = __builtin_fmaf(E4.x, ui, __builtin_fmaf(E4.y, ur, pi));
-        };
-        float xr, xi, yr, yi;
-        join4(0, 2, &xr, &xi);
-        join4(1, 3, &yr, &yi);
-        lane_swap16(xr, yr);
-        lane_swap16(xi, yi);
-        const float sr = __builtin_fmaf(e2r, yr, __builtin_fmaf(-e2i, yi, xr));
-        const float si = __builtin_fmaf(e2r, yi, __builtin_fmaf(e2i, yr, xi));
-        cmulf(sr, si, z0r, z0i, &hr, &hq);
-    }
-    double dh = 0.0, hh = 0.0;
-    if (own) {
-        if constexpr (INNER) {
-            const double xr = hr, xi = hq, dr = dv.x, di = dv.y;
-            dh = dr * xr + di * xi;
-            hh = xr * xr + xi * xi;
-        } else {
-            ((float2 *)jb.out)[jo] = make_float2(hr, hq);
-        }
-    }
-    // the area is rewritten by the next round only after these reads
-    __builtin_amdgcn_wave_barrier();
-    return make_double2(dh, hh);
+    return mf_finish<INNER>(jb, qr, qi, own, sa, jo, jo < e, dv);
 }
 
-// Samples [lo, hi) of one job (matrix-core path), interval by interval; each
-// interval's operand table and row scales are staged in LDS first.  Every
-// lane of the workgroup runs the same loop (lo, hi uniform).  INNER: each
-// lane's binary64 sums accumulate in its LDS slot iacc[threadIdx.x] (zeroed by
-// the caller), which keeps them out of the registers of the product loop.
+// The same round within one block (operands in registers, s in place of v),
+// one sample tile after the other: the columns, T_1 and T_0 of the three row
+// tiles (independent accumulators), the rows.
 template <bool INNER>
+__device__ __forceinline__ double2 mf_round_block(const SumJob &jb, int iv, double ti,
+                                                  double vscale, double vshift, const MfBlock &B,
+                                                  long long wbase, long long e, const float *msc,
+                                                  const int *mm, MfSampleArea *sa) {
+    const int lane = threadIdx.x & (kWave - 1);
+    const long long jo = wbase + lane;
+    const float2 dv = mf_data<INNER>(jb, jo, e);
+    const MfOwn own = mf_samples<true>(jb, iv, ti, vscale, vshift, wbase, e, mm, sa);
+    float se[kMfMT];
+#pragma unroll
+    for (int mt = 0; mt < kMfMT; ++mt) se[mt] = msc[4 * mt + (lane >> 4)];
+    float qr[kMfNT], qi[kMfNT];
+#pragma unroll
+    for (int nt = 0; nt < kMfNT; ++nt) {
+        mf_u4 bh[kMfT], bl[kMfT];
+        mf_columns(sa, nt, bh, bl);
+        const float s = sa->v[16 * nt + (lane & 15)];
+        mf_float4 acc[kMfMT];
+        auto products = [&](const mf_u4 (&A)[kMfMT][kMfT], const mf_u4 (&b)[kMfT], int t, bool first) {
+#pragma unroll
+            for (int mt = 0; mt < kMfMT; ++mt)
+                acc[mt] = __builtin_amdgcn_mfma_f32_16x16x32_f16(
+                    __builtin_bit_cast(mf_half8, A[mt][t]), __builtin_bit_cast(mf_half8, b[t]),
+                    first ? mf_float4{0.0f, 0.0f, 0.0f, 0.0f} : acc[mt], 0, 0, 0);
+        };
+#pragma unroll
+        for (int t = 0; t < kMfT; ++t) products(B.t1, bh, t, t == 0);
+#pragma unroll
+        for (int mt = 0; mt < kMfMT; ++mt)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) acc[mt][i] = acc[mt][i] * s;
+#pragma unroll
+        for (int t = 0; t < kMfT; ++t) {
+            products(B.l0, bh, t, false);
+            products(B.h0, bl, t, false);
+            products(B.h0, bh, t, false);
+        }
+#pragma unroll
+        for (int mt = kMfMT - 1; mt >= 0; --mt)
+            mf_rows<true>(acc[mt], se[mt], mt, nt, mm, sa, qr[nt], qi[nt]);
+    }
+    return mf_finish<INNER>(jb, qr, qi, own, sa, jo, jo < e, dv);
+}
+
+// Interval of sample j: the largest i <= K - 2 with starts[i] <= j.
+__device__ __forceinline__ int mf_interval_of(const SumJob &jb, long long j) {
+    const FEW_AS4 long long *st = cptr(jb.starts);
+    int iv = 0, top = jb.K - 2;
+    while (iv < top) {
+        const int mid = (iv + top + 1) >> 1;
+        if (st[mid] <= j) iv = mid; else top = mid - 1;
+    }
+    return iv;
+}
+
+// Share boundary j moved up to the grid of rounds (64 samples from the first
+// sample of its interval), so that every round belongs to one workgroup and a
+// sample's block does not depend on how the samples are shared out.
+__device__ __forceinline__ long long mf_align(const SumJob &jb, long long j) {
+    if (j <= 0) return 0;
+    if (j >= jb.n) return jb.n;
+    const FEW_AS4 long long *st = cptr(jb.starts);
+    const int iv = mf_interval_of(jb, j);
+    const long long a = st[iv];
+    return min((long long)st[iv + 1], a + (j - a + kMfSPW - 1) / kMfSPW * kMfSPW);
+}
+
+// The constants of interval iv and which products it takes (every wave forms
+// the same).
+template <bool CONSEC>
+__device__ __forceinline__ MfInterval mf_interval(const SumJob &jb, int iv, long long first) {
+    const int lane = threadIdx.x & (kWave - 1);
+    MfInterval I;
+    I.first = first;
+    I.ti = uniform_f64(jb.t[iv]);
+    I.inv_h2 = uniform_f64(2.0 / (jb.t[iv + 1] - I.ti));
+    const unsigned short *top = jb.minfo[iv].top;
+    auto mx = [&](int f) { return __uint_as_float((unsigned)top[f] << 16); };
+    {
+        constexpr int NF = kMfMT * 4 * kMfT;
+        const float v = mx(min(lane, NF - 1));
+        I.any = (unsigned)__ballot(lane < NF && !(v == 0.0f));
+        I.big = (unsigned)__ballot(lane < NF && !(v < kMfSmall));
+    }
+    I.block = 0;
+    if constexpr (CONSEC) {
+        // the widest block (half width w in v) that every fragment (mt, t) allows
+        constexpr int NF = kMfMT * kMfT;
+        const int f = min(lane, NF - 1), mt = f / kMfT, t = f % kMfT;
+        const float b1 = mx((mt * 4 + 1) * kMfT + t), b2 = mx((mt * 4 + 2) * kMfT + t);
+        const float b3 = mx((mt * 4 + 3) * kMfT + t);
+        const float w1 = kMfBlockSlope / (b1 + 2.0f * b2 + 3.75f * b3);
+        const float w2 = sqrtf(kMfBlockRest / (0.5f * b2 + 1.75f * b3));    // (w <= 1)
+        // (NaN and infinite values: no block)
+        float w = w1 > 0.0f && w2 > 0.0f ? fminf(fminf(w1, w2), 1.0f) : 0.0f;
+        for (int off = 4; off > 0; off >>= 1) w = fminf(w, __shfl_xor(w, off));
+        w = uniform_f32(w);
+        // half width of a round in v
+        const double unit = 0.5 * kMfSPW * jb.dt * I.inv_h2;
+        const double r = fmin((double)w / unit, (double)kMfMaxBlock);
+        const int k = (int)r;
+        I.block = __builtin_amdgcn_readfirstlane(k >= kMfMinBlock ? k : 0);
+    }
+    return I;
+}
+
+// Samples [lo, hi) of one job (matrix-core path), interval by interval.  Every
+// lane of the workgroup runs the same loops over intervals (lo, hi uniform).
+// INNER: each lane's binary64 sums accumulate in its LDS slot
+// iacc[threadIdx.x] (zeroed by the caller), which keeps them out of the
+// registers of the product loop.
+template <bool INNER, bool CONSEC>
 __device__ void mf_range(const SumJob &jb, long long lo, long long hi, float4 *lds,
                          float *msc, int *mm, double2 *iacc) {
+    lo = mf_align(jb, lo);
+    hi = mf_align(jb, hi);
     if (lo >= hi) return;
-    // the waves' sample areas follow the operand table in LDS
-    MfSampleArea *sa = (MfSampleArea *)((char *)lds + kMfIntervalHalves * sizeof(_Float16)) +
-                       threadIdx.x / kWave;
+    // the waves' sample areas follow the static table in LDS
+    const int wave = threadIdx.x / kWave;
+    MfSampleArea *sa = (MfSampleArea *)((char *)lds + kMfTableBytes) + wave;
     sa->c[0][threadIdx.x & (kWave - 1)] = make_float2(1.0f, 0.0f);
     __syncthreads();                                // rows of a previous job no longer read
     if ((int)threadIdx.x < kMfRows) {
@@ -2499,42 +2722,53 @@ __device__ void mf_range(const SumJob &jb, long long lo, long long hi, float4 *l
         const FEW_AS4 int2 *mr = cptr(jb.mrows);
         mm[r] = r < jb.n_mrows ? mr[r].x : mr[jb.n_mrows - 1].x + (r - jb.n_mrows + 1);
     }
-    // consecutive signed m values (padding rows continue the run)
-    bool consec = true;
-    {
-        const FEW_AS4 int2 *mr = cptr(jb.mrows);
-        for (int r = 1; r < jb.n_mrows; ++r) consec = consec && mr[r].x == mr[r - 1].x + 1;
-    }
     const FEW_AS4 long long *st = cptr(jb.starts);
-    int iv = 0, top = jb.K - 2;
-    while (iv < top) {
-        const int mid = (iv + top + 1) >> 1;
-        if (st[mid] <= lo) iv = mid; else top = mid - 1;
-    }
-    for (; iv <= jb.K - 2 && lo < hi; ++iv) {
-        const long long e = min(hi, (long long)st[iv + 1]);
+    auto add = [&](double2 v) {
+        if constexpr (INNER) {
+            double2 a = iacc[threadIdx.x];
+            a.x = a.x + v.x;
+            a.y = a.y + v.y;
+            iacc[threadIdx.x] = a;
+        }
+    };
+    for (int iv = mf_interval_of(jb, lo); iv <= jb.K - 2 && lo < hi; ++iv) {
+        const long long a = st[iv], e = min(hi, (long long)st[iv + 1]);
         if (e <= lo) continue;
+        const MfInterval I = mf_interval<CONSEC>(jb, iv, a);
+        const float *tab = jb.mtab + (size_t)iv * kMfIntervalFloats;
         __syncthreads();                            // previous interval no longer read
-        const float4 *src = (const float4 *)((const _Float16 *)jb.mtab +
-                                             (size_t)iv * kMfIntervalHalves);
-        constexpr int n4 = (int)(kMfIntervalHalves * sizeof(_Float16) / 16);
-        for (int v = threadIdx.x; v < n4; v += blockDim.x) lds[v] = src[v];
-        if ((int)threadIdx.x < kMfRows)
-            msc[threadIdx.x] = jb.mscale[(size_t)iv * kMfRows + threadIdx.x];
-        const unsigned long long cls = cptr(jb.mcls)[iv];
+        if ((int)threadIdx.x < kMfRows / 2) msc[threadIdx.x] = jb.minfo[iv].scale[threadIdx.x];
+        if (I.block == 0)
+            mf_build_static(tab, lds);
+        else
+            mf_stage(tab, lds);
         __syncthreads();
-        // a wave whose samples of a round all lie past the interval's end (the
-        // last round of an interval) skips that round
-        const double ti = jb.t[iv], inv_h2 = 2.0 / (jb.t[iv + 1] - ti);
-        for (long long base = lo + (long long)(threadIdx.x / kWave) * kMfSPW; base < e;
-             base += kMfRound) {                    // uniform per wave
-            const double2 v =
-                mf_round<INNER>(jb, iv, ti, inv_h2, base, e, lds, msc, mm, cls, consec, sa);
-            if constexpr (INNER) {
-                double2 a = iacc[threadIdx.x];
-                a.x = a.x + v.x;
-                a.y = a.y + v.y;
-                iacc[threadIdx.x] = a;
+        if (I.block == 0) {
+            // (a wave whose samples of a round all lie past the end skips it)
+            for (long long base = lo + (long long)wave * kMfSPW; base < e; base += kMfRound)
+                add(mf_round_static<INNER, CONSEC>(jb, iv, I, base, e, lds, msc, mm, sa));
+        } else if constexpr (CONSEC) {
+            // the waves take equal contiguous runs of rounds
+            const int r0 = (int)((lo - a) / kMfSPW);
+            const long long n = (e - lo + kMfSPW - 1) / kMfSPW;
+            const int ra = r0 + (int)(n * wave / kMfWaves), rb = r0 + (int)(n * (wave + 1) / kMfWaves);
+            const double x0 = dev_sample_time(jb.t_start, jb.dt, a) - I.ti;
+            const double w = uniform_f64(0.5 * kMfSPW * I.block * jb.dt * I.inv_h2);
+            const double vscale = uniform_f64(I.inv_h2 / w);
+            for (int r = ra; r < rb;) {
+                // the block of round r, centred at the middle of its samples
+                // (the last one's end with the interval, so |v0| <= 1)
+                const int k = r / I.block, end = min(rb, (k + 1) * I.block);
+                const long long j0 = (long long)k * I.block * kMfSPW;
+                const long long j1 = min(j0 + (long long)I.block * kMfSPW, (long long)st[iv + 1] - a);
+                const double mid = 0.5 * (double)(j0 + j1 - 1);
+                const double v0 = uniform_f64(fma(fma(mid, jb.dt, x0), I.inv_h2, -1.0));
+                const double vshift = uniform_f64(-(1.0 + v0) / w);
+                MfBlock B;
+                mf_block_form(lds, v0, w, B);
+                for (; r < end; ++r)
+                    add(mf_round_block<INNER>(jb, iv, I.ti, vscale, vshift, B,
+                                              a + (long long)r * kMfSPW, e, msc, mm, sa));
             }
         }
         lo = e;
@@ -2580,10 +2814,10 @@ __device__ __forceinline__ void mf_share_w(const float *wl, long long total, lon
     *hi = a + (e - a) * (j + 1) / S;
 }
 
-template <bool INNER>
+template <bool INNER, bool CONSEC>
 __global__ __launch_bounds__(64 * kMfWaves) void sum_mfma_kernel(SumJob jb) {
     extern __shared__ float4 mf_lds[];
-    __shared__ float msc[kMfRows];
+    __shared__ float msc[kMfRows / 2];
     __shared__ int mm[kMfRows];
     __shared__ double2 iacc[INNER ? 64 * kMfWaves : 1];
     if constexpr (INNER) iacc[threadIdx.x] = make_double2(0.0, 0.0);
@@ -2595,7 +2829,7 @@ __global__ __launch_bounds__(64 * kMfWaves) void sum_mfma_kernel(SumJob jb) {
         mf_share_w(jb.bw, jb.n, &lo, &hi);
     else
         mf_share(jb.n, &lo, &hi);
-    mf_range<INNER>(jb, lo, hi, mf_lds, msc, mm, iacc);
+    mf_range<INNER, CONSEC>(jb, lo, hi, mf_lds, msc, mm, iacc);
     if (!INNER && jb.btime != nullptr && (int)blockIdx.x < kMfBalanceWG) {
         __syncthreads();
         if (threadIdx.x == 0) {
@@ -2621,10 +2855,11 @@ __global__ __launch_bounds__(64 * kMfWaves) void sum_mfma_kernel(SumJob jb) {
 
 // Batched launch: the jobs' samples laid end to end (job j from sample_base_j),
 // split into equal shares.
+template <bool CONSEC>
 __global__ __launch_bounds__(64 * kMfWaves) void sum_mfma_batch_kernel(const SumJob *jobs, int n_jobs,
                                                              long long total) {
     extern __shared__ float4 mf_lds[];
-    __shared__ float msc[kMfRows];
+    __shared__ float msc[kMfRows / 2];
     __shared__ int mm[kMfRows];
     long long lo, hi;
     mf_share(total, &lo, &hi);
@@ -2638,7 +2873,7 @@ __global__ __launch_bounds__(64 * kMfWaves) void sum_mfma_batch_kernel(const Sum
         if (b0 >= hi) break;
         const SumJob jb = load_uniform(jobs + j);
         const long long a = max(lo, b0) - b0, e = min(hi, b0 + jb.n) - b0;
-        if (a < e) mf_range<false>(jb, a, e, mf_lds, msc, mm, nullptr);
+        if (a < e) mf_range<false, CONSEC>(jb, a, e, mf_lds, msc, mm, nullptr);
     }
 }
 
@@ -3296,7 +3531,7 @@ hipError_t launch_fold_pack_batch(const PrepJob *jobs_dev, int n_jobs, int max_K
 }
 
 static constexpr size_t mf_lds_bytes() {
-    return kMfIntervalHalves * sizeof(_Float16) + kMfWaves * sizeof(MfSampleArea);
+    return kMfTableBytes + kMfWaves * sizeof(MfSampleArea);
 }
 
 // One workgroup per compute unit (the operand table takes most of the LDS).
@@ -3307,26 +3542,36 @@ int mfma_workgroups() {
         return 0;
     static std::once_flag once;
     std::call_once(once, [] {
-        hipFuncSetAttribute((const void *)sum_mfma_kernel<false>,
-                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)mf_lds_bytes());
-        hipFuncSetAttribute((const void *)sum_mfma_kernel<true>,
-                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)mf_lds_bytes());
-        hipFuncSetAttribute((const void *)sum_mfma_batch_kernel,
-                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)mf_lds_bytes());
+        const void *fn[] = {(const void *)sum_mfma_kernel<false, true>,
+                            (const void *)sum_mfma_kernel<false, false>,
+                            (const void *)sum_mfma_kernel<true, true>,
+                            (const void *)sum_mfma_kernel<true, false>,
+                            (const void *)sum_mfma_batch_kernel<true>,
+                            (const void *)sum_mfma_batch_kernel<false>};
+        for (const void *f : fn)
+            hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)mf_lds_bytes());
     });
     return cus;
 }
 
 hipError_t launch_sum_mfma(const SumJob &job, int n_wg, hipStream_t stream) {
-    hipLaunchKernelGGL(sum_mfma_kernel<false>, dim3(n_wg), dim3(64 * kMfWaves), mf_lds_bytes(),
-                       stream, job);
+    if (job.mf_consec)
+        hipLaunchKernelGGL((sum_mfma_kernel<false, true>), dim3(n_wg), dim3(64 * kMfWaves),
+                           mf_lds_bytes(), stream, job);
+    else
+        hipLaunchKernelGGL((sum_mfma_kernel<false, false>), dim3(n_wg), dim3(64 * kMfWaves),
+                           mf_lds_bytes(), stream, job);
     return hipGetLastError();
 }
 
 hipError_t launch_sum_mfma_inner(const SumJob &job, int n_wg, double two_dt, double *out2,
                                  hipStream_t stream) {
-    hipLaunchKernelGGL(sum_mfma_kernel<true>, dim3(n_wg), dim3(64 * kMfWaves), mf_lds_bytes(),
-                       stream, job);
+    if (job.mf_consec)
+        hipLaunchKernelGGL((sum_mfma_kernel<true, true>), dim3(n_wg), dim3(64 * kMfWaves),
+                           mf_lds_bytes(), stream, job);
+    else
+        hipLaunchKernelGGL((sum_mfma_kernel<true, false>), dim3(n_wg), dim3(64 * kMfWaves),
+                           mf_lds_bytes(), stream, job);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(reduce_partials_kernel, dim3(1), dim3(kReduceThreads), 0, stream,
@@ -3334,10 +3579,14 @@ hipError_t launch_sum_mfma_inner(const SumJob &job, int n_wg, double two_dt, dou
     return hipGetLastError();
 }
 
-hipError_t launch_sum_mfma_batch(const SumJob *jobs_dev, int n_jobs, long long total, int n_wg,
-                                 hipStream_t stream) {
-    hipLaunchKernelGGL(sum_mfma_batch_kernel, dim3(n_wg), dim3(64 * kMfWaves), mf_lds_bytes(),
-                       stream, jobs_dev, n_jobs, total);
+hipError_t launch_sum_mfma_batch(const SumJob *jobs_dev, int n_jobs, long long total, bool consec,
+                                 int n_wg, hipStream_t stream) {
+    if (consec)
+        hipLaunchKernelGGL(sum_mfma_batch_kernel<true>, dim3(n_wg), dim3(64 * kMfWaves),
+                           mf_lds_bytes(), stream, jobs_dev, n_jobs, total);
+    else
+        hipLaunchKernelGGL(sum_mfma_batch_kernel<false>, dim3(n_wg), dim3(64 * kMfWaves),
+                           mf_lds_bytes(), stream, jobs_dev, n_jobs, total);
     return hipGetLastError();
 }
 
