@@ -406,9 +406,11 @@ uint64_t few_host_request_bytes(int32_t precision, int32_t K, int32_t M,
  * Matrix-core summation of FEW_MIXED plans (a contraction of the folded
  * coefficients of Eq. (10) with powers of e^{-i Phi_r}, Sec. III C, on fp16
  * hi/lo operands with fp32 accumulation).  few_host_mfma_path returns 1 if a
- * binary32 request with this (l, m, n) mode list is summed on the matrix
- * cores (unless the plan sets FEW_FLAG_VECTOR_ONLY), 0 if on the vector
- * units, or a negative few_status for an invalid list.  few_host_mfma_shape
+ * binary32 request with this (l, m, n) mode list is folded straight into
+ * matrix operands and summed on the matrix cores whatever its length (unless
+ * the plan sets FEW_FLAG_VECTOR_ONLY), 0 if it is folded into a term table,
+ * which the matrix cores take for longer sums and the vector units for
+ * shorter ones, or a negative few_status for an invalid list.  few_host_mfma_shape
  * writes the launch shape: out8 = (waves per workgroup, 16-sample tiles per
  * wave, 16-row tiles, 32-column steps per sign of n, MFMA instructions per
  * tile and round, largest |n| + 1, largest number of signed m values,

@@ -226,6 +226,10 @@ class PinnedPool {
     std::vector<Buf> bufs_;
 };
 
+// Sums from the fold table take part in the XCD split weights from this many
+// samples on (below, their times are those of forming the operands).
+constexpr long long kMfSplitMin = 786432;
+
 enum Stage { ST_FIT = 0, ST_PREP = 1, ST_SUM = 2 };
 
 // One request's host-side description and arena placement.
@@ -238,6 +242,8 @@ struct HostReq {
     ReqLayout L{};
     size_t upload_bytes = 0;   // [0, upload_bytes) of the layout comes from the host
     bool mfma = false;         // binary32 sums of this request run on the matrix-core path
+    bool terms_ok = false;     // .. from its fold table, where mf_terms_path says so
+    bool mf_terms(long long n) const { return terms_ok && mf_terms_path(terms, n); }
     ~HostReq() { free_term_layout(&terms); }
 };
 
@@ -363,6 +369,10 @@ class LayoutCache {
         b->n_max = a.n_max;
         b->l_max = a.l_max;
         b->mfma = a.mfma;
+        b->mf_terms = a.mf_terms;
+        b->m_min = a.m_min;
+        b->k_min = a.k_min;
+        b->k_max = a.k_max;
         b->consec = a.consec;
         b->mrows = (int *)std::malloc(sizeof(int) * 2 * (size_t)(a.n_mrows + 1));
         b->segs = (int *)std::malloc(sizeof(int) * 4 * (size_t)a.n_segs);
@@ -394,6 +404,7 @@ int make_host_req(int K, const double *t, int M, const int32_t *lmn, bool fp32, 
     int rc = cache->get(M, lmn, width, &r->terms);
     if (rc) return fail(rc, "mode list rejected while building the term layout");
     r->mfma = fp32 && allow_mfma && r->terms.mfma && width == 3;
+    r->terms_ok = fp32 && allow_mfma && !r->mfma;
     r->L = request_layout(fp32, K, M, r->terms.n_segs, r->terms.n_terms, r->terms.n_src,
                           r->terms.n_chunks, r->n_ph, r->mfma, r->terms.n_mrows);
     r->upload_bytes = r->L.upload_end;
@@ -526,6 +537,10 @@ SumJob sum_job(const HostReq &r, ReqBase base, double t_start, double dt, int64_
     j.n_mrows = r.terms.n_mrows;
     j.n_min = r.terms.n_min;
     j.mf_consec = r.terms.consec ? 1 : 0;
+    j.mf_terms = (signed char)(r.mf_terms(n) ? r.terms.mf_terms : 0);
+    j.mf_m0 = (signed char)r.terms.m_min;
+    j.mf_k0 = (signed char)r.terms.k_min;
+    j.mf_nk = (unsigned char)(r.terms.k_max - r.terms.k_min + 1);
     j.sample_base = 0;
     return j;
 }
@@ -889,7 +904,7 @@ double plan_us(few_plan p) {
 // One JSON line per retired served request (caller holds p->mu).
 void log_request(few_plan p, const ServedReq *r, double t_done) {
     if (!p->log) return;
-    const char *path = !p->fp32 ? "fp64" : (r->h.mfma ? "mfma" : "vector");
+    const char *path = !p->fp32 ? "fp64" : (r->h.mfma || r->h.mf_terms(r->r.n_samples) ? "mfma" : "vector");
     std::fprintf(p->log,
                  "{\"ticket\": %llu, \"status\": %d, \"knots\": %d, \"modes\": %d, "
                  "\"samples\": %lld, \"path\": \"%s\", \"batch\": %lld, "
@@ -1101,7 +1116,7 @@ int sum_impl(few_plan p, few_spline s, double theta, double phi, double scale, d
         long long slots = part_tile_bound(n, tl.parts, tl.short_len, s->h.K,
                                           tile_samples(p->fp32), pj.short_tile);
         if (slots * tl.parts > 0x7fffffffLL) return fail(FEW_E_ARG, "too many samples");
-        const bool mf = s->h.mfma;
+        const bool mf = s->h.mfma, mf_any = mf || s->h.mf_terms(n);
         const long long need =
             !inner ? 0 : mf ? (long long)p->mf_wg : inner_slots(tl.parts, (int)slots, p->fp32);
         // matrix-core requests fold straight into the operand table
@@ -1109,10 +1124,12 @@ int sum_impl(few_plan p, few_spline s, double theta, double phi, double scale, d
             return mf ? launch_fold_pack(pj, p->stream) : launch_prepare(pj, p->fp32, p->stream);
         };
         auto sum = [&]() -> hipError_t {
-            if (mf) {
-                if (inner) return launch_sum_mfma_inner(sj, p->mf_wg, 2.0 * dt, out2, p->stream);
+            if (mf_any) {
+                if (inner)
+                    return launch_sum_mfma_inner(sj, (int)std::min<long long>(p->mf_wg, need),
+                                                 2.0 * dt, out2, p->stream);
                 SumJob sb = sj;
-                p->xsplit[p->max_inflight].apply(&sb, p->mf_wg);
+                if (mf || n >= kMfSplitMin) p->xsplit[p->max_inflight].apply(&sb, p->mf_wg);
                 return launch_sum_mfma(sb, p->mf_wg, p->stream);
             }
             return inner ? launch_sum_inner(sj, (int)slots, p->fp32, 2.0 * dt, out2, p->stream)
@@ -1453,13 +1470,16 @@ int launch_batch(few_plan p, Batch *b, hipStream_t s, unsigned *counter) {
         if (slots * tl.parts > 0x7fffffffLL) return fail(FEW_E_ARG, "too many samples");
         HIP_TRY(pinned_upload(dev, host, upload_end, s));
         HIP_TRY(launch_fit(f, r->h.t.data(), s));
-        if (r->h.mfma) {
-            SumJob ub = u;
-            p->xsplit[(counter - p->counters) / 64].apply(&ub, p->mf_wg);   // this stream's
+        if (r->h.mfma)
             HIP_TRY(launch_fold_pack(q, s));
+        else
+            HIP_TRY(launch_prepare(q, fp32, s));
+        if (r->h.mfma || u.mf_terms) {
+            SumJob ub = u;
+            if (r->h.mfma || u.n >= kMfSplitMin)
+                p->xsplit[(counter - p->counters) / 64].apply(&ub, p->mf_wg);   // this stream's
             HIP_TRY(launch_sum_mfma(ub, p->mf_wg, s));
         } else {
-            HIP_TRY(launch_prepare(q, fp32, s));
             HIP_TRY(launch_sum(u, (int)slots, fp32, s));
         }
         b->done = sync_event(p);
@@ -1467,17 +1487,23 @@ int launch_batch(few_plan p, Batch *b, hipStream_t s, unsigned *counter) {
         HIP_TRY(hipEventRecord(b->done, s));
         return FEW_OK;
     }
-    // vector-path jobs first in the prepare and sum job arrays, then the
-    // matrix-core ones, those with rows of consecutive m before the others
-    // (each set has its own summation launch)
-    auto set_of = [](const ServedReq *r) { return !r->h.mfma ? 0 : r->h.terms.consec ? 1 : 2; };
-    int first[4] = {0, 0, 0, 0}, next[3];
+    // the jobs by summation launch: the vector kernel, the matrix-core kernels
+    // on the fold table by shape (these share the vector jobs' fold), those on
+    // operand tables with rows of consecutive m, and the others
+    constexpr int kShapes = kMfMT * kMfT, kSets = kShapes + 3;
+    auto set_of = [](const ServedReq *r) {
+        if (r->h.mfma) return kShapes + (r->h.terms.consec ? 1 : 2);
+        if (!r->h.mf_terms(r->r.n_samples)) return 0;
+        const int q = r->h.terms.mf_terms;      // 10 row tiles + steps
+        return 1 + (q / 10 - 1) * kMfT + q % 10 - 1;
+    };
+    int first[kSets + 1] = {}, next[kSets];
     for (ServedReq *r : b->reqs) ++first[set_of(r) + 1];
-    for (int q = 0; q < 3; ++q) first[q + 1] += first[q];
-    std::copy(first, first + 3, next);
-    const int nv = first[1];
+    for (int q = 0; q < kSets; ++q) first[q + 1] += first[q];
+    std::copy(first, first + kSets, next);
+    const int n_fold = first[kShapes + 1];
     int max_amp_blocks = 0, max_K = 4, max_fold_blocks = 0, max_K_mf = 4;
-    long long waves = 0, mf_total[3] = {0, 0, 0};
+    long long waves = 0, mf_total[kSets] = {};
     for (int i = 0; i < n; ++i) {
         ServedReq *r = b->reqs[i];
         const ReqBase rb{dev + up_off[i], dev + dev_off[i]};
@@ -1491,12 +1517,14 @@ int launch_batch(few_plan p, Batch *b, hipStream_t s, unsigned *counter) {
         if (set > 0) {
             sj[k].sample_base = mf_total[set];
             mf_total[set] += r->r.n_samples;
-            max_K_mf = std::max(max_K_mf, r->h.K);
         } else {
             sj[k].wave_base = (int)waves;
             waves += tile_upper_bound(r->r.n_samples, r->h.K, tile);
-            max_fold_blocks = std::max(max_fold_blocks, pj[k].fold_blocks);
         }
+        if (r->h.mfma)
+            max_K_mf = std::max(max_K_mf, r->h.K);
+        else
+            max_fold_blocks = std::max(max_fold_blocks, pj[k].fold_blocks);
         max_amp_blocks = std::max(max_amp_blocks, fj[i].amp_blocks);
         max_K = std::max(max_K, r->h.K);
     }
@@ -1505,15 +1533,20 @@ int launch_batch(few_plan p, Batch *b, hipStream_t s, unsigned *counter) {
     const SumJob *sd = (const SumJob *)(dev + off_sum);
     HIP_TRY(pinned_upload(dev, host, upload_end, s));
     HIP_TRY(launch_fit_batch((const FitJob *)(dev + off_fit), n, max_amp_blocks, max_K, s));
-    if (nv > 0) {
-        HIP_TRY(launch_prepare_batch(pd, nv, max_fold_blocks, fp32, s));
-        HIP_TRY(launch_sum_batch(sd, nv, (int)waves, fp32, true, counter, s));
+    if (n_fold > 0) HIP_TRY(launch_prepare_batch(pd, n_fold, max_fold_blocks, fp32, s));
+    if (first[1] > 0) HIP_TRY(launch_sum_batch(sd, first[1], (int)waves, fp32, true, counter, s));
+    if (n_fold < n) HIP_TRY(launch_fold_pack_batch(pd + n_fold, n - n_fold, max_K_mf, s));
+    for (int set = 1; set < kSets; ++set) {
+        const int jobs = first[set + 1] - first[set];
+        if (jobs == 0) continue;
+        if (set <= kShapes)
+            HIP_TRY(launch_sum_mfma_terms_batch(sd + first[set], jobs, mf_total[set],
+                                                (set - 1) / kMfT + 1, (set - 1) % kMfT + 1,
+                                                p->mf_wg, s));
+        else
+            HIP_TRY(launch_sum_mfma_batch(sd + first[set], jobs, mf_total[set],
+                                          set == kShapes + 1, p->mf_wg, s));
     }
-    if (nv < n) HIP_TRY(launch_fold_pack_batch(pd + nv, n - nv, max_K_mf, s));
-    for (int set = 1; set < 3; ++set)
-        if (first[set + 1] > first[set])
-            HIP_TRY(launch_sum_mfma_batch(sd + first[set], first[set + 1] - first[set],
-                                          mf_total[set], set == 1, p->mf_wg, s));
     b->done = sync_event(p);
     if (!b->done) return fail(FEW_E_HIP, "event creation failed");
     HIP_TRY(hipEventRecord(b->done, s));

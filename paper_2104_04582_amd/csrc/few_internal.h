@@ -220,18 +220,21 @@ struct SumJob {
     int wave_base;          // first global tile slot of this job (batched launch)
     int grp[kTermGroups - 1];   // first segment of term groups 1..3 (binary32)
     int split;              // short tiles are term-split tiles
-    // matrix-core path
+    // matrix-core path: rows of consecutive signed m (mtab); sums from the
+    // fold table, 10 row tiles + steps needed (0: not); their lowest signed m
+    signed char mf_consec, mf_terms, mf_m0;
     const float *mtab;      // [K-1][kMfIntervalFloats] operand values
     const MfInfo *minfo;    // [K-1]
     const int2 *mrows;      // [n_mrows + 1]
     int n_mrows, n_min;
-    int mf_consec;          // rows of consecutive signed m
     long long sample_base;  // first sample of this job in a batched launch's range
     // matrix-core store launches: XCD split weights (all 0: equal split), and
     // where each workgroup reports (tag << kMfTagShift | its time), or nullptr
     float bw[8];
     unsigned long long *btime;
     unsigned btag;
+    signed char mf_k0;      // sums from the fold table: polar indices k0 ..
+    unsigned char mf_nk;    // .. k0 + nk - 1
 };
 
 // Launchers (kernels.hip).  All enqueue on `stream` and return the HIP status.
@@ -282,6 +285,8 @@ hipError_t launch_sum_mfma_inner(const SumJob &job, int n_wg, double two_dt, dou
                                  hipStream_t stream);
 hipError_t launch_sum_mfma_batch(const SumJob *jobs_dev, int n_jobs, long long total,
                                  bool consec, int n_wg, hipStream_t stream);
+hipError_t launch_sum_mfma_terms_batch(const SumJob *jobs_dev, int n_jobs, long long total, int mt,
+                                       int t, int n_wg, hipStream_t stream);
 hipError_t launch_select(const double *amp, int K, int M, double eps, bool sorted, int *keep,
                          hipStream_t stream);
 constexpr int kMaxSelectModes = 4096;   // LDS: (binary64 key + int index) per padded mode
@@ -302,7 +307,42 @@ struct TermLayout {
     int *mrows = nullptr;      // 2 * (n_mrows + 1): (m, first segment), sentinel (0, n_segs)
     bool consec = false;       // those m are consecutive
     bool mfma = false;         // layout fits the matrix-core shape (Schwarzschild terms)
+    // matrix-core sum from the fold table (mf_terms_path): 10 row tiles +
+    // steps needed, 0: outside its shapes
+    int mf_terms = 0;
+    int m_min = 0, k_min = 0, k_max = 0;
 };
+
+// Whether a sum over n samples of this layout (mf_terms != 0, not mfma) runs on
+// the matrix cores.  Their cost per sample depends on the shape alone (rows,
+// |n|), the vector kernel's on the terms, and each workgroup first forms its
+// operands (6 to 10 us per interval and polar index), which only many samples
+// repay; short generic-Kerr sums are split over the terms by the vector kernel.
+// Where the two meet, in terms per polar index, measured as whole requests
+// (60 knots, 10 s cadence; vector / matrix-core, us):
+//   100 to 365 days: 11 rows, |n| <= 3, 77 terms 58.0 / 57.4, 103.5 / 87.6;
+//     9 rows, |n| <= 20, 369 terms 108 / 66, 272 / 108; 17 rows, |n| <= 4, 153
+//     terms 77.2 / 78.5, 158 / 130; Kerr |k| <= 2, 21 rows, |n| <= 20 (100
+//     days), 861 terms 880 / 291
+//   30 days: 7 rows, |n| <= 8, 119 terms 43.8 / 43.1; 11 rows, |n| <= 5, 121
+//     terms 46.6 / 47.7; 7 rows, |n| <= 17, 245 terms 54.6 / 49.9; 17 rows,
+//     |n| <= 7, 255 terms 62.0 / 60.3 and Kerr 154.8 / 169.6
+//   1 day, Kerr: 11 rows, |n| <= 8, 187 terms 111 / 91; 9 rows, |n| <= 20, 369
+//     terms 95.8 / 105; 17 rows, |n| <= 12, 425 terms 115 / 140 and 21 rows,
+//     |n| <= 20, 861 terms 201 / 172
+// (The fold table, its size and its launches are the same either way.)
+inline bool mf_terms_path(const TermLayout &L, long long n) {
+    if (L.mf_terms == 0) return false;
+    const int mt = L.mf_terms / 10, t = L.mf_terms % 10;
+    const int shape = mt == 1 && t == 1 ? 0 : mt <= 2 && t == 1 ? 1 : mt <= 2 ? 2 : 3;
+    const int nk = L.k_max - L.k_min + 1;
+    static const int kShortKerr[4] = {136, 160, 450, 660};
+    static const int kShort[4] = {124, 140, 216, 300};
+    static const int kLong[4] = {80, 96, 160, 180};
+    // samples of 1.5 and 6 rounds of every wave of 256 workgroups
+    const int *least = n >= 786432 ? kLong : nk > 1 && n < 196608 ? kShortKerr : kShort;
+    return L.n_terms >= (long long)least[shape] * nk;
+}
 
 // Build the folded term layout; returns 0 or a few_status error code.
 int build_term_layout(int M, const int32_t *modes, int width, int max_gap, TermLayout *out);

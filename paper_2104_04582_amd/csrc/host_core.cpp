@@ -57,6 +57,9 @@ void free_term_layout(TermLayout *t) {
 // signed term (m, k, n); for m > 0 its mirror contributes
 // (-1)^{l+k} conj(A) Y_{l,-m} to the term (-m, -k, -n).  For fixed viewing
 // angles the l-sum then folds into one complex cubic per signed (m, k, n).
+// k of a segment's m + 256 k (|m| <= kMaxL)
+static int seg_polar(int mk) { return (mk + 128 + 256 * 1024) / 256 - 1024; }
+
 // width 3: modes (l, m, n) with k = 0 (Schwarzschild); width 4: (l, m, k, n).
 int build_term_layout(int M, const int32_t *modes, int width, int max_gap, TermLayout *out) {
     *out = TermLayout{};
@@ -195,6 +198,17 @@ int build_term_layout(int M, const int32_t *modes, int width, int max_gap, TermL
         mr.push_back(n_seg);
         out->n_mrows = (int)mr.size() / 2 - 1;
         out->consec = mr[2 * (out->n_mrows - 1)] - mr[0] == out->n_mrows - 1;
+        int m_min = INT32_MAX, m_max = INT32_MIN, k_min = INT32_MAX, k_max = INT32_MIN;
+        for (int g = 0; g < n_seg; ++g) {
+            const int k = seg_polar(segs[4 * g]), m = segs[4 * g] - 256 * k;
+            m_min = std::min(m_min, m);
+            m_max = std::max(m_max, m);
+            k_min = std::min(k_min, k);
+            k_max = std::max(k_max, k);
+        }
+        out->m_min = m_min;
+        out->k_min = k_min;
+        out->k_max = k_max;
         int lm = 0;
         for (int k = 0; k < M; ++k) lm = std::max(lm, (int)modes[(size_t)width * k]);
         out->l_max = lm;
@@ -202,6 +216,9 @@ int build_term_layout(int M, const int32_t *modes, int width, int max_gap, TermL
         out->n_max = n_max;
         out->mfma = width == 3 && n_min > -kMfA && n_max < kMfA && out->n_mrows <= kMfRows &&
                     term >= kMfMinTerms;
+        const int span = m_max - m_min + 1;
+        if (span <= kMfRows && n_min > -kMfA && n_max < kMfA)
+            out->mf_terms = 10 * ((span + 7) / 8) + (n_min > -16 && n_max < 16 ? 1 : 2);
         out->mrows = (int *)std::malloc(sizeof(int) * mr.size());
         if (!out->mrows) {
             free_term_layout(out);

@@ -2223,44 +2223,194 @@ constexpr int kMfMaxBlock = 1 << 20;
 // Per-interval values.
 struct MfInterval {
     double ti, inv_h2;      // knot time, 2 / h
-    unsigned any, big;      // static tables: bit (mt * 4 + p) * kMfT + t
+    unsigned any, big;      // static tables: bit (mt * 4 + p) * T + t
     int block;              // rounds per block, 0: static tables
-    long long first;        // first sample of the interval
 };
 
-// LDS: the static table, [mt][3 - p][t][hi, lo][lane 64][8 fp16], or the
-// interval's binary32 values, [mt][p][t][half of 4 values][lane 64].
-constexpr size_t kMfTableBytes = kMfIntervalFloats * sizeof(float);
+// LDS: the interval's binary32 values, [mt][p][t][half of 4 values][lane 64],
+// or (static) the same values as fp16, [mt][p][t][hi, lo][lane 64][8].
+// Binary32 values of one interval (or one polar index of it).
+constexpr size_t mf_table_bytes(int MT, int T) { return (size_t)MT * 4 * T * 2048; }
 
-// The interval's binary32 values staged for the blocks.
+// The operand values of fold_pack staged for the blocks.
 __device__ __forceinline__ void mf_stage(const float *tab, float4 *lds) {
-    for (int v = threadIdx.x; v < (int)(kMfIntervalFloats / 4); v += blockDim.x)
+    int tid = threadIdx.x;
+    asm volatile("" : "+v"(tid));       // (addresses formed here, not kept through the rounds)
+    for (int v = tid; v < (int)(kMfIntervalFloats / 4); v += 64 * kMfWaves)
         lds[(v & ~127) | (v & 1) << 6 | ((v >> 1) & 63)] = ((const float4 *)tab)[v];
 }
 
-// The static table of an interval (8 values of one fragment per lane and step).
-__device__ __forceinline__ void mf_build_static(const float *tab, float4 *lds) {
-    for (int it = threadIdx.x; it < kMfMT * 4 * kMfT * 64; it += blockDim.x) {
-        const int ln = it & 63, f = it >> 6, t = f % kMfT, p = (f / kMfT) & 3, mt = f / (4 * kMfT);
-        const float4 a = ((const float4 *)tab)[2 * it], b = ((const float4 *)tab)[2 * it + 1];
+// Staged values -> static table, in place (each lane rewrites what it read).
+template <int MT, int T>
+__device__ __forceinline__ void mf_convert(float4 *lds) {
+    int tid = threadIdx.x;
+    asm volatile("" : "+v"(tid));
+    for (int it = tid; it < MT * 4 * T * 64; it += 64 * kMfWaves) {
+        float4 *d = lds + (it >> 6) * 128 + (it & 63);
+        const float4 a = d[0], b = d[64];
         unsigned hi[4], lo[4];
         split_pair(a.x, a.y, hi[0], lo[0]);
         split_pair(a.z, a.w, hi[1], lo[1]);
         split_pair(b.x, b.y, hi[2], lo[2]);
         split_pair(b.z, b.w, hi[3], lo[3]);
-        uint4 *d = (uint4 *)lds + (size_t)(((mt * 4 + (3 - p)) * kMfT + t) * 2) * 64 + ln;
-        d[0] = make_uint4(hi[0], hi[1], hi[2], hi[3]);
-        d[64] = make_uint4(lo[0], lo[1], lo[2], lo[3]);
+        ((uint4 *)d)[0] = make_uint4(hi[0], hi[1], hi[2], hi[3]);
+        ((uint4 *)d)[64] = make_uint4(lo[0], lo[1], lo[2], lo[3]);
     }
 }
 
+// LDS of the requests whose operand values are formed here from the folded
+// terms of prepare_kernel: the term of every (row, n) of one polar index, the
+// largest |coefficient| of each row pair (as bits) and 2^E, the fragments'
+// largest scaled values.
+template <int MT, int T>
+struct MfTerms {
+    int idx[8 * MT][32 * T];        // n + 16 T; -1: no term
+    unsigned pmax[4 * MT];
+    float un[4 * MT];
+    unsigned top[MT * 4 * T];
+};
+
+// Cubic in u = x / h -> cubic in v = 2 u - 1.
+__device__ __forceinline__ void mf_recentre(float a0, float a1, float a2, float a3, float *b) {
+    const float h1 = 0.5f * a1, h2 = 0.25f * a2, h3 = 0.125f * a3;
+    b[0] = a0 + (h1 + (h2 + h3));
+    b[1] = h1 + __builtin_fmaf(2.0f, h2, 3.0f * h3);
+    b[2] = __builtin_fmaf(3.0f, h3, h2);
+    b[3] = h3;
+}
+
+__device__ __forceinline__ unsigned abs_bits(float x) { return __float_as_uint(x) & 0x7fffffffu; }
+
+// max over the lanes of groups of 2^steps
+template <int STEPS>
+__device__ __forceinline__ unsigned lanes_max(unsigned v) {
+#pragma unroll
+    for (int i = 0; i < STEPS; ++i) v = max(v, (unsigned)__shfl_xor((int)v, 1 << i));
+    return v;
+}
+
+// The operand values of interval iv and polar index kp (0 in Schwarzschild),
+// from the binary32 fold table: the values that fold_pack writes, formed in
+// binary32.  M.idx holds -1 everywhere on entry and on return.  A lane takes
+// the columns n = +-a of one row; a wave 8 rows by 8 of a, so that both maxima
+// are reductions over lanes.  Latency bound (the segments, the terms, then
+// the two maxima: four barriers).
+template <int MT, int T>
+__device__ __forceinline__ void mf_terms_stage(const SumJob &jb, int iv, int kp,
+                                               MfTerms<MT, T> &M, float4 *lds) {
+    int tid = threadIdx.x;
+    asm volatile("" : "+v"(tid));       // (addresses formed here, not kept through the rounds)
+    const int lane = tid & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+    __syncthreads();                                // the previous values no longer read
+    if (tid < 4 * MT) M.pmax[tid] = 0u;
+    if (tid < MT * 4 * T) M.top[tid] = 0u;
+    {
+        int turn = 0;       // the waves take the segments of this k in turn
+        for (int g0 = 0; g0 < jb.n_segs; g0 += kWave) {
+            const int4 S = jb.segs[min(g0 + lane, jb.n_segs - 1)];
+            unsigned long long hit = __ballot(g0 + lane < jb.n_segs && seg_k(S.x) == kp);
+            for (; hit; hit &= hit - 1, ++turn) {
+                if ((turn & (kMfWaves - 1)) != wave) continue;
+                const int src = __ffsll((long long)hit) - 1;
+                const int row = __builtin_amdgcn_readlane(S.x, src) - 256 * kp - jb.mf_m0;
+                const int n_lo = __builtin_amdgcn_readlane(S.y, src);
+                const int len = __builtin_amdgcn_readlane(S.z, src);
+                const int first = __builtin_amdgcn_readlane(S.w, src);
+                for (int q = lane; q < len; q += kWave) M.idx[row][n_lo + q + 16 * T] = first + q;
+            }
+        }
+    }
+    __syncthreads();
+    constexpr int kTasks = MT * T * 2, kTurns = (kTasks + kMfWaves - 1) / kMfWaves;
+    // (terms are stored in reverse order, 8 values each)
+    const float4 *last = (const float4 *)jb.table + ((size_t)iv * jb.n_terms + jb.n_terms - 1) * 2;
+    float4 v[kTurns][4];
+#pragma unroll
+    for (int q = 0; q < kTurns; ++q) {
+        const int task = min(wave + q * kMfWaves, kTasks - 1);      // (mt, t, half of the a)
+        const int row = 8 * (task / (2 * T)) + (lane >> 3), a = 8 * (task % (2 * T)) + (lane & 7);
+        int *ip = &M.idx[row][16 * T + a], *iq = &M.idx[row][16 * T - a];
+        const int tp = *ip, tq = a > 0 ? *iq : -1;
+        const float4 *cp = last - 2 * (size_t)max(tp, 0), *cq = last - 2 * (size_t)max(tq, 0);
+        v[q][0] = cp[0];
+        v[q][1] = cp[1];
+        v[q][2] = cq[0];
+        v[q][3] = cq[1];
+        if (tp < 0) v[q][0] = v[q][1] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+        if (tq < 0) v[q][2] = v[q][3] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+    }
+    __builtin_amdgcn_wave_barrier();
+#pragma unroll
+    for (int q = 0; q < kTurns; ++q) {
+        if (wave + q * kMfWaves >= kTasks) continue;
+        const int task = wave + q * kMfWaves;
+        const int row = 8 * (task / (2 * T)) + (lane >> 3), a = 8 * (task % (2 * T)) + (lane & 7);
+        M.idx[row][16 * T + a] = -1;
+        M.idx[row][16 * T - a] = -1;
+        unsigned m = 0;
+#pragma unroll
+        for (int h = 0; h < 4; h += 2) {
+            float b[4], c[4];
+            mf_recentre(v[q][h].x, v[q][h].z, v[q][h + 1].x, v[q][h + 1].z, b);
+            mf_recentre(v[q][h].y, v[q][h].w, v[q][h + 1].y, v[q][h + 1].w, c);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) m = max(m, max(abs_bits(b[i]), abs_bits(c[i])));
+        }
+        m = lanes_max<4>(m);                        // the 8 columns of two rows
+        if ((lane & 15) == 0) atomicMax(&M.pmax[row >> 1], m);
+    }
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < kTurns; ++q) {
+        if (wave + q * kMfWaves >= kTasks) continue;
+        const int task = wave + q * kMfWaves, mt = task / (2 * T), ta = task % (2 * T);
+        const int r = lane >> 3, a = 8 * ta + (lane & 7), t = ta >> 1;
+        // scale 2^-E, E the exponent of the row pair's largest value (NaN and
+        // infinity: none)
+        const float mx = __uint_as_float(M.pmax[4 * mt + (r >> 1)]);
+        int e = 0;
+        if (mx > 0.0f && mx < INFINITY) frexpf(mx, &e);
+        e = min(max(e, -126), 127);
+        const float sc = ldexpf(1.0f, -e);
+        if ((lane & 15) == 0) M.un[4 * mt + (r >> 1)] = ldexpf(1.0f, e);
+        // columns per power: (Re P + Re Q, Im Q - Im P) of row component 0,
+        // (Im P + Im Q, Re P - Re Q) of component 1
+        const float4 p0 = v[q][0], p1 = v[q][1], q0 = v[q][2], q1 = v[q][3];
+        float o[2][2][4];
+        mf_recentre(p0.x + q0.x, p0.z + q0.z, p1.x + q1.x, p1.z + q1.z, o[0][0]);
+        mf_recentre(q0.y - p0.y, q0.w - p0.w, q1.y - p1.y, q1.w - p1.w, o[0][1]);
+        mf_recentre(p0.y + q0.y, p0.w + q0.w, p1.y + q1.y, p1.w + q1.w, o[1][0]);
+        mf_recentre(p0.x - q0.x, p0.z - q0.z, p1.x - q1.x, p1.z - q1.z, o[1][1]);
+        // a = 16 t + 4 g + j: fragment lane 2 r + component + 16 g, values
+        // 2 j and 2 j + 1 (half j >> 1 of the staged fragment)
+        const int g = (a >> 2) & 3, j = a & 3;
+#pragma unroll
+        for (int p = 0; p < 4; ++p) {
+            unsigned big = 0;
+            float4 *f = lds + ((mt * 4 + p) * T + t) * 128 + 64 * (j >> 1) + 2 * r + 16 * g;
+#pragma unroll
+            for (int c = 0; c < 2; ++c) {
+                const float x = o[c][0][p] * sc, y = o[c][1][p] * sc;
+                big = max(big, max(abs_bits(x), abs_bits(y)));
+                ((float2 *)(f + c))[j & 1] = make_float2(x, y);
+            }
+            big = lanes_max<6>(big);
+            if (lane == 0) atomicMax(&M.top[(mt * 4 + p) * T + t], big);
+        }
+    }
+    __syncthreads();
+}
+
 // The operand registers of a block: T_0 (hi, lo) and T_1 per row tile and step.
+template <int MT, int T>
 struct MfBlock {
-    mf_u4 t1[kMfMT][kMfT], h0[kMfMT][kMfT], l0[kMfMT][kMfT];
+    mf_u4 t1[MT][T], h0[MT][T], l0[MT][T];
 };
 
 // Form them for block centre v0 and half width w from the staged values.
-__device__ __forceinline__ void mf_block_form(const float4 *lds, double v0, double w, MfBlock &B) {
+template <int MT, int T>
+__device__ __forceinline__ void mf_block_form(const float4 *lds, double v0, double w,
+                                              MfBlock<MT, T> &B) {
     const int lane = threadIdx.x & (kWave - 1);
     const double vv = v0 * v0, ww = w * w;
     const float k1 = uniform_f32((float)v0), k2 = uniform_f32((float)fma(0.5, ww, vv)),
@@ -2269,13 +2419,13 @@ __device__ __forceinline__ void mf_block_form(const float4 *lds, double v0, doub
                 q3 = uniform_f32((float)(w * fma(0.75, ww, 3.0 * vv)));
     const float4 *src = lds + lane;
 #pragma unroll
-    for (int mt = 0; mt < kMfMT; ++mt)
+    for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
-        for (int t = 0; t < kMfT; ++t) {
+        for (int t = 0; t < T; ++t) {
             float4 b[4][2];
 #pragma unroll
             for (int p = 0; p < 4; ++p) {
-                const float4 *q = src + ((mt * 4 + p) * kMfT + t) * 128;
+                const float4 *q = src + ((mt * 4 + p) * T + t) * 128;
                 b[p][0] = q[0];
                 b[p][1] = q[64];
             }
@@ -2299,21 +2449,32 @@ __device__ __forceinline__ void mf_block_form(const float4 *lds, double v0, doub
         }
 }
 
-// What a lane keeps of its own sample until the end of the round.
+// What a lane keeps of its own sample until the end of the round: z0 =
+// e^{-i m_0 Phi_phi}, E^2, and for generic Kerr Theta = e^{-i Phi_theta}.
 struct MfOwn {
-    float z0r, z0i, e2r, e2i;
+    float z0r, z0i, e2r, e2i, tr, ti;
+};
+
+// Generic Kerr: the sum over the polar index k is a Horner recurrence in Theta
+// on the sums over (m, n) of each k, highest k first, with the waves' running
+// values in LDS (hp, one per sample of kMfKerrRounds rounds).
+constexpr int kMfKerrRounds = 12;
+struct MfPolar {
+    float2 *hp;             // this round's running values
+    bool first, last;       // highest, lowest k
+    int k0;                 // lowest k
 };
 
 // First part of a round: lane l forms the values of sample wbase + l (phases,
-// harmonics and their powers) into the wave's LDS area.  z0 = e^{-i m_0 Phi_phi}
-// and E^2 stay in registers: the same lane holds the sample at the end.
-template <bool CONSEC>
+// harmonics and their powers) into the wave's LDS area.  z0 and E^2 (and
+// Theta) stay in registers: the same lane holds the sample at the end.
+template <bool CONSEC, bool KERR>
 __device__ __forceinline__ MfOwn mf_samples(const SumJob &jb, int iv, double ti, double vscale,
                                             double vshift, long long wbase, long long e,
-                                            const int *mm, MfSampleArea *sa) {
+                                            int m0, const MfPolar &po, MfSampleArea *sa) {
     const int lane = threadIdx.x & (kWave - 1);
-    const FEW_AS4 double *pc = cptr(jb.pcoef) + (size_t)iv * 16;
-    MfOwn own{1.0f, 0.0f, 1.0f, 0.0f};
+    const FEW_AS4 double *pc = cptr(jb.pcoef) + (size_t)iv * (KERR ? 24 : 16);
+    MfOwn own{1.0f, 0.0f, 1.0f, 0.0f, 1.0f, 0.0f};
     // (wbase and e are whole numbers below 2^53: exact)
     const double jd = fmin((double)wbase + (double)lane, (double)(e - 1));
     const double tj = __dadd_rn(jb.t_start, __dmul_rn(jd, jb.dt));
@@ -2340,7 +2501,7 @@ __device__ __forceinline__ MfOwn mf_samples(const SumJob &jb, int iv, double ti,
     sa->c[3][lane] = make_float2(f12r, f12i);
     sa->e[lane] = make_float2(er, ei);
     if constexpr (CONSEC) {
-        const int m0 = mm[0], am0 = m0 < 0 ? -m0 : m0;
+        const int am0 = m0 < 0 ? -m0 : m0;
         // Rows of consecutive m (m_r = m_0 + r): every z_r is a power of
         // E = e^{-i Phi_phi}.  z_0 = E^{m_0} by binary powering (E^{-1} =
         // conj E), so each z_r carries m_r times the phase error of E, at
@@ -2349,30 +2510,43 @@ __device__ __forceinline__ MfOwn mf_samples(const SumJob &jb, int iv, double ti,
         cmulf(er, ei, er, ei, &own.e2r, &own.e2i);
         cmulf(own.e2r, own.e2i, own.e2r, own.e2i, &e4r, &e4i);
         cmulf(e4r, e4i, e4r, e4i, &e8r, &e8i);
-        float br = e8r, bi = e8i;
-        auto take = [&](float qr, float qi) {
-            float nr, ni;
-            cmulf(own.z0r, own.z0i, qr, qi, &nr, &ni);
-            own.z0r = nr;
-            own.z0i = ni;
-        };
-        if (am0 & 1) take(er, ei);
-        if (am0 & 2) take(own.e2r, own.e2i);
-        if (am0 & 4) take(e4r, e4i);
-        for (int bit = 8; bit <= am0; bit <<= 1) {
-            if (am0 & bit) take(br, bi);
-            float nr, ni;
-            cmulf(br, bi, br, bi, &nr, &ni);
-            br = nr;
-            bi = ni;
+        if (!KERR || po.last) {
+            float br = e8r, bi = e8i;
+            auto take = [&](float qr, float qi) {
+                float nr, ni;
+                cmulf(own.z0r, own.z0i, qr, qi, &nr, &ni);
+                own.z0r = nr;
+                own.z0i = ni;
+            };
+            if (am0 & 1) take(er, ei);
+            if (am0 & 2) take(own.e2r, own.e2i);
+            if (am0 & 4) take(e4r, e4i);
+            for (int bit = 8; bit <= am0; bit <<= 1) {
+                if (am0 & bit) take(br, bi);
+                float nr, ni;
+                cmulf(br, bi, br, bi, &nr, &ni);
+                br = nr;
+                bi = ni;
+            }
+            if (m0 < 0) own.z0i = -own.z0i;
         }
-        if (m0 < 0) own.z0i = -own.z0i;
         sa->e4[lane] = make_float2(e4r, e4i);
         sa->e8[lane] = make_float2(e8r, e8i);
     } else {
         // rows of arbitrary m carry their whole phase themselves
         sa->e4[lane] = make_float2(1.0f, 0.0f);
         ((double *)sa->e8)[lane] = d_reduce_2pi(pf);
+    }
+    if constexpr (KERR) {
+        const double pt = phase_raw(pc + 16, x);
+        phasor_f32(pt, &own.tr, &own.ti);
+        if (po.last && po.k0 != 0) {
+            float zr, zi, kr, ki;
+            phasor_f32((double)po.k0 * d_reduce_2pi(pt), &kr, &ki);
+            cmulf(own.z0r, own.z0i, kr, ki, &zr, &zi);
+            own.z0r = zr;
+            own.z0i = zi;
+        }
     }
     __builtin_amdgcn_wave_barrier();
     return own;
@@ -2381,11 +2555,12 @@ __device__ __forceinline__ MfOwn mf_samples(const SumJob &jb, int iv, double ti,
 // The operand columns of sample tile nt: powers of f for every step, fp16 hi
 // and lo pairs.  Lane group g = l / 16 holds |n| = 16 t + 4 g + j, j < 4, of
 // step t: f^{16 t + 4 g} times f^j (the same fragment serves n and -n).
-__device__ __forceinline__ void mf_columns(const MfSampleArea *sa, int nt, mf_u4 (&bh)[kMfT],
-                                           mf_u4 (&bl)[kMfT]) {
+template <int T>
+__device__ __forceinline__ void mf_columns(const MfSampleArea *sa, int nt, mf_u4 (&bh)[T],
+                                           mf_u4 (&bl)[T]) {
     const int lane = threadIdx.x & (kWave - 1);
     const int g = lane >> 4, sl = 16 * nt + (lane & 15);
-    const float2 f1 = sa->f[sl], f2 = sa->f2[sl], f3 = sa->f3[sl], fs = sa->f16[sl];
+    const float2 f1 = sa->f[sl], f2 = sa->f2[sl], f3 = sa->f3[sl];
     const float2 c0 = sa->c[g][sl];
     float w[8];
     w[0] = c0.x;
@@ -2394,8 +2569,9 @@ __device__ __forceinline__ void mf_columns(const MfSampleArea *sa, int nt, mf_u4
     cmulf(c0.x, c0.y, f2.x, f2.y, &w[4], &w[5]);
     cmulf(c0.x, c0.y, f3.x, f3.y, &w[6], &w[7]);
 #pragma unroll
-    for (int t = 0; t < kMfT; ++t) {
+    for (int t = 0; t < T; ++t) {
         if (t > 0) {
+            const float2 fs = sa->f16[sl];
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
                 float nr, ni;
@@ -2417,7 +2593,7 @@ __device__ __forceinline__ void mf_columns(const MfSampleArea *sa, int nt, mf_u4
 // Rows of tile mt -> the lane's value of its column in sample tile nt.  The
 // lane holds rows r = 8 mt + 2g (a0 + i b0) and r + 1 (a1 + i b1), which share
 // the scale se.
-template <bool CONSEC>
+template <bool CONSEC, int MT>
 __device__ __forceinline__ void mf_rows(const mf_float4 &acc, float se, int mt, int nt,
                                         const int *mm, const MfSampleArea *sa, float &qr,
                                         float &qi) {
@@ -2430,7 +2606,7 @@ __device__ __forceinline__ void mf_rows(const mf_float4 &acc, float se, int mt, 
         // the tiles of s (a0 + i b0 + E (a1 + i b1))
         const float wr = se * __builtin_fmaf(E.x, a1, __builtin_fmaf(-E.y, b1, a0));
         const float wi = se * __builtin_fmaf(E.x, b1, __builtin_fmaf(E.y, a1, b0));
-        if (mt == kMfMT - 1) {
+        if (mt == MT - 1) {
             qr = wr;
             qi = wi;
         } else {
@@ -2455,7 +2631,7 @@ __device__ __forceinline__ void mf_rows(const mf_float4 &acc, float se, int mt, 
         zi = zi * se;
         yr = yr * se;
         yi = yi * se;
-        if (mt == kMfMT - 1) qr = qi = 0.0f;
+        if (mt == MT - 1) qr = qi = 0.0f;
         qr = __builtin_fmaf(zr, a0, __builtin_fmaf(-zi, b0, qr));
         qi = __builtin_fmaf(zr, b0, __builtin_fmaf(zi, a0, qi));
         qr = __builtin_fmaf(yr, a1, __builtin_fmaf(-yi, b1, qr));
@@ -2468,11 +2644,13 @@ __device__ __forceinline__ void mf_rows(const mf_float4 &acc, float se, int mt, 
 // Q: g 0, 1) in one register and (P: g 2, 3; Q: g 2, 3) in the other; swapping
 // rows between the pairs (0, 2) and (1, 3) then leaves lane l with sample l.
 // Stores h, or returns this lane's binary64 inner-product sums with the data
-// dv (INNER).
-template <bool INNER>
+// dv (INNER).  Generic Kerr: the Horner step in Theta, and only the lowest k
+// goes on to h.
+template <bool INNER, bool KERR>
 __device__ __forceinline__ double2 mf_finish(const SumJob &jb, const float *qr, const float *qi,
                                              const MfOwn &own, const MfSampleArea *sa,
-                                             long long jo, bool valid, float2 dv) {
+                                             long long jo, bool valid, float2 dv,
+                                             const MfPolar &po) {
     const int lane = threadIdx.x & (kWave - 1), col = lane & 15;
     auto join4 = [&](int a, int b, float *yr, float *yi) {
         float pr = qr[a], pi = qi[a], ur = qr[b], ui = qi[b];
@@ -2487,8 +2665,21 @@ __device__ __forceinline__ double2 mf_finish(const SumJob &jb, const float *qr, 
     join4(1, 3, &yr, &yi);
     lane_swap16(xr, yr);
     lane_swap16(xi, yi);
-    const float sr = __builtin_fmaf(own.e2r, yr, __builtin_fmaf(-own.e2i, yi, xr));
-    const float si = __builtin_fmaf(own.e2r, yi, __builtin_fmaf(own.e2i, yr, xi));
+    float sr = __builtin_fmaf(own.e2r, yr, __builtin_fmaf(-own.e2i, yi, xr));
+    float si = __builtin_fmaf(own.e2r, yi, __builtin_fmaf(own.e2i, yr, xi));
+    if constexpr (KERR) {
+        if (!po.first) {
+            const float2 q = po.hp[lane];
+            const float nr = __builtin_fmaf(q.x, own.tr, __builtin_fmaf(-q.y, own.ti, sr));
+            si = __builtin_fmaf(q.x, own.ti, __builtin_fmaf(q.y, own.tr, si));
+            sr = nr;
+        }
+        if (!po.last) {
+            po.hp[lane] = make_float2(sr, si);
+            __builtin_amdgcn_wave_barrier();
+            return make_double2(0.0, 0.0);
+        }
+    }
     cmulf(sr, si, own.z0r, own.z0i, &hr, &hq);
     double dh = 0.0, hh = 0.0;
     if (valid) {
@@ -2520,49 +2711,53 @@ __device__ __forceinline__ float2 mf_data(const SumJob &jb, long long jo, long l
 // registers) run a Horner recurrence in v over p = 3 .. 0, then the lane's two
 // rows are combined and added into its running value.  The LDS accesses of
 // one wave complete in order, so its area needs no barrier.
-template <bool INNER, bool CONSEC>
+template <bool INNER, bool CONSEC, int MT, int T, bool KERR>
 __device__ __forceinline__ double2 mf_round_static(const SumJob &jb, int iv, const MfInterval &I,
                                                    long long wbase, long long e,
                                                    const float4 *lds, const float *msc,
-                                                   const int *mm, MfSampleArea *sa) {
+                                                   const int *mm, const MfPolar &po,
+                                                   MfSampleArea *sa) {
     const int lane = threadIdx.x & (kWave - 1);
     const long long jo = wbase + lane;
     const float2 dv = mf_data<INNER>(jb, jo, e);
-    const MfOwn own = mf_samples<CONSEC>(jb, iv, I.ti, I.inv_h2, -1.0, wbase, e, mm, sa);
-    mf_u4 bh[kMfNT][kMfT], bl[kMfNT][kMfT];
+    const MfOwn own = mf_samples<CONSEC, KERR>(jb, iv, I.ti, I.inv_h2, -1.0, wbase, e, mm[0], po,
+                                              sa);
+    mf_u4 bh[kMfNT][T], bl[kMfNT][T];
     float vv[kMfNT];
 #pragma unroll
     for (int nt = 0; nt < kMfNT; ++nt) {
         vv[nt] = sa->v[16 * nt + (lane & 15)];
-        mf_columns(sa, nt, bh[nt], bl[nt]);
+        mf_columns<T>(sa, nt, bh[nt], bl[nt]);
     }
     float qr[kMfNT], qi[kMfNT];
 #pragma unroll
-    for (int mt = kMfMT - 1; mt >= 0; --mt) {
+    for (int mt = MT - 1; mt >= 0; --mt) {
         mf_float4 acc[kMfNT];
         // acc[nt] += A B_nt for the four sample tiles; the first product
         // starts from zero (no accumulator to clear)
-        auto products = [&](float4 A, const mf_u4 (&B)[kMfNT][kMfT], int t, bool first) {
+        auto products = [&](float4 A, const mf_u4 (&B)[kMfNT][T], int t, bool first) {
 #pragma unroll
             for (int nt = 0; nt < kMfNT; ++nt)
                 acc[nt] = __builtin_amdgcn_mfma_f32_16x16x32_f16(
                     __builtin_bit_cast(mf_half8, A), __builtin_bit_cast(mf_half8, B[nt][t]),
                     first ? mf_float4{0.0f, 0.0f, 0.0f, 0.0f} : acc[nt], 0, 0, 0);
         };
-        const float4 *fp = lds + (size_t)mt * 4 * kMfT * 2 * 64 + lane;
+        // fragment k of the tile, p descending
+        const float4 *fp = lds + (size_t)mt * 4 * T * 128 + lane;
+        auto at = [](int k) { return ((3 - k / T) * T + k % T) * 128; };
         // (opaque here, so that the compiler does not keep a condition per
         // fragment in scalar registers across the whole loop over rounds)
-        unsigned any = I.any >> (mt * 4 * kMfT), big = I.big >> (mt * 4 * kMfT);
+        unsigned any = I.any >> (mt * 4 * T), big = I.big >> (mt * 4 * T);
         asm volatile("" : "+s"(any), "+s"(big));
-        constexpr int NF = 4 * kMfT;                // fragments of the tile, p descending
-        float4 ch = fp[0], cl = fp[64];
+        constexpr int NF = 4 * T;
+        float4 ch = fp[at(0)], cl = fp[at(0) + 64];
 #pragma unroll
         for (int k = 0; k < NF; ++k) {
-            const int t = k % kMfT, p = 3 - k / kMfT;
+            const int t = k % T, p = 3 - k / T;
             float4 nh = ch, nl = cl;
             if (k + 1 < NF) {
-                nh = fp[((k + 1) * 2) * 64];
-                nl = fp[((k + 1) * 2 + 1) * 64];
+                nh = fp[at(k + 1)];
+                nl = fp[at(k + 1) + 64];
             }
             // keep the next fragment's reads ahead of this fragment's products
             __builtin_amdgcn_sched_barrier(0);
@@ -2575,68 +2770,70 @@ __device__ __forceinline__ double2 mf_round_static(const SumJob &jb, int iv, con
 #pragma unroll
                     for (int i = 0; i < 4; ++i) acc[nt][i] = acc[nt][i] * vv[nt];
             }
-            if ((big >> (p * kMfT + t)) & 1) {
+            if ((big >> (p * T + t)) & 1) {
                 products(cl, bh, t, false);
                 products(ch, bl, t, false);
             }
-            if (k != 0 && ((any >> (p * kMfT + t)) & 1)) products(ch, bh, t, false);
+            if (k != 0 && ((any >> (p * T + t)) & 1)) products(ch, bh, t, false);
             __builtin_amdgcn_sched_barrier(0);
             ch = nh;
             cl = nl;
         }
         const float se = msc[4 * mt + (lane >> 4)];
 #pragma unroll
-        for (int nt = 0; nt < kMfNT; ++nt) mf_rows<CONSEC>(acc[nt], se, mt, nt, mm, sa, qr[nt], qi[nt]);
+        for (int nt = 0; nt < kMfNT; ++nt) 
+            mf_rows<CONSEC, MT>(acc[nt], se, mt, nt, mm, sa, qr[nt], qi[nt]);
     }
-    return mf_finish<INNER>(jb, qr, qi, own, sa, jo, jo < e, dv);
+    return mf_finish<INNER, KERR>(jb, qr, qi, own, sa, jo, jo < e, dv, po);
 }
 
 // The same round within one block (operands in registers, s in place of v),
 // one sample tile after the other: the columns, T_1 and T_0 of the three row
 // tiles (independent accumulators), the rows.
-template <bool INNER>
+template <bool INNER, int MT, int T, bool KERR>
 __device__ __forceinline__ double2 mf_round_block(const SumJob &jb, int iv, double ti,
-                                                  double vscale, double vshift, const MfBlock &B,
-                                                  long long wbase, long long e, const float *msc,
-                                                  const int *mm, MfSampleArea *sa) {
+                                                  double vscale, double vshift,
+                                                  const MfBlock<MT, T> &B, long long wbase,
+                                                  long long e, const float *msc, const int *mm,
+                                                  const MfPolar &po, MfSampleArea *sa) {
     const int lane = threadIdx.x & (kWave - 1);
     const long long jo = wbase + lane;
     const float2 dv = mf_data<INNER>(jb, jo, e);
-    const MfOwn own = mf_samples<true>(jb, iv, ti, vscale, vshift, wbase, e, mm, sa);
-    float se[kMfMT];
+    const MfOwn own = mf_samples<true, KERR>(jb, iv, ti, vscale, vshift, wbase, e, mm[0], po, sa);
+    float se[MT];
 #pragma unroll
-    for (int mt = 0; mt < kMfMT; ++mt) se[mt] = msc[4 * mt + (lane >> 4)];
+    for (int mt = 0; mt < MT; ++mt) se[mt] = msc[4 * mt + (lane >> 4)];
     float qr[kMfNT], qi[kMfNT];
 #pragma unroll
     for (int nt = 0; nt < kMfNT; ++nt) {
-        mf_u4 bh[kMfT], bl[kMfT];
-        mf_columns(sa, nt, bh, bl);
+        mf_u4 bh[T], bl[T];
+        mf_columns<T>(sa, nt, bh, bl);
         const float s = sa->v[16 * nt + (lane & 15)];
-        mf_float4 acc[kMfMT];
-        auto products = [&](const mf_u4 (&A)[kMfMT][kMfT], const mf_u4 (&b)[kMfT], int t, bool first) {
+        mf_float4 acc[MT];
+        auto products = [&](const mf_u4 (&A)[MT][T], const mf_u4 (&b)[T], int t, bool first) {
 #pragma unroll
-            for (int mt = 0; mt < kMfMT; ++mt)
+            for (int mt = 0; mt < MT; ++mt)
                 acc[mt] = __builtin_amdgcn_mfma_f32_16x16x32_f16(
                     __builtin_bit_cast(mf_half8, A[mt][t]), __builtin_bit_cast(mf_half8, b[t]),
                     first ? mf_float4{0.0f, 0.0f, 0.0f, 0.0f} : acc[mt], 0, 0, 0);
         };
 #pragma unroll
-        for (int t = 0; t < kMfT; ++t) products(B.t1, bh, t, t == 0);
+        for (int t = 0; t < T; ++t) products(B.t1, bh, t, t == 0);
 #pragma unroll
-        for (int mt = 0; mt < kMfMT; ++mt)
+        for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
             for (int i = 0; i < 4; ++i) acc[mt][i] = acc[mt][i] * s;
 #pragma unroll
-        for (int t = 0; t < kMfT; ++t) {
+        for (int t = 0; t < T; ++t) {
             products(B.l0, bh, t, false);
             products(B.h0, bl, t, false);
             products(B.h0, bh, t, false);
         }
 #pragma unroll
-        for (int mt = kMfMT - 1; mt >= 0; --mt)
-            mf_rows<true>(acc[mt], se[mt], mt, nt, mm, sa, qr[nt], qi[nt]);
+        for (int mt = MT - 1; mt >= 0; --mt)
+            mf_rows<true, MT>(acc[mt], se[mt], mt, nt, mm, sa, qr[nt], qi[nt]);
     }
-    return mf_finish<INNER>(jb, qr, qi, own, sa, jo, jo < e, dv);
+    return mf_finish<INNER, KERR>(jb, qr, qi, own, sa, jo, jo < e, dv, po);
 }
 
 // Interval of sample j: the largest i <= K - 2 with starts[i] <= j.
@@ -2662,19 +2859,17 @@ __device__ __forceinline__ long long mf_align(const SumJob &jb, long long j) {
     return min((long long)st[iv + 1], a + (j - a + kMfSPW - 1) / kMfSPW * kMfSPW);
 }
 
-// The constants of interval iv and which products it takes (every wave forms
+// The constants of interval iv and which products it takes, from mx(f), the
+// largest |scaled value| of fragment f = (mt 4 + p) T + t (every wave forms
 // the same).
-template <bool CONSEC>
-__device__ __forceinline__ MfInterval mf_interval(const SumJob &jb, int iv, long long first) {
+template <bool CONSEC, int MT, int T, typename Max>
+__device__ __forceinline__ MfInterval mf_interval(const SumJob &jb, int iv, Max mx) {
     const int lane = threadIdx.x & (kWave - 1);
     MfInterval I;
-    I.first = first;
     I.ti = uniform_f64(jb.t[iv]);
     I.inv_h2 = uniform_f64(2.0 / (jb.t[iv + 1] - I.ti));
-    const unsigned short *top = jb.minfo[iv].top;
-    auto mx = [&](int f) { return __uint_as_float((unsigned)top[f] << 16); };
     {
-        constexpr int NF = kMfMT * 4 * kMfT;
+        constexpr int NF = MT * 4 * T;
         const float v = mx(min(lane, NF - 1));
         I.any = (unsigned)__ballot(lane < NF && !(v == 0.0f));
         I.big = (unsigned)__ballot(lane < NF && !(v < kMfSmall));
@@ -2682,10 +2877,10 @@ __device__ __forceinline__ MfInterval mf_interval(const SumJob &jb, int iv, long
     I.block = 0;
     if constexpr (CONSEC) {
         // the widest block (half width w in v) that every fragment (mt, t) allows
-        constexpr int NF = kMfMT * kMfT;
-        const int f = min(lane, NF - 1), mt = f / kMfT, t = f % kMfT;
-        const float b1 = mx((mt * 4 + 1) * kMfT + t), b2 = mx((mt * 4 + 2) * kMfT + t);
-        const float b3 = mx((mt * 4 + 3) * kMfT + t);
+        constexpr int NF = MT * T;
+        const int f = min(lane, NF - 1), mt = f / T, t = f % T;
+        const float b1 = mx((mt * 4 + 1) * T + t), b2 = mx((mt * 4 + 2) * T + t);
+        const float b3 = mx((mt * 4 + 3) * T + t);
         const float w1 = kMfBlockSlope / (b1 + 2.0f * b2 + 3.75f * b3);
         const float w2 = sqrtf(kMfBlockRest / (0.5f * b2 + 1.75f * b3));    // (w <= 1)
         // (NaN and infinite values: no block)
@@ -2701,6 +2896,35 @@ __device__ __forceinline__ MfInterval mf_interval(const SumJob &jb, int iv, long
     return I;
 }
 
+// Rounds [ra, rb) of interval iv (samples a .. end - 1, valid below e) on one
+// wave, within blocks; each(r): the polar state of round r, add(v): takes its
+// inner-product sums.
+template <bool INNER, int MT, int T, bool KERR, typename Each, typename Add>
+__device__ __forceinline__ void mf_blocks(const SumJob &jb, int iv, const MfInterval &I,
+                                          long long a, long long end, long long e, int ra, int rb,
+                                          const float4 *lds, const float *msc, const int *mm,
+                                          MfSampleArea *sa, Each each, Add add) {
+    const double x0 = dev_sample_time(jb.t_start, jb.dt, a) - I.ti;
+    const double w = uniform_f64(0.5 * kMfSPW * I.block * jb.dt * I.inv_h2);
+    const double vscale = uniform_f64(I.inv_h2 / w);
+    for (int r = ra; r < rb;) {
+        // the block of round r, centred at the middle of its samples (the last
+        // one's end with the interval, so |v0| <= 1)
+        const int k = r / I.block, re = min(rb, (k + 1) * I.block);
+        const long long j0 = (long long)k * I.block * kMfSPW;
+        const long long j1 = min(j0 + (long long)I.block * kMfSPW, end - a);
+        const double mid = 0.5 * (double)(j0 + j1 - 1);
+        const double v0 = uniform_f64(fma(fma(mid, jb.dt, x0), I.inv_h2, -1.0));
+        const double vshift = uniform_f64(-(1.0 + v0) / w);
+        MfBlock<MT, T> B;
+        mf_block_form<MT, T>(lds, v0, w, B);
+        for (; r < re; ++r)
+            add(mf_round_block<INNER, MT, T, KERR>(jb, iv, I.ti, vscale, vshift, B,
+                                                   a + (long long)r * kMfSPW, e, msc, mm, each(r),
+                                                   sa));
+    }
+}
+
 // Samples [lo, hi) of one job (matrix-core path), interval by interval.  Every
 // lane of the workgroup runs the same loops over intervals (lo, hi uniform).
 // INNER: each lane's binary64 sums accumulate in its LDS slot
@@ -2709,12 +2933,13 @@ __device__ __forceinline__ MfInterval mf_interval(const SumJob &jb, int iv, long
 template <bool INNER, bool CONSEC>
 __device__ void mf_range(const SumJob &jb, long long lo, long long hi, float4 *lds,
                          float *msc, int *mm, double2 *iacc) {
+    constexpr int MT = kMfMT, T = kMfT;
     lo = mf_align(jb, lo);
     hi = mf_align(jb, hi);
     if (lo >= hi) return;
-    // the waves' sample areas follow the static table in LDS
+    // the waves' sample areas follow the tables in LDS
     const int wave = threadIdx.x / kWave;
-    MfSampleArea *sa = (MfSampleArea *)((char *)lds + kMfTableBytes) + wave;
+    MfSampleArea *sa = (MfSampleArea *)((char *)lds + mf_table_bytes(MT, T)) + wave;
     sa->c[0][threadIdx.x & (kWave - 1)] = make_float2(1.0f, 0.0f);
     __syncthreads();                                // rows of a previous job no longer read
     if ((int)threadIdx.x < kMfRows) {
@@ -2723,6 +2948,7 @@ __device__ void mf_range(const SumJob &jb, long long lo, long long hi, float4 *l
         mm[r] = r < jb.n_mrows ? mr[r].x : mr[jb.n_mrows - 1].x + (r - jb.n_mrows + 1);
     }
     const FEW_AS4 long long *st = cptr(jb.starts);
+    const MfPolar po{nullptr, true, true, 0};
     auto add = [&](double2 v) {
         if constexpr (INNER) {
             double2 a = iacc[threadIdx.x];
@@ -2732,43 +2958,106 @@ __device__ void mf_range(const SumJob &jb, long long lo, long long hi, float4 *l
         }
     };
     for (int iv = mf_interval_of(jb, lo); iv <= jb.K - 2 && lo < hi; ++iv) {
-        const long long a = st[iv], e = min(hi, (long long)st[iv + 1]);
+        const long long a = st[iv], end = st[iv + 1], e = min(hi, end);
         if (e <= lo) continue;
-        const MfInterval I = mf_interval<CONSEC>(jb, iv, a);
-        const float *tab = jb.mtab + (size_t)iv * kMfIntervalFloats;
+        const unsigned short *top = jb.minfo[iv].top;
+        const MfInterval I = mf_interval<CONSEC, MT, T>(
+            jb, iv, [&](int f) { return __uint_as_float((unsigned)top[f] << 16); });
         __syncthreads();                            // previous interval no longer read
         if ((int)threadIdx.x < kMfRows / 2) msc[threadIdx.x] = jb.minfo[iv].scale[threadIdx.x];
-        if (I.block == 0)
-            mf_build_static(tab, lds);
-        else
-            mf_stage(tab, lds);
+        mf_stage(jb.mtab + (size_t)iv * kMfIntervalFloats, lds);
         __syncthreads();
         if (I.block == 0) {
+            mf_convert<MT, T>(lds);
+            __syncthreads();
             // (a wave whose samples of a round all lie past the end skips it)
             for (long long base = lo + (long long)wave * kMfSPW; base < e; base += kMfRound)
-                add(mf_round_static<INNER, CONSEC>(jb, iv, I, base, e, lds, msc, mm, sa));
+                add(mf_round_static<INNER, CONSEC, MT, T, false>(jb, iv, I, base, e, lds, msc, mm,
+                                                                 po, sa));
         } else if constexpr (CONSEC) {
             // the waves take equal contiguous runs of rounds
             const int r0 = (int)((lo - a) / kMfSPW);
             const long long n = (e - lo + kMfSPW - 1) / kMfSPW;
-            const int ra = r0 + (int)(n * wave / kMfWaves), rb = r0 + (int)(n * (wave + 1) / kMfWaves);
-            const double x0 = dev_sample_time(jb.t_start, jb.dt, a) - I.ti;
-            const double w = uniform_f64(0.5 * kMfSPW * I.block * jb.dt * I.inv_h2);
-            const double vscale = uniform_f64(I.inv_h2 / w);
-            for (int r = ra; r < rb;) {
-                // the block of round r, centred at the middle of its samples
-                // (the last one's end with the interval, so |v0| <= 1)
-                const int k = r / I.block, end = min(rb, (k + 1) * I.block);
-                const long long j0 = (long long)k * I.block * kMfSPW;
-                const long long j1 = min(j0 + (long long)I.block * kMfSPW, (long long)st[iv + 1] - a);
-                const double mid = 0.5 * (double)(j0 + j1 - 1);
-                const double v0 = uniform_f64(fma(fma(mid, jb.dt, x0), I.inv_h2, -1.0));
-                const double vshift = uniform_f64(-(1.0 + v0) / w);
-                MfBlock B;
-                mf_block_form(lds, v0, w, B);
-                for (; r < end; ++r)
-                    add(mf_round_block<INNER>(jb, iv, I.ti, vscale, vshift, B,
-                                              a + (long long)r * kMfSPW, e, msc, mm, sa));
+            mf_blocks<INNER, MT, T, false>(
+                jb, iv, I, a, end, e, r0 + (int)(n * wave / kMfWaves),
+                r0 + (int)(n * (wave + 1) / kMfWaves), lds, msc, mm, sa,
+                [&](int) -> const MfPolar & { return po; }, add);
+        }
+        lo = e;
+    }
+}
+
+// The same for requests summed from the binary32 fold table of
+// prepare_kernel (rows of consecutive m): short mode lists, whose operand
+// table would not fit the space of their fold table, and generic Kerr, one
+// polar index k after the other.  Each workgroup forms the operand values of
+// its intervals itself (5 to 8 us per interval and k, all latency).  In Kerr
+// the waves' running sums of 12 rounds at a time stay in LDS, so a (interval,
+// k) is staged once per 6144 samples.  Measured against the vector kernel:
+// 225 terms on 1.26 million samples 86 -> 46 us (shape 2 x 2), 34587 Kerr
+// modes (9 x 1281 terms) on 3.16 million 7230 -> 1000 us (3 x 2); the error
+// against binary64 falls too, 8.1e-7 -> 2.6e-7 and 1.6e-6 -> 4.6e-7.
+template <bool INNER, int MT, int T, bool KERR>
+__device__ void mf_range_terms(const SumJob &jb, long long lo, long long hi, float4 *lds,
+                               double2 *iacc) {
+    lo = mf_align(jb, lo);
+    hi = mf_align(jb, hi);
+    if (lo >= hi) return;
+    __shared__ MfTerms<MT, T> M;
+    const int wave = threadIdx.x / kWave;
+    MfSampleArea *sa = (MfSampleArea *)((char *)lds + mf_table_bytes(MT, T)) + wave;
+    float2 *hp = (float2 *)((char *)lds + mf_table_bytes(MT, T) + kMfWaves * sizeof(MfSampleArea)) +
+                 wave * kMfKerrRounds * kMfSPW;
+    sa->c[0][threadIdx.x & (kWave - 1)] = make_float2(1.0f, 0.0f);
+    const int mm[1] = {jb.mf_m0};
+    const FEW_AS4 long long *st = cptr(jb.starts);
+    auto add = [&](double2 v) {
+        if constexpr (INNER) {
+            double2 a = iacc[threadIdx.x];
+            a.x = a.x + v.x;
+            a.y = a.y + v.y;
+            iacc[threadIdx.x] = a;
+        }
+    };
+    for (int x = threadIdx.x; x < 8 * MT * 32 * T; x += 64 * kMfWaves) (&M.idx[0][0])[x] = -1;
+    // operand values of (interval, polar index) and how its products are formed
+    auto stage = [&](int iv, int kp) {
+        mf_terms_stage<MT, T>(jb, iv, kp, M, lds);
+        const MfInterval I = mf_interval<true, MT, T>(
+            jb, iv, [&](int f) { return __uint_as_float(M.top[f]); });
+        if (I.block == 0) {
+            mf_convert<MT, T>(lds);
+            __syncthreads();
+        }
+        return I;
+    };
+    for (int iv = mf_interval_of(jb, lo); iv <= jb.K - 2 && lo < hi; ++iv) {
+        const long long a = st[iv], end = st[iv + 1], e = min(hi, end);
+        if (e <= lo) continue;
+        // the waves take equal contiguous runs of rounds
+        const int r0 = (int)((lo - a) / kMfSPW);
+        const int n = (int)((e - lo + kMfSPW - 1) / kMfSPW);
+        const int ra = r0 + (int)((long long)n * wave / kMfWaves);
+        const int rb = r0 + (int)((long long)n * (wave + 1) / kMfWaves);
+        // (generic Kerr: at most kMfKerrRounds rounds of each wave at a time)
+        const int most = (n + kMfWaves - 1) / kMfWaves, step = KERR ? kMfKerrRounds : most;
+        for (int c = 0; c < most; c += step) {      // uniform per workgroup
+            const int ca = min(rb, ra + c), cb = min(rb, ca + step);
+            for (int q = KERR ? jb.mf_nk - 1 : 0; q >= 0; --q) {
+                const MfInterval I = stage(iv, jb.mf_k0 + q);
+                MfPolar po{hp, !KERR || q == jb.mf_nk - 1, !KERR || q == 0, jb.mf_k0};
+                auto each = [&](int r) -> const MfPolar & {
+                    if constexpr (KERR) po.hp = hp + (r - ca) * kMfSPW;
+                    return po;
+                };
+                if (I.block == 0) {
+                    for (int r = ca; r < cb; ++r)
+                        add(mf_round_static<INNER, true, MT, T, KERR>(
+                            jb, iv, I, a + (long long)r * kMfSPW, e, lds, M.un, mm, each(r), sa));
+                } else {
+                    mf_blocks<INNER, MT, T, KERR>(jb, iv, I, a, end, e, ca, cb, lds, M.un, mm, sa,
+                                                  each, add);
+                }
             }
         }
         lo = e;
@@ -2814,12 +3103,10 @@ __device__ __forceinline__ void mf_share_w(const float *wl, long long total, lon
     *hi = a + (e - a) * (j + 1) / S;
 }
 
-template <bool INNER, bool CONSEC>
-__global__ __launch_bounds__(64 * kMfWaves) void sum_mfma_kernel(SumJob jb) {
-    extern __shared__ float4 mf_lds[];
-    __shared__ float msc[kMfRows / 2];
-    __shared__ int mm[kMfRows];
-    __shared__ double2 iacc[INNER ? 64 * kMfWaves : 1];
+// A single-request launch: this workgroup's share of the samples through
+// range(lo, hi), its time reported, and (INNER) its sums of iacc in partial.
+template <bool INNER, typename Range>
+__device__ __forceinline__ void mf_single(const SumJob &jb, double2 *iacc, Range range) {
     if constexpr (INNER) iacc[threadIdx.x] = make_double2(0.0, 0.0);
     long long lo, hi;
     // the inner-product launch keeps the equal split (its binary64 sums
@@ -2829,7 +3116,7 @@ __global__ __launch_bounds__(64 * kMfWaves) void sum_mfma_kernel(SumJob jb) {
         mf_share_w(jb.bw, jb.n, &lo, &hi);
     else
         mf_share(jb.n, &lo, &hi);
-    mf_range<INNER, CONSEC>(jb, lo, hi, mf_lds, msc, mm, iacc);
+    range(lo, hi);
     if (!INNER && jb.btime != nullptr && (int)blockIdx.x < kMfBalanceWG) {
         __syncthreads();
         if (threadIdx.x == 0) {
@@ -2853,14 +3140,11 @@ __global__ __launch_bounds__(64 * kMfWaves) void sum_mfma_kernel(SumJob jb) {
     }
 }
 
-// Batched launch: the jobs' samples laid end to end (job j from sample_base_j),
-// split into equal shares.
-template <bool CONSEC>
-__global__ __launch_bounds__(64 * kMfWaves) void sum_mfma_batch_kernel(const SumJob *jobs, int n_jobs,
-                                                             long long total) {
-    extern __shared__ float4 mf_lds[];
-    __shared__ float msc[kMfRows / 2];
-    __shared__ int mm[kMfRows];
+// A batched launch: the jobs' samples laid end to end (job j from
+// sample_base_j), split into equal shares; range(job, a, e).
+template <typename Range>
+__device__ __forceinline__ void mf_batch(const SumJob *jobs, int n_jobs, long long total,
+                                         Range range) {
     long long lo, hi;
     mf_share(total, &lo, &hi);
     int j = 0, top = n_jobs - 1;
@@ -2873,8 +3157,49 @@ __global__ __launch_bounds__(64 * kMfWaves) void sum_mfma_batch_kernel(const Sum
         if (b0 >= hi) break;
         const SumJob jb = load_uniform(jobs + j);
         const long long a = max(lo, b0) - b0, e = min(hi, b0 + jb.n) - b0;
-        if (a < e) mf_range<false, CONSEC>(jb, a, e, mf_lds, msc, mm, nullptr);
+        if (a < e) range(jb, a, e);
     }
+}
+
+template <bool INNER, bool CONSEC>
+__global__ __launch_bounds__(64 * kMfWaves) void sum_mfma_kernel(SumJob jb) {
+    extern __shared__ float4 mf_lds[];
+    __shared__ float msc[kMfRows / 2];
+    __shared__ int mm[kMfRows];
+    __shared__ double2 iacc[INNER ? 64 * kMfWaves : 1];
+    mf_single<INNER>(jb, iacc, [&](long long lo, long long hi) {
+        mf_range<INNER, CONSEC>(jb, lo, hi, mf_lds, msc, mm, iacc);
+    });
+}
+
+template <bool CONSEC>
+__global__ __launch_bounds__(64 * kMfWaves) void sum_mfma_batch_kernel(const SumJob *jobs, int n_jobs,
+                                                             long long total) {
+    extern __shared__ float4 mf_lds[];
+    __shared__ float msc[kMfRows / 2];
+    __shared__ int mm[kMfRows];
+    mf_batch(jobs, n_jobs, total, [&](const SumJob &jb, long long a, long long e) {
+        mf_range<false, CONSEC>(jb, a, e, mf_lds, msc, mm, nullptr);
+    });
+}
+
+template <bool INNER, int MT, int T, bool KERR>
+__global__ __launch_bounds__(64 * kMfWaves) void sum_mfma_terms_kernel(SumJob jb) {
+    extern __shared__ float4 mf_lds[];
+    __shared__ double2 iacc[INNER ? 64 * kMfWaves : 1];
+    mf_single<INNER>(jb, iacc, [&](long long lo, long long hi) {
+        mf_range_terms<INNER, MT, T, KERR>(jb, lo, hi, mf_lds, iacc);
+    });
+}
+
+template <int MT, int T>
+__global__ __launch_bounds__(64 * kMfWaves) void sum_mfma_terms_batch_kernel(const SumJob *jobs,
+                                                                             int n_jobs,
+                                                                             long long total) {
+    extern __shared__ float4 mf_lds[];
+    mf_batch(jobs, n_jobs, total, [&](const SumJob &jb, long long a, long long e) {
+        mf_range_terms<false, MT, T, false>(jb, a, e, mf_lds, nullptr);
+    });
 }
 
 #pragma clang fp contract(on)
@@ -3531,7 +3856,26 @@ hipError_t launch_fold_pack_batch(const PrepJob *jobs_dev, int n_jobs, int max_K
 }
 
 static constexpr size_t mf_lds_bytes() {
-    return kMfTableBytes + kMfWaves * sizeof(MfSampleArea);
+    return mf_table_bytes(kMfMT, kMfT) + kMfWaves * sizeof(MfSampleArea);
+}
+
+static constexpr size_t mf_terms_lds_bytes(int MT, int T, bool kerr) {
+    return mf_table_bytes(MT, T) + kMfWaves * sizeof(MfSampleArea) +
+           (kerr ? sizeof(float2) * kMfWaves * kMfKerrRounds * kMfSPW : 0);
+}
+
+// Calls f(MT, T) with the smallest compiled shape that holds a request's rows
+// and |n| (as std::integral_constants).
+template <typename F>
+static void mf_with_shape(int mt, int t, F f) {
+    using std::integral_constant;
+    using I1 = integral_constant<int, 1>;
+    using I2 = integral_constant<int, 2>;
+    using I3 = integral_constant<int, 3>;
+    if (mt == 1 && t == 1) f(I1{}, I1{});
+    else if (mt <= 2 && t == 1) f(I2{}, I1{});
+    else if (mt <= 2) f(I2{}, I2{});
+    else f(I3{}, I2{});
 }
 
 // One workgroup per compute unit (the operand table takes most of the LDS).
@@ -3550,12 +3894,38 @@ int mfma_workgroups() {
                             (const void *)sum_mfma_batch_kernel<false>};
         for (const void *f : fn)
             hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)mf_lds_bytes());
+        for (int mt = 1; mt <= kMfMT; ++mt)
+            for (int t = 1; t <= kMfT; ++t)
+                mf_with_shape(mt, t, [](auto MT, auto T) {
+                    constexpr int mtv = decltype(MT)::value, tv = decltype(T)::value;
+                    auto set = [](const void *f, bool kerr) {
+                        hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                            (int)mf_terms_lds_bytes(mtv, tv, kerr));
+                    };
+                    set((const void *)sum_mfma_terms_kernel<false, mtv, tv, false>, false);
+                    set((const void *)sum_mfma_terms_kernel<true, mtv, tv, false>, false);
+                    set((const void *)sum_mfma_terms_kernel<false, mtv, tv, true>, true);
+                    set((const void *)sum_mfma_terms_kernel<true, mtv, tv, true>, true);
+                    set((const void *)sum_mfma_terms_batch_kernel<mtv, tv>, false);
+                });
     });
     return cus;
 }
 
 hipError_t launch_sum_mfma(const SumJob &job, int n_wg, hipStream_t stream) {
-    if (job.mf_consec)
+    if (job.mf_terms)
+        mf_with_shape(job.mf_terms / 10, job.mf_terms % 10, [&](auto MT, auto T) {
+            constexpr int mtv = decltype(MT)::value, tv = decltype(T)::value;
+            if (job.n_ph == 3)
+                hipLaunchKernelGGL((sum_mfma_terms_kernel<false, mtv, tv, true>), dim3(n_wg),
+                                   dim3(64 * kMfWaves), mf_terms_lds_bytes(mtv, tv, true), stream,
+                                   job);
+            else
+                hipLaunchKernelGGL((sum_mfma_terms_kernel<false, mtv, tv, false>), dim3(n_wg),
+                                   dim3(64 * kMfWaves), mf_terms_lds_bytes(mtv, tv, false), stream,
+                                   job);
+        });
+    else if (job.mf_consec)
         hipLaunchKernelGGL((sum_mfma_kernel<false, true>), dim3(n_wg), dim3(64 * kMfWaves),
                            mf_lds_bytes(), stream, job);
     else
@@ -3566,7 +3936,19 @@ hipError_t launch_sum_mfma(const SumJob &job, int n_wg, hipStream_t stream) {
 
 hipError_t launch_sum_mfma_inner(const SumJob &job, int n_wg, double two_dt, double *out2,
                                  hipStream_t stream) {
-    if (job.mf_consec)
+    if (job.mf_terms)
+        mf_with_shape(job.mf_terms / 10, job.mf_terms % 10, [&](auto MT, auto T) {
+            constexpr int mtv = decltype(MT)::value, tv = decltype(T)::value;
+            if (job.n_ph == 3)
+                hipLaunchKernelGGL((sum_mfma_terms_kernel<true, mtv, tv, true>), dim3(n_wg),
+                                   dim3(64 * kMfWaves), mf_terms_lds_bytes(mtv, tv, true), stream,
+                                   job);
+            else
+                hipLaunchKernelGGL((sum_mfma_terms_kernel<true, mtv, tv, false>), dim3(n_wg),
+                                   dim3(64 * kMfWaves), mf_terms_lds_bytes(mtv, tv, false), stream,
+                                   job);
+        });
+    else if (job.mf_consec)
         hipLaunchKernelGGL((sum_mfma_kernel<true, true>), dim3(n_wg), dim3(64 * kMfWaves),
                            mf_lds_bytes(), stream, job);
     else
@@ -3587,6 +3969,16 @@ hipError_t launch_sum_mfma_batch(const SumJob *jobs_dev, int n_jobs, long long t
     else
         hipLaunchKernelGGL(sum_mfma_batch_kernel<false>, dim3(n_wg), dim3(64 * kMfWaves),
                            mf_lds_bytes(), stream, jobs_dev, n_jobs, total);
+    return hipGetLastError();
+}
+
+hipError_t launch_sum_mfma_terms_batch(const SumJob *jobs_dev, int n_jobs, long long total, int mt,
+                                       int t, int n_wg, hipStream_t stream) {
+    mf_with_shape(mt, t, [&](auto MT, auto T) {
+        constexpr int mtv = decltype(MT)::value, tv = decltype(T)::value;
+        hipLaunchKernelGGL((sum_mfma_terms_batch_kernel<mtv, tv>), dim3(n_wg), dim3(64 * kMfWaves),
+                           mf_terms_lds_bytes(mtv, tv, false), stream, jobs_dev, n_jobs, total);
+    });
     return hipGetLastError();
 }
 
