@@ -243,7 +243,8 @@ struct HostReq {
     size_t upload_bytes = 0;   // [0, upload_bytes) of the layout comes from the host
     bool mfma = false;         // binary32 sums of this request run on the matrix-core path
     bool terms_ok = false;     // .. from its fold table, where mf_terms_path says so
-    bool mf_terms(long long n) const { return terms_ok && mf_terms_path(terms, n); }
+    bool fp32 = false;
+    bool mf_terms(long long n) const { return terms_ok && mf_terms_path(terms, n, fp32); }
     ~HostReq() { free_term_layout(&terms); }
 };
 
@@ -404,7 +405,8 @@ int make_host_req(int K, const double *t, int M, const int32_t *lmn, bool fp32, 
     int rc = cache->get(M, lmn, width, &r->terms);
     if (rc) return fail(rc, "mode list rejected while building the term layout");
     r->mfma = fp32 && allow_mfma && r->terms.mfma && width == 3;
-    r->terms_ok = fp32 && allow_mfma && !r->mfma;
+    r->fp32 = fp32;
+    r->terms_ok = allow_mfma && !r->mfma;
     r->L = request_layout(fp32, K, M, r->terms.n_segs, r->terms.n_terms, r->terms.n_src,
                           r->terms.n_chunks, r->n_ph, r->mfma, r->terms.n_mrows);
     r->upload_bytes = r->L.upload_end;
@@ -540,6 +542,8 @@ SumJob sum_job(const HostReq &r, ReqBase base, double t_start, double dt, int64_
     j.mf_terms = (signed char)(r.mf_terms(n) ? r.terms.mf_terms : 0);
     j.mf_m0 = (signed char)r.terms.m_min;
     j.mf_k0 = (signed char)r.terms.k_min;
+    j.mf_ns = (signed char)(std::max(-r.terms.n_min, r.terms.n_max) / 2 + 1);
+    j.mf_f64 = r.fp32 ? 0 : 1;
     j.mf_nk = (unsigned char)(r.terms.k_max - r.terms.k_min + 1);
     j.sample_base = 0;
     return j;
@@ -828,8 +832,8 @@ int32_t few_plan_create(const few_plan_desc *desc, few_plan *out) {
         p->fp32 = desc->precision == FEW_MIXED;
         p->resident_wg = p->fp32 ? sum_resident_workgroups(2) : 0;
         p->resident_wg3 = p->fp32 ? sum_resident_workgroups(3) : 0;
-        p->mf_wg = p->fp32 ? mfma_workgroups() : 0;
-        p->allow_mfma = p->fp32 && p->mf_wg > 0 && !(desc->flags & FEW_FLAG_VECTOR_ONLY);
+        p->mf_wg = mfma_workgroups();
+        p->allow_mfma = p->mf_wg > 0 && !(desc->flags & FEW_FLAG_VECTOR_ONLY);
         p->max_knots = desc->max_knots ? desc->max_knots : kMaxKnots;
         p->max_modes = desc->max_modes ? desc->max_modes : 65536;
         p->max_inflight = desc->max_inflight ? desc->max_inflight : 2;
@@ -1129,7 +1133,7 @@ int sum_impl(few_plan p, few_spline s, double theta, double phi, double scale, d
                     return launch_sum_mfma_inner(sj, (int)std::min<long long>(p->mf_wg, need),
                                                  2.0 * dt, out2, p->stream);
                 SumJob sb = sj;
-                if (mf || n >= kMfSplitMin) p->xsplit[p->max_inflight].apply(&sb, p->mf_wg);
+                if (mf || (p->fp32 && n >= kMfSplitMin)) p->xsplit[p->max_inflight].apply(&sb, p->mf_wg);
                 return launch_sum_mfma(sb, p->mf_wg, p->stream);
             }
             return inner ? launch_sum_inner(sj, (int)slots, p->fp32, 2.0 * dt, out2, p->stream)
@@ -1476,7 +1480,7 @@ int launch_batch(few_plan p, Batch *b, hipStream_t s, unsigned *counter) {
             HIP_TRY(launch_prepare(q, fp32, s));
         if (r->h.mfma || u.mf_terms) {
             SumJob ub = u;
-            if (r->h.mfma || u.n >= kMfSplitMin)
+            if (r->h.mfma || (fp32 && u.n >= kMfSplitMin))
                 p->xsplit[(counter - p->counters) / 64].apply(&ub, p->mf_wg);   // this stream's
             HIP_TRY(launch_sum_mfma(ub, p->mf_wg, s));
         } else {
@@ -1540,7 +1544,7 @@ int launch_batch(few_plan p, Batch *b, hipStream_t s, unsigned *counter) {
         const int jobs = first[set + 1] - first[set];
         if (jobs == 0) continue;
         if (set <= kShapes)
-            HIP_TRY(launch_sum_mfma_terms_batch(sd + first[set], jobs, mf_total[set],
+            HIP_TRY(launch_sum_mfma_terms_batch(sd + first[set], jobs, mf_total[set], !fp32,
                                                 (set - 1) / kMfT + 1, (set - 1) % kMfT + 1,
                                                 p->mf_wg, s));
         else

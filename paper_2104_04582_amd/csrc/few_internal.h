@@ -223,6 +223,7 @@ struct SumJob {
     // matrix-core path: rows of consecutive signed m (mtab); sums from the
     // fold table, 10 row tiles + steps needed (0: not); their lowest signed m
     signed char mf_consec, mf_terms, mf_m0;
+    signed char mf_ns;      // steps of two |n| (binary64)
     const float *mtab;      // [K-1][kMfIntervalFloats] operand values
     const MfInfo *minfo;    // [K-1]
     const int2 *mrows;      // [n_mrows + 1]
@@ -235,6 +236,7 @@ struct SumJob {
     unsigned btag;
     signed char mf_k0;      // sums from the fold table: polar indices k0 ..
     unsigned char mf_nk;    // .. k0 + nk - 1
+    signed char mf_f64;     // the fold table is binary64
 };
 
 // Launchers (kernels.hip).  All enqueue on `stream` and return the HIP status.
@@ -285,8 +287,8 @@ hipError_t launch_sum_mfma_inner(const SumJob &job, int n_wg, double two_dt, dou
                                  hipStream_t stream);
 hipError_t launch_sum_mfma_batch(const SumJob *jobs_dev, int n_jobs, long long total,
                                  bool consec, int n_wg, hipStream_t stream);
-hipError_t launch_sum_mfma_terms_batch(const SumJob *jobs_dev, int n_jobs, long long total, int mt,
-                                       int t, int n_wg, hipStream_t stream);
+hipError_t launch_sum_mfma_terms_batch(const SumJob *jobs_dev, int n_jobs, long long total,
+                                       bool f64, int mt, int t, int n_wg, hipStream_t stream);
 hipError_t launch_select(const double *amp, int K, int M, double eps, bool sorted, int *keep,
                          hipStream_t stream);
 constexpr int kMaxSelectModes = 4096;   // LDS: (binary64 key + int index) per padded mode
@@ -330,12 +332,31 @@ struct TermLayout {
 //   1 day, Kerr: 11 rows, |n| <= 8, 187 terms 111 / 91; 9 rows, |n| <= 20, 369
 //     terms 95.8 / 105; 17 rows, |n| <= 12, 425 terms 115 / 140 and 21 rows,
 //     |n| <= 20, 861 terms 201 / 172
+// Binary64: both kernels are bound by the binary64 unit, the vector one with
+// its terms, the matrix one with the cells (row, n) that its products cover,
+// empty ones too; at 3.15 million samples (365 days, 10 s) 46 + 1.07 terms against
+// 125 + 0.5 cells us (full 3843-mode list, 1281 terms of 1536 cells 1460 / 934;
+// 217 of 256 308 / 293; 861 of 1056 1015 / 717; selected lists, 351 of 768
+// 513 / 570 and 870 of 1536 1080 / 927).  With few rounds per wave the margin is
+// wider, since a batch runs its requests of each kind in a launch of their own
+// (six uneven requests, one of 989 terms and 96192 samples: 545 / 585).  Below
+// one round per SIMD the vector kernel's serial walk over the terms is what a
+// call waits for: one day, 77 terms 48.4 / 44.8, 1281 terms 265 / 111, Kerr
+// 5 x 99 terms 148 / 127 (at 3 days 150 / 154).
 // (The fold table, its size and its launches are the same either way.)
-inline bool mf_terms_path(const TermLayout &L, long long n) {
+inline bool mf_terms_path(const TermLayout &L, long long n, bool fp32) {
     if (L.mf_terms == 0) return false;
     const int mt = L.mf_terms / 10, t = L.mf_terms % 10;
     const int shape = mt == 1 && t == 1 ? 0 : mt <= 2 && t == 1 ? 1 : mt <= 2 ? 2 : 3;
     const int nk = L.k_max - L.k_min + 1;
+    if (!fp32) {
+        const int steps = (L.n_max > -L.n_min ? L.n_max : -L.n_min) / 2 + 1;
+        const int cells = 8 * (shape == 0 ? 1 : shape == 3 ? 3 : 2) * 4 * steps;
+        long long least = n >= 262144 ? 74 + cells / 2 : 150 + cells * 11 / 20;
+        const long long brief = nk > 1 && n >= 16384 ? 120 : 72;
+        if (n < 65536 && least > brief) least = brief;
+        return L.n_terms >= least * nk;
+    }
     static const int kShortKerr[4] = {136, 160, 450, 660};
     static const int kShort[4] = {124, 140, 216, 300};
     static const int kLong[4] = {80, 96, 160, 180};

@@ -2289,6 +2289,26 @@ __device__ __forceinline__ unsigned lanes_max(unsigned v) {
     return v;
 }
 
+// Terms of polar index kp into idx[row][n + half] (rows of `stride`); the waves
+// take its segments in turn.
+__device__ __forceinline__ void mf_terms_scatter(const SumJob &jb, int kp, int half, int stride,
+                                                 int *idx, int lane, int wave) {
+    int turn = 0;
+    for (int g0 = 0; g0 < jb.n_segs; g0 += kWave) {
+        const int4 S = jb.segs[min(g0 + lane, jb.n_segs - 1)];
+        unsigned long long hit = __ballot(g0 + lane < jb.n_segs && seg_k(S.x) == kp);
+        for (; hit; hit &= hit - 1, ++turn) {
+            if ((turn & (kMfWaves - 1)) != wave) continue;
+            const int src = __ffsll((long long)hit) - 1;
+            const int row = __builtin_amdgcn_readlane(S.x, src) - 256 * kp - jb.mf_m0;
+            const int n_lo = __builtin_amdgcn_readlane(S.y, src);
+            const int len = __builtin_amdgcn_readlane(S.z, src);
+            const int first = __builtin_amdgcn_readlane(S.w, src);
+            for (int q = lane; q < len; q += kWave) idx[row * stride + n_lo + q + half] = first + q;
+        }
+    }
+}
+
 // The operand values of interval iv and polar index kp (0 in Schwarzschild),
 // from the binary32 fold table: the values that fold_pack writes, formed in
 // binary32.  M.idx holds -1 everywhere on entry and on return.  A lane takes
@@ -2304,22 +2324,7 @@ __device__ __forceinline__ void mf_terms_stage(const SumJob &jb, int iv, int kp,
     __syncthreads();                                // the previous values no longer read
     if (tid < 4 * MT) M.pmax[tid] = 0u;
     if (tid < MT * 4 * T) M.top[tid] = 0u;
-    {
-        int turn = 0;       // the waves take the segments of this k in turn
-        for (int g0 = 0; g0 < jb.n_segs; g0 += kWave) {
-            const int4 S = jb.segs[min(g0 + lane, jb.n_segs - 1)];
-            unsigned long long hit = __ballot(g0 + lane < jb.n_segs && seg_k(S.x) == kp);
-            for (; hit; hit &= hit - 1, ++turn) {
-                if ((turn & (kMfWaves - 1)) != wave) continue;
-                const int src = __ffsll((long long)hit) - 1;
-                const int row = __builtin_amdgcn_readlane(S.x, src) - 256 * kp - jb.mf_m0;
-                const int n_lo = __builtin_amdgcn_readlane(S.y, src);
-                const int len = __builtin_amdgcn_readlane(S.z, src);
-                const int first = __builtin_amdgcn_readlane(S.w, src);
-                for (int q = lane; q < len; q += kWave) M.idx[row][n_lo + q + 16 * T] = first + q;
-            }
-        }
-    }
+    mf_terms_scatter(jb, kp, 16 * T, 32 * T, &M.idx[0][0], lane, wave);
     __syncthreads();
     constexpr int kTasks = MT * T * 2, kTurns = (kTasks + kMfWaves - 1) / kMfWaves;
     // (terms are stored in reverse order, 8 values each)
@@ -3161,6 +3166,587 @@ __device__ __forceinline__ void mf_batch(const SumJob *jobs, int n_jobs, long lo
     }
 }
 
+// ---- binary64 on the matrix cores ------------------------------------------
+// The same contraction from the binary64 fold table on
+// v_mfma_f64_16x16x4_f64: 16 matrix rows (8 signed m, re/im) by 16 samples,
+// two values of a = |n| (re/im columns) per product, f^a by a recurrence in
+// f^2 per column lane.  Products and vector binary64 arithmetic share one unit
+// (measured: they add), and it is the bound, so the count of binary64
+// operations per term decides: the vector kernel spends 10 FMAs per term
+// (cubic and recurrence), a product spends 2 per power of v (n and -n meet in
+// one column pair).
+//
+// The cubic is written about the centre v0 of a block of 32 or 16 samples, with
+// d = v - v0:
+//   C(v) = T_0 + d T_1 + d^2 (b_2 + (3 v0 + d) b_3),
+//   T_0 = C(v0), T_1 = C'(v0),
+// T_0 and T_1 formed in binary64 from the staged b_p for each use (6 operations of
+// 4 cycles against 4 or 2 products of 64).  The rest is small: |d| <= w, half the
+// block's width in v.  Where (M_2 + 4 M_3) w^2 <= 2^-30 M_0 (M_p the largest |b_p| of the
+// interval, M_0 of p <= 1) it is summed from fp16 hi + lo operands with binary32
+// accumulation, 22 bits and so below 2^-52 M_0 (the vector kernel's Horner
+// recurrence rounds at 2^-53 of its running sum for each of its terms), at 1/16
+// of the binary64 products' cost: 4 binary64 operations per term in all.  Else
+// T_2 = C''(v0) / 2 takes binary64 products too and only d^3 b_3 is left to
+// fp16 (w^3 M_3 <= 2^-30 M_0), else all four powers take them.
+// Measured (3843 modes, 1281 terms, 3.16 million samples): 1430 -> 920 us, of which
+// the products 560 at the rate of a large binary64 matrix product; the largest
+// error against the oracle 1e-15 to 2e-15, the vector kernel's 5e-15 and more.
+struct MfPlan64 {
+    int P;          // powers in binary64 products: 2, 3 or 4
+    int nt;         // P = 2: sample tiles of 16 per block, 2 or 1
+    bool lo3;       // b_3 of the rest takes all three fp16 products
+};
+
+template <int MT, int T>
+struct MfTerms64 {
+    int idx[8 * MT][32 * T];            // n + 16 T; -1: no term
+    unsigned m01[4 * MT], m2[4 * MT], m3[4 * MT];   // largest |b_p| per row pair (binary32 bits)
+    float un[4 * MT];                   // 2^E of the fp16 values
+};
+
+// Cubic in u -> cubic in v = 2 u - 1.
+__device__ __forceinline__ void mf_recentre(double a0, double a1, double a2, double a3, double *b) {
+    const double h1 = 0.5 * a1, h2 = 0.25 * a2, h3 = 0.125 * a3;
+    b[0] = a0 + (h1 + (h2 + h3));
+    b[1] = h1 + fma(2.0, h2, 3.0 * h3);
+    b[2] = fma(3.0, h3, h2);
+    b[3] = h3;
+}
+
+// LDS: base [mt][step][p][lane 64] doubles, then rest [mt][p - 2][t][hi, lo][lane 64][8].
+static constexpr size_t mf64_base_bytes(int MT, int ns) { return (size_t)MT * ns * 2048; }
+static constexpr size_t mf64_rest_bytes(int MT, int T) { return (size_t)MT * 2 * T * 2048; }
+
+// Operand values of interval iv and polar index kp: mf_terms_stage in binary64.
+// Lane 16 k + rho of a product's left operand holds row rho = 4 i + g of (signed m
+// 2 g + i / 2, component i % 2) and column k = 2 (a % 2) + component, so that a
+// result lane (16 g + sample) holds both components of rows 2 g and 2 g + 1, as
+// the fp16 products' does.
+template <int MT, int T>
+__device__ __forceinline__ void mf64_stage(const SumJob &jb, int iv, int kp, int ns,
+                                           MfTerms64<MT, T> &M, double *base, unsigned *rest) {
+    int tid = threadIdx.x;
+    asm volatile("" : "+v"(tid));       // (addresses formed here, not kept through the rounds)
+    const int lane = tid & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+    __syncthreads();                                // the previous values no longer read
+    if (tid < 4 * MT) M.m01[tid] = M.m2[tid] = M.m3[tid] = 0u;
+    mf_terms_scatter(jb, kp, 16 * T, 32 * T, &M.idx[0][0], lane, wave);
+    __syncthreads();
+    constexpr int kTasks = MT * T * 2, kTurns = (kTasks + kMfWaves - 1) / kMfWaves;
+    const double2 *last = (const double2 *)jb.table + ((size_t)iv * jb.n_terms + jb.n_terms - 1) * 4;
+    double2 v[kTurns][8];
+#pragma unroll
+    for (int q = 0; q < kTurns; ++q) {
+        const int task = min(wave + q * kMfWaves, kTasks - 1);      // (mt, t, half of the a)
+        const int row = 8 * (task / (2 * T)) + (lane >> 3), a = 8 * (task % (2 * T)) + (lane & 7);
+        const int tp = M.idx[row][16 * T + a], tq = a > 0 ? M.idx[row][16 * T - a] : -1;
+        const double2 *cp = last - 4 * (size_t)max(tp, 0), *cq = last - 4 * (size_t)max(tq, 0);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            v[q][i] = cp[i];
+            v[q][4 + i] = cq[i];
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            if (tp < 0) v[q][i] = make_double2(0.0, 0.0);
+            if (tq < 0) v[q][4 + i] = make_double2(0.0, 0.0);
+        }
+    }
+    __builtin_amdgcn_wave_barrier();
+#pragma unroll
+    for (int q = 0; q < kTurns; ++q) {
+        if (wave + q * kMfWaves >= kTasks) continue;
+        const int task = wave + q * kMfWaves;
+        const int row = 8 * (task / (2 * T)) + (lane >> 3), a = 8 * (task % (2 * T)) + (lane & 7);
+        M.idx[row][16 * T + a] = -1;
+        M.idx[row][16 * T - a] = -1;
+        unsigned m01 = 0, m2 = 0, m3 = 0;
+#pragma unroll
+        for (int h = 0; h < 8; h += 4) {
+            double b[4], c[4];
+            mf_recentre(v[q][h].x, v[q][h + 1].x, v[q][h + 2].x, v[q][h + 3].x, b);
+            mf_recentre(v[q][h].y, v[q][h + 1].y, v[q][h + 2].y, v[q][h + 3].y, c);
+            auto up = [](unsigned m, double x, double y) {
+                return max(m, max(abs_bits((float)x), abs_bits((float)y)));
+            };
+            m01 = up(up(m01, b[0], c[0]), b[1], c[1]);
+            m2 = up(m2, b[2], c[2]);
+            m3 = up(m3, b[3], c[3]);
+        }
+        m01 = lanes_max<4>(m01);                    // the 8 columns of two rows
+        m2 = lanes_max<4>(m2);
+        m3 = lanes_max<4>(m3);
+        if ((lane & 15) == 0) {
+            atomicMax(&M.m01[row >> 1], m01);
+            atomicMax(&M.m2[row >> 1], m2);
+            atomicMax(&M.m3[row >> 1], m3);
+        }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < kTurns; ++q) {
+        if (wave + q * kMfWaves >= kTasks) continue;
+        const int task = wave + q * kMfWaves, mt = task / (2 * T), ta = task % (2 * T);
+        const int r = lane >> 3, a = 8 * ta + (lane & 7), t = ta >> 1;
+        const float mx = __uint_as_float(max(M.m2[4 * mt + (r >> 1)], M.m3[4 * mt + (r >> 1)]));
+        int e = 0;
+        if (mx > 0.0f && mx < INFINITY) frexpf(mx, &e);
+        e = min(max(e, -126), 127);
+        const double sc = ldexp(1.0, -e);
+        if ((lane & 15) == 0) M.un[4 * mt + (r >> 1)] = ldexpf(1.0f, e);
+        // columns per power: (Re P + Re Q, Im Q - Im P) of row component 0,
+        // (Im P + Im Q, Re P - Re Q) of component 1
+        const double2 *P = v[q], *Q = v[q] + 4;
+        double o[2][2][4];
+        mf_recentre(P[0].x + Q[0].x, P[1].x + Q[1].x, P[2].x + Q[2].x, P[3].x + Q[3].x, o[0][0]);
+        mf_recentre(Q[0].y - P[0].y, Q[1].y - P[1].y, Q[2].y - P[2].y, Q[3].y - P[3].y, o[0][1]);
+        mf_recentre(P[0].y + Q[0].y, P[1].y + Q[1].y, P[2].y + Q[2].y, P[3].y + Q[3].y, o[1][0]);
+        mf_recentre(P[0].x - Q[0].x, P[1].x - Q[1].x, P[2].x - Q[2].x, P[3].x - Q[3].x, o[1][1]);
+        const int step = a >> 1, g = (a >> 2) & 3, j = a & 3;
+#pragma unroll
+        for (int c = 0; c < 2; ++c) {
+            if (step < ns) {
+                const int rho = 4 * (2 * (r & 1) + c) + (r >> 1);
+                double *d = base + (size_t)(mt * ns + step) * 256 + rho + 32 * (a & 1);
+#pragma unroll
+                for (int p = 0; p < 4; ++p) {
+                    d[64 * p] = o[c][0][p];
+                    d[64 * p + 16] = o[c][1][p];
+                }
+            }
+            // a = 16 t + 4 g + j: fragment lane 2 r + c + 16 g, values 2 j, 2 j + 1
+#pragma unroll
+            for (int p = 2; p < 4; ++p) {
+                unsigned hi, lo;
+                split_pair((float)(o[c][0][p] * sc), (float)(o[c][1][p] * sc), hi, lo);
+                unsigned *f = rest + (((mt * 2 + p - 2) * T + t) * 128 + 2 * r + c + 16 * g) * 4 + j;
+                f[0] = hi;
+                f[256] = lo;
+            }
+        }
+    }
+    __syncthreads();
+}
+
+// How the interval's rounds are summed (every wave forms the same).
+template <int MT, int T>
+__device__ __forceinline__ MfPlan64 mf64_plan(const SumJob &jb, double inv_h2,
+                                              const MfTerms64<MT, T> &M) {
+    unsigned b01 = 0, b2 = 0, b3 = 0;
+#pragma unroll
+    for (int i = 0; i < 4 * MT; ++i) {
+        b01 = max(b01, M.m01[i]);
+        b2 = max(b2, M.m2[i]);
+        b3 = max(b3, M.m3[i]);
+    }
+    const float M0 = uniform_f32(__uint_as_float(b01)), M2 = uniform_f32(__uint_as_float(b2)),
+                M3 = uniform_f32(__uint_as_float(b3));
+    // half width of a block of 32 samples
+    const float w = uniform_f32(fminf((float)(16.0 * jb.dt * inv_h2), 1.0f));
+    MfPlan64 I{4, 1, true};
+    // (NaN, infinite and tiny values: all in binary64)
+    if (M0 > 1e-30f && M0 < 1e30f && M2 < 1e30f && M3 < 1e30f) {
+        const float lim = 0x1p-30f * M0, q = (M2 + 4.0f * M3) * w * w;
+        if (q <= 4.0f * lim) {
+            I.P = 2;
+            I.nt = q <= lim ? 2 : 1;
+        } else if (M3 * w * w * w <= lim) {
+            I.P = 3;
+        }
+        const float u = I.nt == 2 ? w : 0.5f * w;
+        I.lo3 = !(I.P == 2 && (M2 + 8192.0f * M3) * u * u <= lim);
+    }
+    return I;
+}
+
+__device__ __forceinline__ void cmul64(double ar, double ai, double br, double bi, double *r,
+                                       double *i) {
+    *r = fma(ar, br, -(ai * bi));
+    *i = fma(ar, bi, ai * br);
+}
+
+struct MfPolar64 {
+    double2 *hp;            // this round's running values
+    bool first, last;       // highest, lowest k
+    int k0;
+};
+
+// fp16 sum over |n| of the rest of one sample tile: the columns f^a.
+template <int T>
+__device__ __forceinline__ void mf64_columns(float fr, float fi, mf_u4 (&bh)[T], mf_u4 (&bl)[T]) {
+    const int g = (threadIdx.x & (kWave - 1)) >> 4;
+    float r2, i2, r3, i3, r4, i4, r8, i8, cr, ci;
+    cmulf(fr, fi, fr, fi, &r2, &i2);
+    cmulf(r2, i2, fr, fi, &r3, &i3);
+    cmulf(r2, i2, r2, i2, &r4, &i4);
+    cmulf(r4, i4, r4, i4, &r8, &i8);
+    cmulf(g & 1 ? r4 : 1.0f, g & 1 ? i4 : 0.0f, g & 2 ? r8 : 1.0f, g & 2 ? i8 : 0.0f, &cr, &ci);
+    float w[8] = {cr, ci};
+    cmulf(cr, ci, fr, fi, &w[2], &w[3]);
+    cmulf(cr, ci, r2, i2, &w[4], &w[5]);
+    cmulf(cr, ci, r3, i3, &w[6], &w[7]);
+    float r16, i16;
+    cmulf(r8, i8, r8, i8, &r16, &i16);
+#pragma unroll
+    for (int t = 0; t < T; ++t) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            if (t > 0) {
+                float nr, ni;
+                cmulf(w[2 * i], w[2 * i + 1], r16, i16, &nr, &ni);
+                w[2 * i] = nr;
+                w[2 * i + 1] = ni;
+            }
+            unsigned h, l;
+            split_pair(w[2 * i], w[2 * i + 1], h, l);
+            bh[t][i] = h;
+            bl[t][i] = l;
+        }
+    }
+}
+
+typedef double mf_double4 __attribute__((ext_vector_type(4)));
+
+// 4 x 4 exchange between the 16-lane groups: x[q] of group g <- x[g] of group q.
+__device__ __forceinline__ void lane_transpose(float (&x)[4]) {
+    lane_swap32(x[0], x[2]);
+    lane_swap32(x[1], x[3]);
+    lane_swap16(x[0], x[1]);
+    lane_swap16(x[2], x[3]);
+}
+
+// This lane's sample from the rows of one tile: c[i][g] holds component i % 2 of
+// row 2 g + i / 2; sum over the 8 rows of E^row (the row's value), by Horner.
+template <typename R>
+__device__ __forceinline__ void mf64_rows(const R (&c)[4][4], R er, R ei, R *yr, R *yi) {
+    R sr = c[2][3], si = c[3][3];
+#pragma unroll
+    for (int row = 6; row >= 0; --row) {
+        const R vr = c[2 * (row & 1)][row >> 1], vi = c[2 * (row & 1) + 1][row >> 1];
+        const R nr = fmar(sr, er, fmar(-si, ei, vr));
+        si = fmar(sr, ei, fmar(si, er, vi));
+        sr = nr;
+    }
+    *yr = sr;
+    *yi = si;
+}
+
+// The rest of a round, sum of d^(P-2).. b_p f^a over fp16 operands, without its factor
+// d^2 (P = 2) or d^3 (P = 3): this lane's sample.
+template <int MT, int T, int P>
+__device__ __forceinline__ void mf64_rest(const uint4 *rest, const float *un, bool lo3, float fr,
+                                          float fi, float vq, float er, float ei, float e8r,
+                                          float e8i, float *yr, float *yi) {
+    const int lane = threadIdx.x & (kWave - 1), col = lane & 15, g = lane >> 4;
+    mf_u4 bh[4][T], bl[4][T];
+    float vv[4];
+#pragma unroll
+    for (int nt = 0; nt < 4; ++nt) {
+        const int src = 16 * nt + col;
+        mf64_columns<T>(__shfl(fr, src), __shfl(fi, src), bh[nt], bl[nt]);
+        vv[nt] = __shfl(vq, src);
+    }
+    float sr = 0.0f, si = 0.0f;
+#pragma unroll 1
+    for (int mt = MT - 1; mt >= 0; --mt) {
+        mf_float4 s[4];
+        auto prod = [&](uint4 A, const mf_u4 (&B)[4][T], int t) {
+#pragma unroll
+            for (int nt = 0; nt < 4; ++nt)
+                s[nt] = __builtin_amdgcn_mfma_f32_16x16x32_f16(
+                    __builtin_bit_cast(mf_half8, A), __builtin_bit_cast(mf_half8, B[nt][t]), s[nt],
+                    0, 0, 0);
+        };
+#pragma unroll
+        for (int nt = 0; nt < 4; ++nt) s[nt] = mf_float4{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+        for (int p = 3; p >= P; --p) {
+            if (p == 2) {
+#pragma unroll
+                for (int nt = 0; nt < 4; ++nt)
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) s[nt][i] = s[nt][i] * vv[nt];
+            }
+#pragma unroll
+            for (int t = 0; t < T; ++t) {
+                const uint4 *f = rest + ((mt * 2 + p - 2) * T + t) * 128 + lane;
+                const uint4 ah = f[0];
+                if (p == 2 || lo3) {
+                    prod(f[64], bh, t);
+                    prod(ah, bl, t);
+                }
+                prod(ah, bh, t);
+            }
+        }
+        const float u = un[4 * mt + g];
+        float c[4][4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+#pragma unroll
+            for (int nt = 0; nt < 4; ++nt) c[i][nt] = s[nt][i] * u;
+            lane_transpose(c[i]);
+        }
+        float wr, wi;
+        mf64_rows<float>(c, er, ei, &wr, &wi);
+        const float nr = fmar(sr, e8r, fmar(-si, e8i, wr));
+        si = fmar(sr, e8i, fmar(si, e8r, wi));
+        sr = nr;
+    }
+    *yr = sr;
+    *yi = si;
+}
+
+// One round of a wave: the 64 samples wbase + l, P powers in binary64, blocks of
+// NT sample tiles (P = 4: none, v0 = 0).
+template <bool INNER, int MT, int T, bool KERR, int P, int NT>
+__device__ __forceinline__ double2 mf64_round(const SumJob &jb, int iv, double ti, double inv_h2,
+                                              bool lo3, long long wbase, long long e, int ns,
+                                              const double *base, const uint4 *rest,
+                                              const float *un, const MfPolar64 &po) {
+    const int lane = threadIdx.x & (kWave - 1), col = lane & 15, g = lane >> 4;
+    const FEW_AS4 double *pc = cptr(jb.pcoef) + (size_t)iv * (KERR ? 24 : 16);
+    const long long jo = wbase + lane;
+    double2 dv = make_double2(0.0, 0.0);
+    if constexpr (INNER) {
+        if (jo < e) dv = ((const double2 *)jb.data)[jo];
+    }
+    // this lane's sample; v at the centre of the round's first block, and the
+    // step from block to block
+    const dd x = two_sum(dev_sample_time(jb.t_start, jb.dt, jo < e ? jo : e - 1), -ti);
+    double vc = 0.0, vs = 0.0;
+    if constexpr (P < 4) {
+        const double xm = dev_sample_time(jb.t_start, jb.dt, wbase) - ti;
+        vc = uniform_f64(fma(fma(0.5 * (16 * NT - 1), jb.dt, xm), inv_h2, -1.0));
+        vs = uniform_f64(16.0 * NT * jb.dt * inv_h2);
+    }
+    const double v0 = fma((double)(g / NT), vs, vc);        // of this lane's block
+    const double dl = fma(x.hi, inv_h2, -1.0) - v0;
+    double z0r = 1.0, z0i = 0.0, tr = 1.0, tth = 0.0, Er, Ei, fr, fi;
+    {
+        const double pf = phase_eval<true>(pc, x), pr = phase_eval<true>(pc + 8, x);
+        unit_phasor<double>(pf, &Er, &Ei);
+        unit_phasor<double>(pr, &fr, &fi);
+        if constexpr (KERR) {
+            const double pt = phase_eval<true>(pc + 16, x);
+            unit_phasor<double>(pt, &tr, &tth);
+            if (po.last && po.k0 != 0)
+                unit_phasor<double>(d_reduce_2pi((double)po.k0 * pt), &z0r, &z0i);
+        }
+    }
+    double E8r, E8i, hr, hq;
+    {
+        double E2r, E2i, E4r, E4i;
+        cmul64(Er, Ei, Er, Ei, &E2r, &E2i);
+        cmul64(E2r, E2i, E2r, E2i, &E4r, &E4i);
+        cmul64(E4r, E4i, E4r, E4i, &E8r, &E8i);
+        if (!KERR || po.last) {
+            // z_0 = E^{m_0} (e^{-i k_0 Phi_theta}) from the binary powers
+            const int m0 = jb.mf_m0, am = m0 < 0 ? -m0 : m0;
+            double ar = 1.0, ai = 0.0;
+            auto take = [&](double r, double i) {
+                double nr, ni;
+                cmul64(ar, ai, r, i, &nr, &ni);
+                ar = nr;
+                ai = ni;
+            };
+            if (am & 1) take(Er, Ei);
+            if (am & 2) take(E2r, E2i);
+            if (am & 4) take(E4r, E4i);
+            if (am & 8) take(E8r, E8i);
+            if (am & 16) {
+                take(E8r, E8i);
+                take(E8r, E8i);
+            }
+            if (m0 < 0) ai = -ai;
+            if (KERR && po.k0 != 0) take(z0r, z0i);
+            z0r = ar;
+            z0i = ai;
+        }
+    }
+    float yr = 0.0f, yi = 0.0f;
+    if constexpr (P < 4)
+        mf64_rest<MT, T, P>(rest, un, lo3, (float)fr, (float)fi, (float)fma(3.0, v0, dl), (float)Er,
+                            (float)Ei, (float)E8r, (float)E8i, &yr, &yi);
+    double sr = 0.0, si = 0.0;
+#pragma unroll 1
+    for (int n0 = 0; n0 < 4; n0 += NT) {
+        const double vb = uniform_f64(fma((double)(n0 / NT), vs, vc));
+        mf_double4 acc[MT][P][NT];
+        double own[NT], oth[NT], f2r[NT], f2i[NT];
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) {
+            // columns: lane group g holds component g % 2 of f^a, a = 2 s + g / 2
+            // in step s
+            const int src = 16 * (n0 + nt) + col;
+            const double ar = __shfl(fr, src), ai = __shfl(fi, src);
+            double i2;
+            cmul64(ar, ai, ar, ai, &f2r[nt], &i2);
+            const double pr = g & 2 ? ar : 1.0, pi = g & 2 ? ai : 0.0;
+            own[nt] = g & 1 ? pi : pr;
+            oth[nt] = g & 1 ? pr : pi;
+            f2i[nt] = g & 1 ? i2 : -i2;
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+                for (int p = 0; p < P; ++p) acc[mt][p][nt] = mf_double4{0.0, 0.0, 0.0, 0.0};
+        }
+        const double *b = base + lane;
+#pragma unroll 1
+        for (int s = 0; s < ns; ++s, b += 256) {
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt) {
+                const double *bm = b + (size_t)mt * ns * 256;
+                const double b0 = bm[0], b1 = bm[64], b2 = bm[128], b3 = bm[192];
+                double q[4] = {b0, b1, b2, b3};
+                if constexpr (P < 4) {
+                    const double h = fma(vb, b3, b2);
+                    q[0] = fma(vb, fma(vb, h, b1), b0);
+                    q[1] = fma(vb, fma(vb, b3, h + h), b1);
+                    if constexpr (P == 3) q[2] = fma(vb, b3 + b3, h);
+                }
+#pragma unroll
+                for (int p = 0; p < P; ++p)
+#pragma unroll
+                    for (int nt = 0; nt < NT; ++nt)
+                        acc[mt][p][nt] = __builtin_amdgcn_mfma_f64_16x16x4f64(
+                            q[p], own[nt], acc[mt][p][nt], 0, 0, 0);
+            }
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt) {
+                const double o = fma(own[nt], f2r[nt], oth[nt] * f2i[nt]);
+                oth[nt] = fma(oth[nt], f2r[nt], -(own[nt] * f2i[nt]));
+                own[nt] = o;
+            }
+        }
+        // rows: z_r = z_0 E^{2g} E^{8 mt} (E for the odd row), Horner in E^8
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) {
+            const int src = 16 * (n0 + nt) + col;
+            const double d = __shfl(dl, src), er = __shfl(Er, src), ei = __shfl(Ei, src);
+            const double e8r = __shfl(E8r, src), e8i = __shfl(E8i, src);
+            double yr = 0.0, yi = 0.0;
+#pragma unroll
+            for (int mt = MT - 1; mt >= 0; --mt) {
+                double c[4];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    c[i] = acc[mt][P - 1][nt][i];
+#pragma unroll
+                    for (int p = P - 2; p >= 0; --p) c[i] = fma(d, c[i], acc[mt][p][nt][i]);
+                }
+                const double wr = fma(er, c[2], fma(-ei, c[3], c[0]));
+                const double wi = fma(er, c[3], fma(ei, c[2], c[1]));
+                const double nr = mt == MT - 1 ? wr : fma(yr, e8r, fma(-yi, e8i, wr));
+                yi = mt == MT - 1 ? wi : fma(yr, e8i, fma(yi, e8r, wi));
+                yr = nr;
+            }
+            // times E^{2g}, summed over the lane groups; the tile's own lanes keep it
+            double e2r, e2i, e4r, e4i, gr, gi, hr, hi;
+            cmul64(er, ei, er, ei, &e2r, &e2i);
+            cmul64(e2r, e2i, e2r, e2i, &e4r, &e4i);
+            cmul64(g & 1 ? e2r : 1.0, g & 1 ? e2i : 0.0, g & 2 ? e4r : 1.0, g & 2 ? e4i : 0.0, &gr, &gi);
+            cmul64(yr, yi, gr, gi, &hr, &hi);
+            hr = hr + __shfl_xor(hr, 16);
+            hi = hi + __shfl_xor(hi, 16);
+            hr = hr + __shfl_xor(hr, 32);
+            hi = hi + __shfl_xor(hi, 32);
+            sr = g == n0 + nt ? hr : sr;
+            si = g == n0 + nt ? hi : si;
+        }
+    }
+    if constexpr (P < 4) {
+        const double w = P == 2 ? dl * dl : dl * dl * dl;
+        sr = fma(w, (double)yr, sr);
+        si = fma(w, (double)yi, si);
+    }
+    if constexpr (KERR) {
+        if (!po.first) {
+            const double2 q = po.hp[lane];
+            const double nr = fma(q.x, tr, fma(-q.y, tth, sr));
+            si = fma(q.x, tth, fma(q.y, tr, si));
+            sr = nr;
+        }
+        if (!po.last) {
+            po.hp[lane] = make_double2(sr, si);
+            __builtin_amdgcn_wave_barrier();
+            return make_double2(0.0, 0.0);
+        }
+    }
+    cmul64(sr, si, z0r, z0i, &hr, &hq);
+    double dh = 0.0, hh = 0.0;
+    if (jo < e) {
+        if constexpr (INNER) {
+            dh = dv.x * hr + dv.y * hq;
+            hh = hr * hr + hq * hq;
+        } else {
+            ((double2 *)jb.out)[jo] = make_double2(hr, hq);
+        }
+    }
+    return make_double2(dh, hh);
+}
+
+constexpr int kMfKerrRounds64 = 3;
+
+// Samples [lo, hi) of one job, interval by interval (mf_range_terms in
+// binary64).
+template <bool INNER, int MT, int T, bool KERR>
+__device__ void mf_range_f64(const SumJob &jb, long long lo, long long hi, double *base,
+                             double2 *iacc) {
+    lo = mf_align(jb, lo);
+    hi = mf_align(jb, hi);
+    if (lo >= hi) return;
+    __shared__ MfTerms64<MT, T> M;
+    const int wave = threadIdx.x / kWave, ns = jb.mf_ns;
+    unsigned *rest = (unsigned *)((char *)base + mf64_base_bytes(MT, ns));
+    double2 *hp = (double2 *)((char *)rest + mf64_rest_bytes(MT, T)) + wave * kMfKerrRounds64 * kMfSPW;
+    const FEW_AS4 long long *st = cptr(jb.starts);
+    for (int x = threadIdx.x; x < 8 * MT * 32 * T; x += 64 * kMfWaves) (&M.idx[0][0])[x] = -1;
+    for (int iv = mf_interval_of(jb, lo); iv <= jb.K - 2 && lo < hi; ++iv) {
+        const long long a = st[iv], end = st[iv + 1], e = min(hi, end);
+        if (e <= lo) continue;
+        const double ti = uniform_f64(jb.t[iv]);
+        const double inv_h2 = uniform_f64(2.0 / (jb.t[iv + 1] - ti));
+        const int r0 = (int)((lo - a) / kMfSPW);
+        const int n = (int)((e - lo + kMfSPW - 1) / kMfSPW);
+        const int ra = r0 + (int)((long long)n * wave / kMfWaves);
+        const int rb = r0 + (int)((long long)n * (wave + 1) / kMfWaves);
+        const int most = (n + kMfWaves - 1) / kMfWaves, step = KERR ? kMfKerrRounds64 : most;
+        for (int c = 0; c < most; c += step) {      // uniform per workgroup
+            const int ca = min(rb, ra + c), cb = min(rb, ca + step);
+            for (int q = KERR ? jb.mf_nk - 1 : 0; q >= 0; --q) {
+                mf64_stage<MT, T>(jb, iv, jb.mf_k0 + q, ns, M, base, rest);
+                const MfPlan64 I = mf64_plan<MT, T>(jb, inv_h2, M);
+                MfPolar64 po{hp, !KERR || q == jb.mf_nk - 1, !KERR || q == 0, jb.mf_k0};
+                auto run = [&](auto P, auto NT) {
+                    for (int r = ca; r < cb; ++r) {
+                        if constexpr (KERR) po.hp = hp + (r - ca) * kMfSPW;
+                        const double2 v = mf64_round<INNER, MT, T, KERR, decltype(P)::value, decltype(NT)::value>(
+                            jb, iv, ti, inv_h2, I.lo3, a + (long long)r * kMfSPW, e, ns, base,
+                            (const uint4 *)rest, M.un, po);
+                        if constexpr (INNER) {
+                            double2 s = iacc[threadIdx.x];
+                            s.x = s.x + v.x;
+                            s.y = s.y + v.y;
+                            iacc[threadIdx.x] = s;
+                        }
+                    }
+                };
+                using std::integral_constant;
+                if (I.P == 2 && I.nt == 2)
+                    run(integral_constant<int, 2>{}, integral_constant<int, 2>{});
+                else if (I.P == 2)
+                    run(integral_constant<int, 2>{}, integral_constant<int, 1>{});
+                else if (I.P == 3)
+                    run(integral_constant<int, 3>{}, integral_constant<int, 2>{});
+                else
+                    run(integral_constant<int, 4>{}, integral_constant<int, 1>{});
+            }
+        }
+        lo = e;
+    }
+}
+
 template <bool INNER, bool CONSEC>
 __global__ __launch_bounds__(64 * kMfWaves) void sum_mfma_kernel(SumJob jb) {
     extern __shared__ float4 mf_lds[];
@@ -3189,6 +3775,25 @@ __global__ __launch_bounds__(64 * kMfWaves) void sum_mfma_terms_kernel(SumJob jb
     __shared__ double2 iacc[INNER ? 64 * kMfWaves : 1];
     mf_single<INNER>(jb, iacc, [&](long long lo, long long hi) {
         mf_range_terms<INNER, MT, T, KERR>(jb, lo, hi, mf_lds, iacc);
+    });
+}
+
+template <bool INNER, int MT, int T, bool KERR>
+__global__ __launch_bounds__(64 * kMfWaves) void sum_mfma_f64_kernel(SumJob jb) {
+    extern __shared__ float4 mf_lds[];
+    __shared__ double2 iacc[INNER ? 64 * kMfWaves : 1];
+    mf_single<INNER>(jb, iacc, [&](long long lo, long long hi) {
+        mf_range_f64<INNER, MT, T, KERR>(jb, lo, hi, (double *)mf_lds, iacc);
+    });
+}
+
+template <int MT, int T>
+__global__ __launch_bounds__(64 * kMfWaves) void sum_mfma_f64_batch_kernel(const SumJob *jobs,
+                                                                           int n_jobs,
+                                                                           long long total) {
+    extern __shared__ float4 mf_lds[];
+    mf_batch(jobs, n_jobs, total, [&](const SumJob &jb, long long a, long long e) {
+        mf_range_f64<false, MT, T, false>(jb, a, e, (double *)mf_lds, nullptr);
     });
 }
 
@@ -3864,6 +4469,11 @@ static constexpr size_t mf_terms_lds_bytes(int MT, int T, bool kerr) {
            (kerr ? sizeof(float2) * kMfWaves * kMfKerrRounds * kMfSPW : 0);
 }
 
+static constexpr size_t mf_f64_lds_bytes(int MT, int T, int ns, bool kerr) {
+    return mf64_base_bytes(MT, ns) + mf64_rest_bytes(MT, T) +
+           (kerr ? sizeof(double2) * kMfWaves * kMfKerrRounds64 * kMfSPW : 0);
+}
+
 // Calls f(MT, T) with the smallest compiled shape that holds a request's rows
 // and |n| (as std::integral_constants).
 template <typename F>
@@ -3907,24 +4517,46 @@ int mfma_workgroups() {
                     set((const void *)sum_mfma_terms_kernel<false, mtv, tv, true>, true);
                     set((const void *)sum_mfma_terms_kernel<true, mtv, tv, true>, true);
                     set((const void *)sum_mfma_terms_batch_kernel<mtv, tv>, false);
+                    auto set64 = [](const void *f, bool kerr) {
+                        hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                            (int)mf_f64_lds_bytes(mtv, tv, 8 * tv, kerr));
+                    };
+                    set64((const void *)sum_mfma_f64_kernel<false, mtv, tv, false>, false);
+                    set64((const void *)sum_mfma_f64_kernel<true, mtv, tv, false>, false);
+                    set64((const void *)sum_mfma_f64_kernel<false, mtv, tv, true>, true);
+                    set64((const void *)sum_mfma_f64_kernel<true, mtv, tv, true>, true);
+                    set64((const void *)sum_mfma_f64_batch_kernel<mtv, tv>, false);
                 });
     });
     return cus;
 }
 
+// One request summed from its fold table.
+template <bool INNER>
+static void launch_terms(const SumJob &job, int n_wg, hipStream_t stream) {
+    const dim3 grid(n_wg), block(64 * kMfWaves);
+    const bool kerr = job.n_ph == 3;
+    mf_with_shape(job.mf_terms / 10, job.mf_terms % 10, [&](auto MT, auto T) {
+        constexpr int mt = decltype(MT)::value, t = decltype(T)::value;
+        if (job.mf_f64) {
+            const size_t lds = mf_f64_lds_bytes(mt, t, job.mf_ns, kerr);
+            if (kerr)
+                hipLaunchKernelGGL((sum_mfma_f64_kernel<INNER, mt, t, true>), grid, block, lds, stream, job);
+            else
+                hipLaunchKernelGGL((sum_mfma_f64_kernel<INNER, mt, t, false>), grid, block, lds, stream, job);
+        } else {
+            const size_t lds = mf_terms_lds_bytes(mt, t, kerr);
+            if (kerr)
+                hipLaunchKernelGGL((sum_mfma_terms_kernel<INNER, mt, t, true>), grid, block, lds, stream, job);
+            else
+                hipLaunchKernelGGL((sum_mfma_terms_kernel<INNER, mt, t, false>), grid, block, lds, stream, job);
+        }
+    });
+}
+
 hipError_t launch_sum_mfma(const SumJob &job, int n_wg, hipStream_t stream) {
     if (job.mf_terms)
-        mf_with_shape(job.mf_terms / 10, job.mf_terms % 10, [&](auto MT, auto T) {
-            constexpr int mtv = decltype(MT)::value, tv = decltype(T)::value;
-            if (job.n_ph == 3)
-                hipLaunchKernelGGL((sum_mfma_terms_kernel<false, mtv, tv, true>), dim3(n_wg),
-                                   dim3(64 * kMfWaves), mf_terms_lds_bytes(mtv, tv, true), stream,
-                                   job);
-            else
-                hipLaunchKernelGGL((sum_mfma_terms_kernel<false, mtv, tv, false>), dim3(n_wg),
-                                   dim3(64 * kMfWaves), mf_terms_lds_bytes(mtv, tv, false), stream,
-                                   job);
-        });
+        launch_terms<false>(job, n_wg, stream);
     else if (job.mf_consec)
         hipLaunchKernelGGL((sum_mfma_kernel<false, true>), dim3(n_wg), dim3(64 * kMfWaves),
                            mf_lds_bytes(), stream, job);
@@ -3937,17 +4569,7 @@ hipError_t launch_sum_mfma(const SumJob &job, int n_wg, hipStream_t stream) {
 hipError_t launch_sum_mfma_inner(const SumJob &job, int n_wg, double two_dt, double *out2,
                                  hipStream_t stream) {
     if (job.mf_terms)
-        mf_with_shape(job.mf_terms / 10, job.mf_terms % 10, [&](auto MT, auto T) {
-            constexpr int mtv = decltype(MT)::value, tv = decltype(T)::value;
-            if (job.n_ph == 3)
-                hipLaunchKernelGGL((sum_mfma_terms_kernel<true, mtv, tv, true>), dim3(n_wg),
-                                   dim3(64 * kMfWaves), mf_terms_lds_bytes(mtv, tv, true), stream,
-                                   job);
-            else
-                hipLaunchKernelGGL((sum_mfma_terms_kernel<true, mtv, tv, false>), dim3(n_wg),
-                                   dim3(64 * kMfWaves), mf_terms_lds_bytes(mtv, tv, false), stream,
-                                   job);
-        });
+        launch_terms<true>(job, n_wg, stream);
     else if (job.mf_consec)
         hipLaunchKernelGGL((sum_mfma_kernel<true, true>), dim3(n_wg), dim3(64 * kMfWaves),
                            mf_lds_bytes(), stream, job);
@@ -3972,12 +4594,18 @@ hipError_t launch_sum_mfma_batch(const SumJob *jobs_dev, int n_jobs, long long t
     return hipGetLastError();
 }
 
-hipError_t launch_sum_mfma_terms_batch(const SumJob *jobs_dev, int n_jobs, long long total, int mt,
-                                       int t, int n_wg, hipStream_t stream) {
+hipError_t launch_sum_mfma_terms_batch(const SumJob *jobs_dev, int n_jobs, long long total,
+                                       bool f64, int mt, int t, int n_wg, hipStream_t stream) {
     mf_with_shape(mt, t, [&](auto MT, auto T) {
         constexpr int mtv = decltype(MT)::value, tv = decltype(T)::value;
-        hipLaunchKernelGGL((sum_mfma_terms_batch_kernel<mtv, tv>), dim3(n_wg), dim3(64 * kMfWaves),
-                           mf_terms_lds_bytes(mtv, tv, false), stream, jobs_dev, n_jobs, total);
+        if (f64)
+            hipLaunchKernelGGL((sum_mfma_f64_batch_kernel<mtv, tv>), dim3(n_wg), dim3(64 * kMfWaves),
+                               mf_f64_lds_bytes(mtv, tv, 8 * tv, false), stream, jobs_dev, n_jobs,
+                               total);
+        else
+            hipLaunchKernelGGL((sum_mfma_terms_batch_kernel<mtv, tv>), dim3(n_wg),
+                               dim3(64 * kMfWaves), mf_terms_lds_bytes(mtv, tv, false), stream,
+                               jobs_dev, n_jobs, total);
     });
     return hipGetLastError();
 }
