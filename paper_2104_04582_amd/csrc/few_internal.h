@@ -25,8 +25,9 @@ constexpr int kMaxGap = 4;            // zero terms filled inside one segment
 constexpr int kFitSeriesPerBlock = 64;
 // Grids of at most this many knots keep each lane's knot values in registers
 // (a quarter of the rows per wave) and factor the grid with one wave's scan;
-// larger grids stream knot values with one lane per series.
-constexpr int kFitStageKnots = 128;
+// larger grids stream knot values with one lane per series (45 us at 137 knots,
+// where the wave form takes 25).
+constexpr int kFitStageKnots = 192;
 constexpr int kChunkTerms = FEW_CHUNK_TERMS;   // terms staged in LDS at once (binary32: 32 B each)
 
 // Samples per lane in one wave tile of the summation kernel.
@@ -156,8 +157,9 @@ constexpr int kMaxPhases = 3;
 
 // Knot times of a single-request fit of at most kFitStageKnots knots, passed
 // by value as a launch argument.
+template <int R>
 struct FitKnots {
-    double t[kFitStageKnots];
+    double t[R > 0 ? R * kWave : 1];
 };
 
 // Fold + interval bookkeeping for one request.

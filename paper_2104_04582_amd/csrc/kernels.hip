@@ -200,7 +200,7 @@ __device__ __forceinline__ void slope_row(const double *h, int K, int r, double 
 }
 
 // The same factor (invd, wv, bv as fit_factor_finish leaves them) on one wave
-// for K <= kFitStageKnots.  With every continuant divided by the diagonals,
+// for K <= R kWave.  With every continuant divided by the diagonals,
 // qt_r = q_r / (a_0 ... a_r), the recurrence becomes
 //   qt_r = qt_{r-1} - g_r qt_{r-2},  g_r = b_r c_{r-1} / (a_r a_{r-1}),
 // qt_{-1} = qt_0 = 1, and den_r = a_r qt_r / qt_{r-1}.  For this system
@@ -209,31 +209,37 @@ __device__ __forceinline__ void slope_row(const double *h, int K, int r, double 
 // (0, 1) on row K - 1: the qt stay positive and above 2^-K times the last
 // ratio, with no rescaling.  In matrix form (qt_r, qt_{r-1}) =
 // T_r (qt_{r-1}, qt_{r-2}), T_r = [[1, -g_r], [1, 0]]; lane l takes rows
-// 2l + 1 and 2l + 2, and the lanes' products are composed by a log-step scan
+// R l + 1 .. R l + R, and the lanes' products are composed by a log-step scan
 // (later rows on the left).
+template <int R>
 __device__ void fit_factor_wave(const double *h, int K, double *invd, double *wv, double *bv) {
     const int lane = threadIdx.x & (kWave - 1);
-    const int r0 = 2 * lane + 1, r1 = r0 + 1;
-    double bb0 = 0.0, aa0 = 1.0, cc0 = 0.0, bb1 = 0.0, aa1 = 1.0, cc1 = 0.0;
-    double g0 = 0.0, g1 = 0.0;
-    if (r0 < K) {
-        double bp, ap, cp;
-        slope_row(h, K, r0 - 1, &bp, &ap, &cp);
-        slope_row(h, K, r0, &bb0, &aa0, &cc0);
-        g0 = bb0 * cp / (aa0 * ap);
-    }
-    if (r1 < K) {
-        slope_row(h, K, r1, &bb1, &aa1, &cc1);
-        g1 = bb1 * cc0 / (aa1 * aa0);
-    }
-    // this lane's product T_{r1} T_{r0} (identity rows past the end)
-    double m00, m01, m10, m11;
-    if (r1 < K) {
-        m00 = 1.0 - g1; m01 = -g0; m10 = 1.0; m11 = -g0;
-    } else if (r0 < K) {
-        m00 = 1.0; m01 = -g0; m10 = 1.0; m11 = 0.0;
-    } else {
-        m00 = 1.0; m01 = 0.0; m10 = 0.0; m11 = 1.0;
+    const int r0 = R * lane + 1;
+    double bb[R], aa[R], cc[R], gg[R];
+    // this lane's product T_{r0+R-1} .. T_{r0} (identity rows past the end)
+    double m00 = 1.0, m01 = 0.0, m10 = 0.0, m11 = 1.0;
+    {
+        double ap = 1.0, cp = 0.0;
+        if (r0 < K) {
+            double bp;
+            slope_row(h, K, r0 - 1, &bp, &ap, &cp);
+        }
+#pragma unroll
+        for (int j = 0; j < R; ++j) {
+            bb[j] = cc[j] = gg[j] = 0.0;
+            aa[j] = 1.0;
+            if (r0 + j < K) {
+                slope_row(h, K, r0 + j, &bb[j], &aa[j], &cc[j]);
+                gg[j] = bb[j] * cp / (aa[j] * ap);
+                ap = aa[j];
+                cp = cc[j];
+                const double n00 = fma(-gg[j], m10, m00), n01 = fma(-gg[j], m11, m01);
+                m10 = m00;
+                m11 = m01;
+                m00 = n00;
+                m01 = n01;
+            }
+        }
     }
 #pragma unroll
     for (int d = 1; d < kWave; d <<= 1) {
@@ -249,19 +255,17 @@ __device__ void fit_factor_wave(const double *h, int K, double *invd, double *wv
     double p00 = __shfl_up(m00, 1), p01 = __shfl_up(m01, 1);
     double p10 = __shfl_up(m10, 1), p11 = __shfl_up(m11, 1);
     if (lane == 0) { p00 = 1.0; p01 = 0.0; p10 = 0.0; p11 = 1.0; }
-    const double qa = p00 + p01, qb = p10 + p11;    // qt_{r0-1}, qt_{r0-2}
-    if (r0 < K) {
-        const double q0 = fma(-g0, qb, qa);           // qt_{r0}
-        const double id0 = qa / (aa0 * q0);
-        invd[r0] = id0;
-        wv[r0] = cc0 * id0;
-        bv[r0] = bb0 * id0;
-        if (r1 < K) {
-            const double q1 = fma(-g1, qa, q0);
-            const double id1 = q0 / (aa1 * q1);
-            invd[r1] = id1;
-            wv[r1] = cc1 * id1;
-            bv[r1] = bb1 * id1;
+    double qa = p00 + p01, qb = p10 + p11;          // qt_{r-1}, qt_{r-2}
+#pragma unroll
+    for (int j = 0; j < R; ++j) {
+        if (r0 + j < K) {
+            const double q = fma(-gg[j], qb, qa);
+            const double id = qa / (aa[j] * q);
+            invd[r0 + j] = id;
+            wv[r0 + j] = cc[j] * id;
+            bv[r0 + j] = bb[j] * id;
+            qb = qa;
+            qa = q;
         }
     }
     if (lane == 0) {                                 // row 0: den_0 = a_0
@@ -272,18 +276,23 @@ __device__ void fit_factor_wave(const double *h, int K, double *invd, double *wv
     }
 }
 
-// y_r = a(r) + m(r) y_{r-1} for r < n <= 2 kWave, y_{-1} = 0, on one wave:
-// lane l takes rows 2l and 2l + 1, and the lanes' affine maps y -> A + M y are
-// composed by a log-step scan (later rows on the left).  Returns this lane's
-// two values (y_{2l}, y_{2l+1}); rows past n are identities.
-template <typename FA, typename FM>
-__device__ __forceinline__ double2 wave_affine(int n, FA a, FM m) {
+// y_r = a(r) + m(r) y_{r-1} for r < n <= R kWave, y_{-1} = 0, on one wave:
+// lane l takes rows R l .. R l + R - 1, and the lanes' affine maps y -> A + M y
+// are composed by a log-step scan (later rows on the left).  y: this lane's
+// values; rows past n are identities.
+template <int R, typename FA, typename FM>
+__device__ __forceinline__ void wave_affine(int n, FA a, FM m, double (&y)[R]) {
     const int lane = threadIdx.x & (kWave - 1);
-    const int r0 = 2 * lane, r1 = r0 + 1;
-    double a0 = 0.0, m0 = 1.0, a1 = 0.0, m1 = 1.0;
-    if (r0 < n) { a0 = a(r0); m0 = m(r0); }
-    if (r1 < n) { a1 = a(r1); m1 = m(r1); }
-    double A = fma(m1, a0, a1), M = m1 * m0;
+    double av[R], mv[R], A = 0.0, M = 1.0;
+#pragma unroll
+    for (int j = 0; j < R; ++j) {
+        const int r = R * lane + j;
+        av[j] = 0.0;
+        mv[j] = 1.0;
+        if (r < n) { av[j] = a(r); mv[j] = m(r); }
+        A = j == 0 ? av[0] : fma(mv[j], A, av[j]);
+        M = j == 0 ? mv[0] : mv[j] * M;
+    }
 #pragma unroll
     for (int d = 1; d < kWave; d <<= 1) {
         const double Ao = __shfl_up(A, d), Mo = __shfl_up(M, d);
@@ -292,10 +301,10 @@ __device__ __forceinline__ double2 wave_affine(int n, FA a, FM m) {
             M = M * Mo;
         }
     }
-    double yin = __shfl_up(A, 1);
-    if (lane == 0) yin = 0.0;
-    const double y0 = fma(m0, yin, a0);
-    return make_double2(y0, fma(m1, y0, a1));
+    double v = __shfl_up(A, 1);
+    if (lane == 0) v = 0.0;
+#pragma unroll
+    for (int j = 0; j < R; ++j) y[j] = v = fma(mv[j], v, av[j]);
 }
 
 // Phase series ph (workgroup ph), to double-double accuracy by one step of
@@ -307,6 +316,8 @@ __device__ __forceinline__ double2 wave_affine(int n, FA a, FM m) {
 // coefficient p on interval i; p = 0 holds y_i reduced mod 2 pi.
 // LDS (binary64 arrays of length K): h hi/lo, delta hi/lo, w, inverse pivot,
 // first solution s0, right-hand side / residual / correction.
+// K <= R kWave: the sweeps run on one wave (R = 0: longer grids, one lane).
+template <int R>
 __device__ void fit_phase_dd(const FitJob &jb, const double *t, int ph, double *lds) {
     const double *y = ph == 0 ? jb.phi_phi : (ph == 1 ? jb.phi_r : jb.phi_theta);
     const int K = jb.K;
@@ -348,24 +359,28 @@ __device__ void fit_phase_dd(const FitJob &jb, const double *t, int ph, double *
     };
     // binary64 Thomas sweeps with the factor in invd / wv / bv (of the rounded
     // matrix; the refinement step uses the exact rows): x <- A^-1 x in place.
-    // K <= kFitStageKnots: wave 0 takes each sweep as one affine scan
-    // (wave_affine; the back sweep in reversed row order).  Otherwise one lane
+    // R > 0: wave 0 takes each sweep as one affine scan (wave_affine; the back
+    // sweep in reversed row order).  Otherwise one lane
     // carries the recurrence in registers: the LDS operands of C rows are
     // loaded together, the rows eliminated (one fused multiply-add each on
     // the serial chain), and the C results stored after the batch.
-    const bool wave_solve = K <= kFitStageKnots;
+    constexpr bool wave_solve = R > 0;
     auto solve_wave = [&](double *x) {
-        const int r0 = 2 * tid, r1 = r0 + 1;
-        const double2 g = wave_affine(
-            K, [&](int r) { return x[r] * invd[r]; }, [&](int r) { return -bv[r]; });
-        if (r0 < K) x[r0] = g.x;
-        if (r1 < K) x[r1] = g.y;
+        constexpr int RR = R > 0 ? R : 1;
+        const int r0 = RR * tid;
+        double g[RR];
+        wave_affine<RR>(
+            K, [&](int r) { return x[r] * invd[r]; }, [&](int r) { return -bv[r]; }, g);
+#pragma unroll
+        for (int j = 0; j < RR; ++j)
+            if (r0 + j < K) x[r0 + j] = g[j];
         lds_wave_sync();
-        const double2 v = wave_affine(
-            K, [&](int r) { return x[K - 1 - r]; }, [&](int r) { return -wv[K - 1 - r]; });
+        wave_affine<RR>(
+            K, [&](int r) { return x[K - 1 - r]; }, [&](int r) { return -wv[K - 1 - r]; }, g);
         lds_wave_sync();
-        if (r0 < K) x[K - 1 - r0] = v.x;
-        if (r1 < K) x[K - 1 - r1] = v.y;
+#pragma unroll
+        for (int j = 0; j < RR; ++j)
+            if (r0 + j < K) x[K - 1 - r0 - j] = g[j];
     };
     auto solve = [&](double *x) {
         constexpr int C = 16;
@@ -427,7 +442,7 @@ __device__ void fit_phase_dd(const FitJob &jb, const double *t, int ph, double *
     // binary64 factor of the rounded matrix (wave 0, or one lane of it) while
     // the other waves form the right-hand side, then the first solve
     if (wave_solve) {
-        if (tid < kWave) fit_factor_wave(Hh, K, invd, wv, bv);
+        if (tid < kWave) fit_factor_wave<(R > 0 ? R : 1)>(Hh, K, invd, wv, bv);
     } else if (tid == 0) {
         fit_factor_serial(Hh, K, invd, wv);
     }
@@ -685,7 +700,7 @@ __device__ __forceinline__ double lane_value(double v, int l) {
 }
 
 // Binary64 solve of the amplitude series of workgroup blk (64 real series,
-// lane = series) for K <= kFitStageKnots.  The rows are split over the four
+// lane = series) for K <= R kWave.  The rows are split over the four
 // waves: wave w takes rows [R_w, R_{w+1}) and keeps its lanes' knot values
 // y_{R_w - 1} .. y_{R_{w+1}} and its forward results and slopes in
 // registers; row-wise constants are formed lane-parallel (lane c for row
@@ -704,9 +719,10 @@ __device__ __forceinline__ double lane_value(double v, int l) {
 // The values entering the chunks follow from the chunk ends (exchanged in
 // LDS) in at most three steps.  Each wave then writes the coefficients of its
 // intervals.
+template <int R>
 __device__ void fit_amplitudes_staged(const FitJob &jb, const double *t, int blk, double *lds) {
     constexpr int NW = 4;                            // waves (launched with 256 lanes)
-    constexpr int LC = (kFitStageKnots + NW - 1) / NW;   // most rows of a chunk
+    constexpr int LC = R * kWave / NW;               // most rows of a chunk
     const int K = jb.K, M = jb.M;
     const int tid = threadIdx.x, lane = tid & (kWave - 1), w = tid / kWave;
     double *hs = lds, *invd = lds + K, *wv = lds + 2 * K, *bv = lds + 3 * K;
@@ -719,12 +735,16 @@ __device__ void fit_amplitudes_staged(const FitJob &jb, const double *t, int blk
     const int L = (K + NW - 1) / NW;
     const int r_lo = min(K, w * L), n = min(K, r_lo + L) - r_lo;
     // The knot times of the spacings h_i = t_{i+1} - t_i that wave 0 forms for
-    // the factor (i = lane and lane + 64, clamped), requested first: a wave's
+    // the factor (i = lane, lane + 64, ..., clamped), requested first: a wave's
     // loads complete in order, so the factor waits only for these and starts
     // while the knot values and the upload requested below are in flight.
-    static_assert(kFitStageKnots <= 2 * kWave + 1, "two spacings per lane");
-    double ta0 = t[min(lane, K - 2)], tb0 = t[min(lane, K - 2) + 1];
-    double ta1 = t[min(lane + kWave, K - 2)], tb1 = t[min(lane + kWave, K - 2) + 1];
+    double ta[R], tb[R];
+#pragma unroll
+    for (int j = 0; j < R; ++j) {
+        const int i = min(lane + j * kWave, K - 2);
+        ta[j] = t[i];
+        tb[j] = t[i + 1];
+    }
     // the workgroup's share of the upload: each lane's first word requested
     // now (host memory is far) and stored at the end
     long long up_x = -1, up_end = 0;
@@ -749,12 +769,14 @@ __device__ void fit_amplitudes_staged(const FitJob &jb, const double *t, int blk
     }
     // the knot times are taken here, after the loads above were issued (this
     // keeps the compiler from moving their loads into the branch below)
-    asm volatile("" : "+v"(ta0), "+v"(tb0), "+v"(ta1), "+v"(tb1));
+#pragma unroll
+    for (int j = 0; j < R; ++j) asm volatile("" : "+v"(ta[j]), "+v"(tb[j]));
     if (w == 0) {
-        if (lane < K - 1) hs[lane] = tb0 - ta0;
-        if (lane + kWave < K - 1) hs[lane + kWave] = tb1 - ta1;
+#pragma unroll
+        for (int j = 0; j < R; ++j)
+            if (lane + j * kWave < K - 1) hs[lane + j * kWave] = tb[j] - ta[j];
         lds_wave_sync();
-        fit_factor_wave(hs, K, invd, wv, bv);
+        fit_factor_wave<R>(hs, K, invd, wv, bv);
     }
     __syncthreads();
     // row-wise constants of row r_lo + c in lane c
@@ -892,30 +914,41 @@ __device__ void fit_amplitudes_staged(const FitJob &jb, const double *t, int blk
 
 // Workgroups 0 .. n_ph-1 fit the phases, the rest the amplitude series; t:
 // the knot times.
+template <int R>
 __device__ __forceinline__ void fit_body(const FitJob &jb, const double *t, double *lds) {
     if ((int)blockIdx.x < jb.n_ph) {
-        fit_phase_dd(jb, t, blockIdx.x, lds);
+        fit_phase_dd<R>(jb, t, blockIdx.x, lds);
         return;
     }
-    if ((int)blockIdx.x - jb.n_ph >= jb.amp_blocks) return;
-    if (jb.K <= kFitStageKnots)
-        fit_amplitudes_staged(jb, t, blockIdx.x - jb.n_ph, lds);
+    const int blk = (int)blockIdx.x - jb.n_ph;
+    if (blk >= jb.amp_blocks) return;
+    if constexpr (R > 0)
+        fit_amplitudes_staged<R>(jb, t, blk, lds);
     else
-        fit_amplitudes_stream(jb, t, blockIdx.x - jb.n_ph, lds);
+        fit_amplitudes_stream(jb, t, blk, lds);
 }
 
-// Single-request fit.  Grids of at most kFitStageKnots knots also arrive in
-// the launch's arguments (kt), so no workgroup waits on the host-memory
-// staging slot for them.
-__global__ __launch_bounds__(256) void fit_kernel(FitJob jb, FitKnots kt) {
+// Single-request fit.  Grids of at most R kWave knots also arrive in the
+// launch's arguments (kt), so no workgroup waits on the host-memory staging
+// slot for them.  R = 2 up to 128 knots, 3 up to 192 (whose chunks of 48 rows take
+// half as many registers again): 137 knots, 611 modes 45 -> 25 us.
+template <int R>
+__global__ __launch_bounds__(256) void fit_kernel(FitJob jb, FitKnots<R> kt) {
     extern __shared__ double lds_fit[];
-    fit_body(jb, jb.K <= kFitStageKnots ? kt.t : jb.t, lds_fit);
+    fit_body<R>(jb, R > 0 ? kt.t : jb.t, lds_fit);
 }
 
+// R: the longest grids of the batch (its other grids take their own form).
+template <int R>
 __global__ __launch_bounds__(256) void fit_batch_kernel(const FitJob *jobs) {
     extern __shared__ double lds_fit[];
     const FitJob jb = jobs[blockIdx.y];
-    fit_body(jb, jb.t, lds_fit);
+    if (jb.K <= 2 * kWave)
+        fit_body<2>(jb, jb.t, lds_fit);
+    else if (R == 3 || (R == 0 && jb.K <= kFitStageKnots))
+        fit_body<3>(jb, jb.t, lds_fit);
+    else if constexpr (R == 0)
+        fit_body<0>(jb, jb.t, lds_fit);
 }
 
 // ===========================================================================
@@ -4256,19 +4289,31 @@ static void fit_lds_attributes() {
     static std::once_flag once;
     std::call_once(once, [] {
         const int bytes = (int)fit_lds_bytes(kFitStageKnots);
-        hipFuncSetAttribute((const void *)fit_kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
-                            bytes);
-        hipFuncSetAttribute((const void *)fit_batch_kernel,
-                            hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+        for (const void *f : {(const void *)fit_kernel<0>, (const void *)fit_kernel<2>,
+                              (const void *)fit_kernel<3>, (const void *)fit_batch_kernel<0>,
+                              (const void *)fit_batch_kernel<2>, (const void *)fit_batch_kernel<3>})
+            hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
     });
+}
+
+// Rows per lane of the wave sweeps for K knots (0: one lane).
+static int fit_rows(int K) { return K <= 2 * kWave ? 2 : K <= kFitStageKnots ? 3 : 0; }
+
+template <int R>
+static void launch_fit_rows(const FitJob &job, const double *t_host, hipStream_t stream) {
+    FitKnots<R> kt;
+    if (R > 0) std::memcpy(kt.t, t_host, sizeof(double) * job.K);
+    hipLaunchKernelGGL(fit_kernel<R>, dim3(job.n_ph + job.amp_blocks), dim3(256),
+                       fit_lds_bytes(job.K), stream, job, kt);
 }
 
 hipError_t launch_fit(const FitJob &job, const double *t_host, hipStream_t stream) {
     fit_lds_attributes();
-    dim3 grid(job.n_ph + job.amp_blocks);
-    FitKnots kt;
-    if (job.K <= kFitStageKnots) std::memcpy(kt.t, t_host, sizeof(double) * job.K);
-    hipLaunchKernelGGL(fit_kernel, grid, dim3(256), fit_lds_bytes(job.K), stream, job, kt);
+    switch (fit_rows(job.K)) {
+    case 2: launch_fit_rows<2>(job, t_host, stream); break;
+    case 3: launch_fit_rows<3>(job, t_host, stream); break;
+    default: launch_fit_rows<0>(job, t_host, stream);
+    }
     return hipGetLastError();
 }
 
@@ -4279,8 +4324,9 @@ hipError_t launch_fit_batch(const FitJob *jobs_dev, int n_jobs, int max_blocks, 
     // jobs of up to kFitStageKnots knots stage in LDS whatever max_K is
     const size_t bytes =
         std::max(fit_lds_bytes(max_K), fit_lds_bytes(std::min(max_K, kFitStageKnots)));
-    hipLaunchKernelGGL(fit_batch_kernel, grid, dim3(256), bytes, stream,
-                       jobs_dev);
+    const int R = fit_rows(max_K);
+    hipLaunchKernelGGL(R == 2 ? fit_batch_kernel<2> : R == 3 ? fit_batch_kernel<3> : fit_batch_kernel<0>,
+                       grid, dim3(256), bytes, stream, jobs_dev);
     return hipGetLastError();
 }
 
