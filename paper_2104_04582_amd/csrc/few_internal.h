@@ -324,10 +324,12 @@ struct TermLayout {
 // repay; short generic-Kerr sums are split over the terms by the vector kernel.
 // Where the two meet, in terms per polar index, measured as whole requests
 // (60 knots, 10 s cadence; vector / matrix-core, us):
-//   100 to 365 days: 11 rows, |n| <= 3, 77 terms 58.0 / 57.4, 103.5 / 87.6;
-//     9 rows, |n| <= 20, 369 terms 108 / 66, 272 / 108; 17 rows, |n| <= 4, 153
-//     terms 77.2 / 78.5, 158 / 130; Kerr |k| <= 2, 21 rows, |n| <= 20 (100
-//     days), 861 terms 880 / 291
+//   365 days: 7 rows, |n| <= 3, 49 terms 80.5 / 76.5; 11 rows, |n| <= 3, 77 terms
+//     103.5 / 87.6; 17 rows, |n| <= 4, 153 terms 158 / 130; Kerr |k| <= 2, 7 rows,
+//     |n| <= 3, 49 terms 258 / 292, |n| <= 5, 77 terms 340 / 293
+//   100 days: 7 rows, |n| <= 5, 77 terms 54.0 / 51.4; 11 rows, |n| <= 3, 77 terms 58.0 /
+//     57.4; 9 rows, |n| <= 20, 369 terms 108 / 66; 17 rows, |n| <= 4, 153 terms
+//     77.2 / 78.5; Kerr |k| <= 2, 21 rows, |n| <= 20, 861 terms 880 / 291
 //   30 days: 7 rows, |n| <= 8, 119 terms 43.8 / 43.1; 11 rows, |n| <= 5, 121
 //     terms 46.6 / 47.7; 7 rows, |n| <= 17, 245 terms 54.6 / 49.9; 17 rows,
 //     |n| <= 7, 255 terms 62.0 / 60.3 and Kerr 154.8 / 169.6
@@ -361,10 +363,16 @@ inline bool mf_terms_path(const TermLayout &L, long long n, bool fp32) {
     }
     static const int kShortKerr[4] = {136, 160, 450, 660};
     static const int kShort[4] = {124, 140, 216, 300};
-    static const int kLong[4] = {80, 96, 160, 180};
-    // samples of 1.5 and 6 rounds of every wave of 256 workgroups
-    const int *least = n >= 786432 ? kLong : nk > 1 && n < 196608 ? kShortKerr : kShort;
-    return L.n_terms >= (long long)least[shape] * nk;
+    // many samples: terms that cost the shape's rate, plus the staging shared out
+    // over the samples (terms x 10^6 samples)
+    static const int kRate[4] = {37, 44, 92, 94}, kStage[4] = {24, 31, 50, 60};
+    // (196608 samples: 1.5 rounds of every wave of 256 workgroups)
+    const int brief = (nk > 1 && n < 196608 ? kShortKerr : kShort)[shape];
+    long long least = brief;
+    if (n >= 196608)
+        least = std::min<long long>(brief, kRate[shape] + (nk > 1 ? 16 : 0) +
+                                               kStage[shape] * 1000000ll / n);
+    return L.n_terms >= least * nk;
 }
 
 // Build the folded term layout; returns 0 or a few_status error code.
