@@ -3869,6 +3869,10 @@ __global__ __launch_bounds__(64 * kMfWaves) void sum_mfma_terms_batch_kernel(con
 // in sorted order (values loaded 32 at a time, so only the chain of adds is
 // serial) and every threshold decision is taken on exactly those sums.
 // ===========================================================================
+// No contraction: a power is re re + im im with each product rounded (with
+// __dmul_rn, a plain product of another header, the sum was fused, and powers
+// that differ in their last bits ranked in another order).
+#pragma clang fp contract(off)
 __device__ __forceinline__ bool sel_before(double ka, int ia, double kb, int ib) {
     return ka > kb || (ka == kb && ia < ib);
 }
@@ -3908,7 +3912,7 @@ __device__ void select_sorted(const double *amp, int M, int N, double one_minus_
         const int p = tid + kSelectThreads * r;
         if (r < R && p < M) {
             const double re = amp[(k * M + p) * 2], im = amp[(k * M + p) * 2 + 1];
-            kv[r] = __dadd_rn(__dmul_rn(re, re), __dmul_rn(im, im));
+            kv[r] = re * re + im * im;
             iv[r] = p;
         } else {
             kv[r] = -1.0;           // below every power
@@ -4045,7 +4049,7 @@ __device__ bool select_bounded(const double *amp, int M, double one_minus_eps, i
         pv[r] = 0.0;
         if (ok[r]) {
             const double re = amp[(k * M + p) * 2], im = amp[(k * M + p) * 2 + 1];
-            pv[r] = __dadd_rn(__dmul_rn(re, re), __dmul_rn(im, im));
+            pv[r] = re * re + im * im;
         }
         kb[r] = (unsigned long long)__double_as_longlong(pv[r]);
         loc += pv[r];
@@ -4222,6 +4226,8 @@ __global__ __launch_bounds__(kSelectThreads) void select_kernel(const double *am
     __syncthreads();                                // the bounded stage's LDS reads are done
     select_sorted(amp, M, N, one_minus_eps, keep, sel_lds);
 }
+
+#pragma clang fp contract(on)
 
 __global__ void zero_u32_kernel(unsigned *p, int n) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
