@@ -73,26 +73,6 @@ def path_flops(native, lmn, n: int, precision: str) -> float:
     return algorithmic_flops(n_terms, segs.shape[0], n)
 
 
-def mfma_instructions(native, w, n_wg: int) -> int:
-    """MFMA instructions of one matrix-core launch of request w: every
-    workgroup takes an equal contiguous share of the samples and runs rounds
-    (waves x tiles x 16 samples) inside each knot interval; in the last round
-    of an interval only the waves with samples run."""
-    sh = native.host_mfma_shape()
-    per_wave = sh["tiles_per_wave"] * 16
-    starts = [int(x) for x in native.host_interval_starts(w.t_knots, w.t_start, w.dt,
-                                                          w.n_samples)]
-    n = w.n_samples
-    wave_rounds = 0
-    for r in range(n_wg):
-        lo, hi = n * r // n_wg, n * (r + 1) // n_wg
-        for i in range(len(starts) - 1):
-            a, e = max(lo, starts[i]), min(hi, starts[i + 1])
-            if e > a:
-                wave_rounds += (e - a + per_wave - 1) // per_wave
-    return wave_rounds * sh["tiles_per_wave"] * sh["mfma_per_tile"]
-
-
 def time_path(native, plan, w, dev, steps: int, warmup: int, settle_s: float = 0.0):
     """Mean wall time of `steps` fit + sum steps after at least `warmup` untimed
     steps and at least `settle_s` seconds of them (the shader clock takes a few
@@ -543,10 +523,8 @@ def main() -> int:
     flops_vec = algorithmic_flops(n_terms, n_segs, w.n_samples)
     flops_mf = mfma_algorithmic_flops(n_terms, n_rows, w.n_samples)
     canonical = 32.0 * w.M * w.n_samples
-    n_wg = torch.cuda.get_device_properties(0).multi_processor_count
-    mf_instr = mfma_instructions(native, w, n_wg) if mfma else 0
     log(f"[bench] workload K={w.K} M={w.M} N={w.n_samples} terms={n_terms} segs={n_segs} "
-        f"matrix-core path={mfma} ({mf_instr} MFMA instructions per launch on {n_wg} CUs)")
+        f"matrix-core path={mfma}")
 
     res = {}
     outs = {}
@@ -674,15 +652,11 @@ def main() -> int:
         "roofline": ({"bound": "mfma", "achieved": ach, "peak": PEAK_FP16_MFMA,
                       "unit": "TFLOP/s", "frac": ach / PEAK_FP16_MFMA,
                       "traffic": measured_traffic(),
-                      "kernel": "sum_mfma_kernel<false>",
+                      "kernel": "sum_mfma_kernel<false, true>",
                       "flop_per_launch": flops_mf,
                       "flop_count": "folded contraction counted once: 32 flop per folded "
                                     "term and sample + 8 per signed-m row and sample",
                       "launch_ms": m["sum_ms"],
-                      "executed_mfma_instructions": mf_instr,
-                      "executed_mfma_tflops": mf_instr * 16384.0 / (m["sum_ms"] * 1e-3) / 1e12,
-                      "executed_mfma_frac": mf_instr * 16384.0 / (m["sum_ms"] * 1e-3) / 1e12
-                      / PEAK_FP16_MFMA,
                       "canonical_32flop_frac": m["canonical_tflops"] / PEAK_FP16_MFMA}
                      if mfma else
                      {"bound": "alu", "achieved": ach, "peak": PEAK_FP32_VALU,

@@ -90,10 +90,10 @@ enum {
                                  delays the launch after it by several microseconds, so this
                                  keeps the other stages back to back while the dominant
                                  kernel is timed */
-    FEW_FLAG_VECTOR_ONLY = 4, /* FEW_MIXED: never use the matrix-core summation (fp16 hi/lo
-                                 operands on the MFMA units, fp32 accumulation); every sum
-                                 runs on the vector units in binary32 with Kahan-compensated
-                                 accumulation */
+    FEW_FLAG_VECTOR_ONLY = 4, /* never use the matrix-core summation: every sum runs on the
+                                 vector units (FEW_MIXED: in binary32 with Kahan-compensated
+                                 accumulation, in place of fp16 hi/lo operands on the MFMA
+                                 units with fp32 accumulation) */
     FEW_FLAG_TIMING_SPARSE = 16, /* with FEW_FLAG_TIMING_SUM: events around every 8th
                                    summation launch only (the first, the ninth, ... counted
                                    from plan creation or the last few_plan_timing reset), so
@@ -412,8 +412,9 @@ uint64_t few_host_request_bytes(int32_t precision, int32_t K, int32_t M,
  * which the matrix cores take for longer sums and the vector units for
  * shorter ones, or a negative few_status for an invalid list.  few_host_mfma_shape
  * writes the launch shape: out8 = (waves per workgroup, 16-sample tiles per
- * wave, 16-row tiles, 32-column steps per sign of n, MFMA instructions per
- * tile and round, largest |n| + 1, largest number of signed m values,
+ * wave, 16-row tiles, 32-column steps per sign of n, most MFMA instructions
+ * per tile and round (about a third of them where the cubic is written about
+ * blocks of samples), largest |n| + 1, largest number of signed m values,
  * smallest number of folded terms).  Each workgroup (one per compute unit)
  * takes a contiguous share of the samples; the shares of the GPU's eight XCDs
  * are weighted by the rule of few_host_xcd_split_step.

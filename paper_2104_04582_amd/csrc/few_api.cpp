@@ -1491,21 +1491,19 @@ int launch_batch(few_plan p, Batch *b, hipStream_t s, unsigned *counter) {
         HIP_TRY(hipEventRecord(b->done, s));
         return FEW_OK;
     }
-    // the jobs by summation launch: the vector kernel, the matrix-core kernels
-    // on the fold table by shape (these share the vector jobs' fold), those on
-    // operand tables with rows of consecutive m, and the others
-    constexpr int kShapes = kMfMT * kMfT, kSets = kShapes + 3;
+    // the jobs by summation launch: the vector kernel, the matrix-core kernel on
+    // the fold table (these two share the fold), those on operand tables with
+    // rows of consecutive m, and the others
+    constexpr int kSets = 4;
     auto set_of = [](const ServedReq *r) {
-        if (r->h.mfma) return kShapes + (r->h.terms.consec ? 1 : 2);
-        if (!r->h.mf_terms(r->r.n_samples)) return 0;
-        const int q = r->h.terms.mf_terms;      // 10 row tiles + steps
-        return 1 + (q / 10 - 1) * kMfT + q % 10 - 1;
+        if (r->h.mfma) return r->h.terms.consec ? 2 : 3;
+        return r->h.mf_terms(r->r.n_samples) ? 1 : 0;
     };
     int first[kSets + 1] = {}, next[kSets];
     for (ServedReq *r : b->reqs) ++first[set_of(r) + 1];
     for (int q = 0; q < kSets; ++q) first[q + 1] += first[q];
     std::copy(first, first + kSets, next);
-    const int n_fold = first[kShapes + 1];
+    const int n_fold = first[2];
     int max_amp_blocks = 0, max_K = 4, max_fold_blocks = 0, max_K_mf = 4;
     long long waves = 0, mf_total[kSets] = {};
     for (int i = 0; i < n; ++i) {
@@ -1520,7 +1518,8 @@ int launch_batch(few_plan p, Batch *b, hipStream_t s, unsigned *counter) {
                         Tiling{1, 0});
         if (set > 0) {
             sj[k].sample_base = mf_total[set];
-            mf_total[set] += r->r.n_samples;
+            mf_total[set] += r->r.n_samples *
+                             (set == 1 ? mf_terms_cost(sj[k].mf_terms, sj[k].mf_ns, !fp32) : 1);
         } else {
             sj[k].wave_base = (int)waves;
             waves += tile_upper_bound(r->r.n_samples, r->h.K, tile);
@@ -1543,13 +1542,12 @@ int launch_batch(few_plan p, Batch *b, hipStream_t s, unsigned *counter) {
     for (int set = 1; set < kSets; ++set) {
         const int jobs = first[set + 1] - first[set];
         if (jobs == 0) continue;
-        if (set <= kShapes)
+        if (set == 1)
             HIP_TRY(launch_sum_mfma_terms_batch(sd + first[set], jobs, mf_total[set], !fp32,
-                                                (set - 1) / kMfT + 1, (set - 1) % kMfT + 1,
                                                 p->mf_wg, s));
         else
-            HIP_TRY(launch_sum_mfma_batch(sd + first[set], jobs, mf_total[set],
-                                          set == kShapes + 1, p->mf_wg, s));
+            HIP_TRY(launch_sum_mfma_batch(sd + first[set], jobs, mf_total[set], set == 2, p->mf_wg,
+                                          s));
     }
     b->done = sync_event(p);
     if (!b->done) return fail(FEW_E_HIP, "event creation failed");

@@ -290,7 +290,7 @@ hipError_t launch_sum_mfma_inner(const SumJob &job, int n_wg, double two_dt, dou
 hipError_t launch_sum_mfma_batch(const SumJob *jobs_dev, int n_jobs, long long total,
                                  bool consec, int n_wg, hipStream_t stream);
 hipError_t launch_sum_mfma_terms_batch(const SumJob *jobs_dev, int n_jobs, long long total,
-                                       bool f64, int mt, int t, int n_wg, hipStream_t stream);
+                                       bool f64, int n_wg, hipStream_t stream);
 hipError_t launch_select(const double *amp, int K, int M, double eps, bool sorted, int *keep,
                          hipStream_t stream);
 constexpr int kMaxSelectModes = 4096;   // LDS: (binary64 key + int index) per padded mode
@@ -341,23 +341,26 @@ struct TermLayout {
 // empty ones too; at 3.15 million samples (365 days, 10 s) 46 + 1.07 terms against
 // 125 + 0.5 cells us (full 3843-mode list, 1281 terms of 1536 cells 1460 / 934;
 // 217 of 256 308 / 293; 861 of 1056 1015 / 717; selected lists, 351 of 768
-// 513 / 570 and 870 of 1536 1080 / 927).  With few rounds per wave the margin is
-// wider, since a batch runs its requests of each kind in a launch of their own
-// (six uneven requests, one of 989 terms and 96192 samples: 545 / 585).  Below
-// one round per SIMD the vector kernel's serial walk over the terms is what a
-// call waits for: one day, 77 terms 48.4 / 44.8, 1281 terms 265 / 111, Kerr
-// 5 x 99 terms 148 / 127 (at 3 days 150 / 154).
+// 513 / 570 and 870 of 1536 1080 / 927).  Below one round per SIMD the vector
+// kernel's serial walk over the terms is what a call waits for: one day, Kerr
+// 5 x 99 terms 148 / 127 (at 3 days 150 / 154), 3 x 341 terms 233 / 130.
+// Schwarzschild requests below 262144 samples stay on the vector kernel: alone
+// they would gain (1281 terms over one day, binary64, 265 / 111), but batches of
+// them share its persistent launch, and a second launch of few workgroups at
+// work each costs more than it saves (6 of up to 10 days, binary32, 111 / 127
+// us; 6 of up to 30 days, binary64, 430 / 465).
 // (The fold table, its size and its launches are the same either way.)
 inline bool mf_terms_path(const TermLayout &L, long long n, bool fp32) {
     if (L.mf_terms == 0) return false;
     const int mt = L.mf_terms / 10, t = L.mf_terms % 10;
     const int shape = mt == 1 && t == 1 ? 0 : mt <= 2 && t == 1 ? 1 : mt <= 2 ? 2 : 3;
     const int nk = L.k_max - L.k_min + 1;
+    if (nk == 1 && n < 262144) return false;
     if (!fp32) {
         const int steps = (L.n_max > -L.n_min ? L.n_max : -L.n_min) / 2 + 1;
         const int cells = 8 * (shape == 0 ? 1 : shape == 3 ? 3 : 2) * 4 * steps;
         long long least = n >= 262144 ? 74 + cells / 2 : 150 + cells * 11 / 20;
-        const long long brief = nk > 1 && n >= 16384 ? 120 : 72;
+        const long long brief = n >= 16384 ? 120 : 72;
         if (n < 65536 && least > brief) least = brief;
         return L.n_terms >= least * nk;
     }
@@ -373,6 +376,14 @@ inline bool mf_terms_path(const TermLayout &L, long long n, bool fp32) {
         least = std::min<long long>(brief, kRate[shape] + (nk > 1 ? 16 : 0) +
                                                kStage[shape] * 1000000ll / n);
     return L.n_terms >= least * nk;
+}
+
+// Relative time of a sample of such a sum (shape 10 row tiles + steps; ns steps of
+// two |n| in binary64): the shares of a batched launch are cut in these units.
+__host__ __device__ inline int mf_terms_cost(int shape, int ns, bool f64) {
+    const int mt = shape / 10, t = shape % 10;
+    const int tiles = mt == 1 && t == 1 ? 1 : mt <= 2 ? 2 : 3;
+    return f64 ? 8 + tiles * ns : tiles == 1 ? 5 : tiles == 3 ? 10 : t == 1 ? 6 : 8;
 }
 
 // Build the folded term layout; returns 0 or a few_status error code.

@@ -12,19 +12,23 @@
 //                  the multipliers' products; the grid's tridiagonal factor by
 //                  one wave's scan.  Phase series: double-double (one
 //                  refinement step, scan solves).
-//  fold_pack_kernel  matrix-core requests: interval starts; per interval and
-//                  row tile, -2Y_lm, the fold of the l-sum, the row scales and
-//                  the operand table of the products.
-//  prepare_kernel  vector-path requests: interval starts and tile prefixes;
+//  fold_pack_kernel  long Schwarzschild lists with a binary32 result: interval
+//                  starts; per interval and row tile, -2Y_lm, the fold of the
+//                  l-sum, the row scales and the operand values of the products.
+//  prepare_kernel  all other requests: interval starts and tile prefixes;
 //                  -2Y_lm and the fold of the l-sum into one complex cubic per
 //                  signed (m, [k,] n) term.
 //  sum_mfma_kernel binary32 result on the matrix cores: per interval the
 //                  product of the coefficient matrix (signed m rows) with the
 //                  harmonics f^|n| of the samples, v_mfma_f32_16x16x32_f16 on
-//                  fp16 hi/lo parts with fp32 accumulation, a Horner
-//                  recurrence in u on the accumulators, rows combined with
-//                  e^{-i m Phi_phi}.
-//  sum_wg_kernel   binary32 on the vector units: one workgroup of 4 waves = one
+//                  fp16 hi/lo parts with fp32 accumulation; the cubic in time
+//                  about the centre of blocks of samples (one Horner step) or
+//                  of the interval (three); rows combined with e^{-i m Phi_phi}.
+//  sum_mfma_terms_kernel  the same from prepare_kernel's terms (middle lists,
+//                  generic Kerr), operands formed by each workgroup.
+//  sum_mfma_f64_kernel  the same in binary64 (v_mfma_f64_16x16x4_f64).
+//  sum_wg_kernel   binary32 on the vector units (few terms, or few samples):
+//                  one workgroup of 4 waves = one
 //                  tile of consecutive samples inside one knot interval; the
 //                  term coefficients are staged in LDS and broadcast to VGPR
 //                  operands.  Per sample: phases in binary64 reduced mod 2 pi,
@@ -34,8 +38,9 @@
 //                  m or k), Kahan-compensated within four term groups whose
 //                  values are added in order; the end of a launch uses
 //                  term-split tiles (the four waves take one group each).
-//  sum_kernel      binary64: one wave = one tile; phases in double-double;
-//                  coefficients read by scalar loads into SGPR operands.
+//  sum_kernel      binary64 on the vector units (sparse lists): one wave = one
+//                  tile; phases in double-double; coefficients read by scalar
+//                  loads into SGPR operands.
 //  select_kernel   the mode selector of Sec. III D: per knot a radix select
 //                  with error-bounded sums, the sorted sequential sums when a
 //                  comparison falls inside the bound.
@@ -3046,6 +3051,7 @@ __device__ void mf_range_terms(const SumJob &jb, long long lo, long long hi, flo
     MfSampleArea *sa = (MfSampleArea *)((char *)lds + mf_table_bytes(MT, T)) + wave;
     float2 *hp = (float2 *)((char *)lds + mf_table_bytes(MT, T) + kMfWaves * sizeof(MfSampleArea)) +
                  wave * kMfKerrRounds * kMfSPW;
+    __syncthreads();        // areas of a previous job of another shape no longer read
     sa->c[0][threadIdx.x & (kWave - 1)] = make_float2(1.0f, 0.0f);
     const int mm[1] = {jb.mf_m0};
     const FEW_AS4 long long *st = cptr(jb.starts);
@@ -3178,11 +3184,11 @@ __device__ __forceinline__ void mf_single(const SumJob &jb, double2 *iacc, Range
     }
 }
 
-// A batched launch: the jobs' samples laid end to end (job j from
-// sample_base_j), split into equal shares; range(job, a, e).
-template <typename Range>
+// A batched launch: the jobs' samples, cost(job) units each, laid end to end
+// (job j from unit sample_base_j), split into equal shares; range(job, a, e).
+template <typename Cost, typename Range>
 __device__ __forceinline__ void mf_batch(const SumJob *jobs, int n_jobs, long long total,
-                                         Range range) {
+                                         Cost cost, Range range) {
     long long lo, hi;
     mf_share(total, &lo, &hi);
     int j = 0, top = n_jobs - 1;
@@ -3194,7 +3200,10 @@ __device__ __forceinline__ void mf_batch(const SumJob *jobs, int n_jobs, long lo
         const long long b0 = *cptr(&jobs[j].sample_base);
         if (b0 >= hi) break;
         const SumJob jb = load_uniform(jobs + j);
-        const long long a = max(lo, b0) - b0, e = min(hi, b0 + jb.n) - b0;
+        // (a share's end and the next one's start round to the same sample)
+        const long long c = cost(jb);
+        const long long a = (max(lo, b0) - b0 + c - 1) / c;
+        const long long e = (min(hi, b0 + jb.n * c) - b0 + c - 1) / c;
         if (a < e) range(jb, a, e);
     }
 }
@@ -3797,7 +3806,8 @@ __global__ __launch_bounds__(64 * kMfWaves) void sum_mfma_batch_kernel(const Sum
     extern __shared__ float4 mf_lds[];
     __shared__ float msc[kMfRows / 2];
     __shared__ int mm[kMfRows];
-    mf_batch(jobs, n_jobs, total, [&](const SumJob &jb, long long a, long long e) {
+    auto one = [](const SumJob &) { return 1ll; };
+    mf_batch(jobs, n_jobs, total, one, [&](const SumJob &jb, long long a, long long e) {
         mf_range<false, CONSEC>(jb, a, e, mf_lds, msc, mm, nullptr);
     });
 }
@@ -3820,23 +3830,40 @@ __global__ __launch_bounds__(64 * kMfWaves) void sum_mfma_f64_kernel(SumJob jb) 
     });
 }
 
-template <int MT, int T>
-__global__ __launch_bounds__(64 * kMfWaves) void sum_mfma_f64_batch_kernel(const SumJob *jobs,
-                                                                           int n_jobs,
-                                                                           long long total) {
-    extern __shared__ float4 mf_lds[];
-    mf_batch(jobs, n_jobs, total, [&](const SumJob &jb, long long a, long long e) {
-        mf_range_f64<false, MT, T, false>(jb, a, e, (double *)mf_lds, nullptr);
-    });
+// Calls f(MT, T) with the smallest compiled shape that holds a request's rows
+// and |n| (as std::integral_constants).
+template <typename F>
+__host__ __device__ static inline void mf_with_shape(int mt, int t, F f) {
+    using std::integral_constant;
+    using I1 = integral_constant<int, 1>;
+    using I2 = integral_constant<int, 2>;
+    using I3 = integral_constant<int, 3>;
+    if (mt == 1 && t == 1) f(I1{}, I1{});
+    else if (mt <= 2 && t == 1) f(I2{}, I1{});
+    else if (mt <= 2) f(I2{}, I2{});
+    else f(I3{}, I2{});
 }
 
-template <int MT, int T>
+// Batches: one launch over all shapes (a workgroup per compute unit either way,
+// and short requests of one shape would leave most of a launch of their own
+// idle).
+template <bool F64>
 __global__ __launch_bounds__(64 * kMfWaves) void sum_mfma_terms_batch_kernel(const SumJob *jobs,
                                                                              int n_jobs,
                                                                              long long total) {
     extern __shared__ float4 mf_lds[];
-    mf_batch(jobs, n_jobs, total, [&](const SumJob &jb, long long a, long long e) {
-        mf_range_terms<false, MT, T, false>(jb, a, e, mf_lds, nullptr);
+    auto cost = [](const SumJob &jb) {
+        return (long long)mf_terms_cost(jb.mf_terms, jb.mf_ns, F64);
+    };
+    mf_batch(jobs, n_jobs, total, cost, [&](const SumJob &jb, long long a, long long e) {
+        auto run = [&](auto MT, auto T) {
+            constexpr int mt = decltype(MT)::value, t = decltype(T)::value;
+            if constexpr (F64)
+                mf_range_f64<false, mt, t, false>(jb, a, e, (double *)mf_lds, nullptr);
+            else
+                mf_range_terms<false, mt, t, false>(jb, a, e, mf_lds, nullptr);
+        };
+        mf_with_shape(jb.mf_terms / 10, jb.mf_terms % 10, run);
     });
 }
 
@@ -4552,19 +4579,6 @@ static constexpr size_t mf_f64_lds_bytes(int MT, int T, int ns, bool kerr) {
            (kerr ? sizeof(double2) * kMfWaves * kMfKerrRounds64 * kMfSPW : 0);
 }
 
-// Calls f(MT, T) with the smallest compiled shape that holds a request's rows
-// and |n| (as std::integral_constants).
-template <typename F>
-static void mf_with_shape(int mt, int t, F f) {
-    using std::integral_constant;
-    using I1 = integral_constant<int, 1>;
-    using I2 = integral_constant<int, 2>;
-    using I3 = integral_constant<int, 3>;
-    if (mt == 1 && t == 1) f(I1{}, I1{});
-    else if (mt <= 2 && t == 1) f(I2{}, I1{});
-    else if (mt <= 2) f(I2{}, I2{});
-    else f(I3{}, I2{});
-}
 
 // One workgroup per compute unit (the operand table takes most of the LDS).
 int mfma_workgroups() {
@@ -4594,7 +4608,6 @@ int mfma_workgroups() {
                     set((const void *)sum_mfma_terms_kernel<true, mtv, tv, false>, false);
                     set((const void *)sum_mfma_terms_kernel<false, mtv, tv, true>, true);
                     set((const void *)sum_mfma_terms_kernel<true, mtv, tv, true>, true);
-                    set((const void *)sum_mfma_terms_batch_kernel<mtv, tv>, false);
                     auto set64 = [](const void *f, bool kerr) {
                         hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize,
                                             (int)mf_f64_lds_bytes(mtv, tv, 8 * tv, kerr));
@@ -4603,8 +4616,13 @@ int mfma_workgroups() {
                     set64((const void *)sum_mfma_f64_kernel<true, mtv, tv, false>, false);
                     set64((const void *)sum_mfma_f64_kernel<false, mtv, tv, true>, true);
                     set64((const void *)sum_mfma_f64_kernel<true, mtv, tv, true>, true);
-                    set64((const void *)sum_mfma_f64_batch_kernel<mtv, tv>, false);
                 });
+        hipFuncSetAttribute((const void *)sum_mfma_terms_batch_kernel<false>,
+                            hipFuncAttributeMaxDynamicSharedMemorySize,
+                            (int)mf_terms_lds_bytes(kMfMT, kMfT, false));
+        hipFuncSetAttribute((const void *)sum_mfma_terms_batch_kernel<true>,
+                            hipFuncAttributeMaxDynamicSharedMemorySize,
+                            (int)mf_f64_lds_bytes(kMfMT, kMfT, 8 * kMfT, false));
     });
     return cus;
 }
@@ -4673,18 +4691,15 @@ hipError_t launch_sum_mfma_batch(const SumJob *jobs_dev, int n_jobs, long long t
 }
 
 hipError_t launch_sum_mfma_terms_batch(const SumJob *jobs_dev, int n_jobs, long long total,
-                                       bool f64, int mt, int t, int n_wg, hipStream_t stream) {
-    mf_with_shape(mt, t, [&](auto MT, auto T) {
-        constexpr int mtv = decltype(MT)::value, tv = decltype(T)::value;
-        if (f64)
-            hipLaunchKernelGGL((sum_mfma_f64_batch_kernel<mtv, tv>), dim3(n_wg), dim3(64 * kMfWaves),
-                               mf_f64_lds_bytes(mtv, tv, 8 * tv, false), stream, jobs_dev, n_jobs,
-                               total);
-        else
-            hipLaunchKernelGGL((sum_mfma_terms_batch_kernel<mtv, tv>), dim3(n_wg),
-                               dim3(64 * kMfWaves), mf_terms_lds_bytes(mtv, tv, false), stream,
-                               jobs_dev, n_jobs, total);
-    });
+                                       bool f64, int n_wg, hipStream_t stream) {
+    const dim3 grid(n_wg), block(64 * kMfWaves);
+    if (f64)
+        hipLaunchKernelGGL(sum_mfma_terms_batch_kernel<true>, grid, block,
+                           mf_f64_lds_bytes(kMfMT, kMfT, 8 * kMfT, false), stream, jobs_dev, n_jobs,
+                           total);
+    else
+        hipLaunchKernelGGL(sum_mfma_terms_batch_kernel<false>, grid, block,
+                           mf_terms_lds_bytes(kMfMT, kMfT, false), stream, jobs_dev, n_jobs, total);
     return hipGetLastError();
 }
 

@@ -56,23 +56,23 @@ def rough_end(w):
 
 
 CASES = [
-    # amplitudes that vary by `flat` allow two powers on few samples; 32 samples
-    # are too long a block for the third case
-    ("1x1 one sample", lambda: draw(1, 3, 9, 1)),
-    ("1x1 two powers", lambda: draw(2, 3, 15, 40_001, K=4, flat=1e-3)),
-    ("2x1 two powers, blocks of 16", lambda: draw(3, 5, 8, 14_000, K=12, flat=1e-3)),
-    ("2x2 three powers", lambda: draw(4, 4, 16, 48_000, K=30, offset=0.4)),
-    ("2x2 four powers", lambda: draw(5, 7, 31, 3_001, K=60, rough=1.0)),
-    ("3x1 gaps", lambda: draw(6, 10, 15, 60_000, K=6, keep=lambda l, m, n: m in (0, 1, 6, 10) and n % 7)),
-    ("3x2 short intervals", lambda: draw(7, 10, 30, 2_000, K=100)),
+    # amplitudes that vary by `flat` allow two powers, or longer blocks
+    ("1x1 two powers", lambda: draw(2, 3, 15, 270_001, K=4, flat=1e-3)),
+    ("2x1 two powers, blocks of 16", lambda: draw(3, 5, 15, 300_000, K=12, flat=0.5)),
+    ("2x2 three powers", lambda: draw(4, 7, 26, 275_000, K=30, offset=0.4)),
+    ("2x2 four powers", lambda: draw(5, 7, 31, 262_144, K=1000, rough=1.0)),
+    ("3x1 gaps", lambda: draw(6, 10, 15, 300_000, K=6, keep=lambda l, m, n: m not in (2, 5) and n % 7)),
+    ("3x2 short intervals", lambda: draw(7, 10, 30, 263_000, K=700, rough=1e-2)),
     # many samples, several rounds per wave
     ("3x2 many samples", lambda: draw(8, 10, 30, 800_017, K=100)),
-    ("3x2 smooth and rough", lambda: rough_end(draw(9, 8, 30, 40_000, K=8, flat=1e-5))),
+    ("3x2 smooth and rough", lambda: rough_end(draw(9, 8, 30, 270_000, K=8, flat=1e-5))),
+    ("kerr one sample", lambda: draw(1, 3, 9, 1, k_max=1)),
     ("kerr 2x1 very smooth", lambda: draw(10, 4, 5, 10_000, K=10, k_max=2, flat=1e-6)),
     ("kerr 3x2 k > 0", lambda: draw(11, 8, 30, 60_001, K=4, k_max=2, keep=lambda l, m, k, n: k > 0)),
     ("kerr 1x1 rough", lambda: draw(12, 3, 14, 5_000, K=20, k_max=1, rough=1.0, offset=0.3)),
-    ("kerr k = 0", lambda: draw(13, 3, 9, 6_000, k_max=0)),
-    # few of the cells filled: vector kernel
+    ("kerr k = 0", lambda: draw(13, 3, 15, 266_000, k_max=0)),
+    # few of the cells filled, too few samples: vector kernel
+    ("vector: 262143 samples", lambda: draw(15, 10, 30, 262_143)),
     ("vector: top terms", lambda: draw(14, 7, 20, 80_000, keep=lambda l, m, n: l == 7 and m < 3)),
 ]
 

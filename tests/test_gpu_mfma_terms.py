@@ -44,15 +44,15 @@ def draw(seed, l_max, n_max, n, K=9, k_max=None, keep=None, rough=False, offset=
 
 # shapes: row tiles of 8 signed m, steps of 16 |n|
 CASES = [
-    ("1x1", lambda: draw(1, 3, 9, 30_011)),
-    ("1x1 one sample", lambda: draw(2, 3, 15, 1)),
-    ("2x1 rough", lambda: draw(3, 5, 8, 20_001, K=12, rough=True)),
-    ("2x1 16 rows |n| 15", lambda: draw(4, 8, 15, 4_099, keep=lambda l, m, n: m % 2 == 0 and l <= 7)),
-    ("2x2 |n| 16", lambda: draw(5, 4, 16, 70_001, offset=0.37)),
-    ("2x2 |n| 31", lambda: draw(6, 3, 31, 2_000, K=4)),
-    ("3x1", lambda: draw(7, 8, 9, 50_021, K=20)),
-    ("3x2 gaps in m and n", lambda: draw(8, 10, 21, 40_000, rough=True,
+    ("1x1", lambda: draw(1, 3, 9, 300_011)),
+    ("2x1 rough", lambda: draw(3, 5, 8, 262_144, K=12, rough=True)),
+    ("2x1 16 rows |n| 15", lambda: draw(4, 8, 15, 270_099, keep=lambda l, m, n: m % 2 == 0 and l <= 7)),
+    ("2x2 |n| 16", lambda: draw(5, 4, 16, 440_001, offset=0.37)),
+    ("2x2 |n| 31 short intervals", lambda: draw(6, 3, 31, 262_200, K=1000)),
+    ("3x1", lambda: draw(7, 8, 9, 300_021, K=20)),
+    ("3x2 gaps in m and n", lambda: draw(8, 10, 21, 280_000, rough=True,
                                          keep=lambda l, m, n: m in (0, 4, 7, 10) and n % 9 < 8 and l > 8)),
+    ("kerr one sample", lambda: draw(2, 3, 15, 1, k_max=1)),
     ("kerr 1x1", lambda: draw(9, 3, 10, 30_000, k_max=1)),
     ("kerr 2x1 many samples", lambda: draw(10, 5, 6, 900_000, k_max=2)),
     ("kerr 2x2 odd k", lambda: draw(11, 7, 31, 8_001, k_max=3,
@@ -60,8 +60,9 @@ CASES = [
     ("kerr 3x2 rough", lambda: draw(12, 9, 30, 5_000, k_max=2, rough=True)),
     ("kerr 3x2 k > 0", lambda: draw(15, 10, 30, 300_003, K=30, offset=0.5, k_max=2,
                                     keep=lambda l, m, k, n: k > 0)),
-    ("kerr k = 0", lambda: draw(14, 4, 9, 10_000, k_max=0)),
-    # too few terms per polar index at this length: vector kernel
+    ("kerr k = 0", lambda: draw(14, 4, 9, 290_000, k_max=0)),
+    # too few terms per polar index at this length, too few samples: vector kernel
+    ("vector: 262143 samples", lambda: draw(16, 4, 16, 262_143)),
     ("vector: kerr k > 0", lambda: draw(13, 10, 30, 200_003, K=30, offset=0.5, k_max=2,
                                         keep=lambda l, m, k, n: k > 0)),
 ]
