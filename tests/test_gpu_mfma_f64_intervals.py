@@ -1,0 +1,111 @@
+"""Binary64 matrix-core summation where its blocks of samples meet the knot grid:
+intervals of fewer samples than a block, down to none.
+
+Bar: 1e-13 of the largest |h| (the phases' rounding, 2^-53 pi (|m| + |n| + |k|),
+stays below 1.5e-14), or twice the vector path's error where the fit of two
+close knots itself is worse.
+"""
+import numpy as np
+import pytest
+
+import oracle
+from paper_2104_04582_amd import synth
+
+pytestmark = pytest.mark.gpu
+SHORT_BAR = 1e-13
+
+
+@pytest.fixture(scope="module")
+def env():
+    import torch
+    from paper_2104_04582_amd import native
+    native.load()
+    assert torch.cuda.is_available(), "GPU tests need a GPU"
+    return native, torch, torch.device("cuda:0")
+
+
+def build(seed, l_max, n_max, n, knots, k_max=None, noise=0.0):
+    """Cubic amplitudes in t / T on the given knots ((n samples, 10 s) -> times)."""
+    rng = np.random.default_rng(seed)
+    T = 10.0 * n
+    t = knots(T)
+    if k_max is None:
+        w = synth.draw_waveform(rng, synth.mode_list(2, l_max, n_max), T, len(t), 10.0)
+    else:
+        w = synth.draw_kerr(rng, synth.mode_list_kerr(2, l_max, k_max, n_max), T, len(t), 10.0)
+    s = t / T
+    w.amp = np.einsum("pk,mpc->kmc", np.stack([s ** p for p in range(4)]), w.amp_poly)
+    w.amp = np.ascontiguousarray(w.amp * (1.0 + noise * rng.standard_normal(w.amp.shape)))
+    w.t_knots = t
+    w.phi_phi = synth.chirp_phase(t, w.f0, w.tc)
+    w.phi_r = w.kappa * w.phi_phi
+    if k_max is not None:
+        w.phi_theta = 0.93 * w.phi_phi
+    return w
+
+
+def close_pair(K, samples):
+    """K log-spaced knots, and one `samples` samples after the middle one, which
+    lies on a sample."""
+    def knots(T):
+        t = synth.knot_times(T, K, 1.2 * T)
+        t[K // 2] = 10.0 * round(t[K // 2] / 10.0)
+        return np.insert(t, K // 2 + 1, t[K // 2] + 10.0 * samples)
+    return knots
+
+
+def plunge(K):
+    """Spacing falling by 10^5 towards the end."""
+    def knots(T):
+        t = np.concatenate([[0.0], np.cumsum(np.geomspace(1.0, 1e-5, K - 1))])
+        t *= T / t[-1]
+        t[-1] = T
+        return t
+    return knots
+
+
+def uniform(K):
+    return lambda T: np.linspace(0.0, T, K)
+
+
+GAPS = (63, 31, 8, 2, 0.5, 1e-3)
+SHORT = [(f"{'kerr ' if kerr else ''}{g} samples, noise {q}", dict(
+    seed=i, l_max=6 if kerr else 10, n_max=12 if kerr else 30, n=9_000 if kerr else 263_000,
+    knots=close_pair(60, g), k_max=2 if kerr else None, noise=q))
+    for i, g in enumerate(GAPS) for kerr in (False, True) for q in (0.0, 1e-2)]
+SHORT += [(f"kerr {n} samples on {K} knots", dict(seed=n + K, l_max=6, n_max=12, n=n, knots=uniform(K), k_max=2))
+          for n, K in ((64, 400), (600, 400), (2_000, 100), (4_000, 100))]
+SHORT += [("plunge", dict(seed=70, l_max=10, n_max=30, n=300_000, knots=plunge(100))),
+          ("kerr plunge", dict(seed=71, l_max=6, n_max=12, n=9_000, knots=plunge(100), k_max=2))]
+
+
+def sums(env, w):
+    """(sample indices, default path, vector path, oracle): the samples around
+    every interval's start, all of the shortest intervals and some others."""
+    native, torch, dev = env
+    d = lambda a: torch.from_numpy(np.ascontiguousarray(a)).to(dev)
+    out = []
+    for vec in (False, True):
+        with native.Plan(0, "fp64", vector_only=vec) as plan:
+            if w.phi_theta is None:
+                sp = plan.spline_fit(w.t_knots, d(w.phi_phi), d(w.phi_r), w.lmn, d(w.amp))
+            else:
+                sp = plan.spline_fit_kerr(w.t_knots, d(w.phi_phi), d(w.phi_theta), d(w.phi_r), w.lmn, d(w.amp))
+            out.append(plan.mode_sum(sp, w.theta, w.phi, w.dt, w.n_samples).cpu().numpy())
+    st = native.host_interval_starts(w.t_knots, 0.0, w.dt, w.n_samples)
+    idx = set(np.random.default_rng(1).choice(w.n_samples, min(300, w.n_samples), replace=False).tolist())
+    for a, e in zip(st[:-1], st[1:]):
+        idx.update(range(a, e) if e - a < 70 else (a, a + 15, a + 31, e - 1))
+    idx = np.array(sorted(idx)[:4000])
+    return idx, out[0], out[1], oracle.mode_sum_waveform(w, idx=idx)
+
+
+@pytest.mark.parametrize("case", SHORT, ids=[c[0] for c in SHORT])
+def test_short_intervals(env, case):
+    w = build(**case[1])
+    idx, got, vec, ref = sums(env, w)
+    err, base = oracle.max_rel_error(got[idx], ref), oracle.max_rel_error(vec[idx], ref)
+    print(f"    {case[0]}: max_rel_err={err:.2e} (vector path {base:.2e})", flush=True)
+    assert not np.array_equal(got, vec)             # (two paths round differently)
+    assert err <= max(SHORT_BAR, 2.0 * base)
+    assert oracle.max_rel_error(got, vec) <= max(SHORT_BAR, 2.0 * base)
