@@ -3225,15 +3225,19 @@ __device__ __forceinline__ void mf_batch(const SumJob *jobs, int n_jobs, long lo
 // T_0 and T_1 formed in binary64 from the staged b_p for each use (6 operations of
 // 4 cycles against 4 or 2 products of 64).  The rest is small: |d| <= w, half the
 // block's width in v.  Where (M_2 + 4 M_3) w^2 <= 2^-30 M_0 (M_p the largest |b_p| of the
-// interval, M_0 of p <= 1) it is summed from fp16 hi + lo operands with binary32
-// accumulation, 22 bits and so below 2^-52 M_0 (the vector kernel's Horner
-// recurrence rounds at 2^-53 of its running sum for each of its terms), at 1/16
-// of the binary64 products' cost: 4 binary64 operations per term in all.  Else
-// T_2 = C''(v0) / 2 takes binary64 products too and only d^3 b_3 is left to
-// fp16 (w^3 M_3 <= 2^-30 M_0), else all four powers take them.
+// interval, M_0 of p <= 1) it is summed from fp16 hi + lo operands (22 bits, b_2 and
+// b_3 each in their own scale) with binary32 harmonics and accumulation, at 1/16 of
+// the binary64 products' cost: 4 binary64 operations per term in all.  The
+// harmonics f^a and E^row are binary32 power chains of up to 31 and 24 steps, so
+// a term's rest is good to 2^-19 at worst and adds up to 2^-49 M_0; the vector kernel's
+// Horner recurrence rounds at 2^-53 of its running sum once per term it walks.
+// Else T_2 = C''(v0) / 2 takes binary64 products too and only d^3 b_3 is left to
+// fp16 (w^3 M_3 <= 2^-30 M_0), else all four powers take them.  Measured at the limits
+// (cubics swept through them, modes of one size, 0.02 to 3 million samples): the
+// largest error is 1.3e-15 to 4e-15, as with four powers everywhere, the vector
+// kernel's 4e-15 to 1e-14.
 // Measured (3843 modes, 1281 terms, 3.16 million samples): 1430 -> 920 us, of which
-// the products 560 at the rate of a large binary64 matrix product; the largest
-// error against the oracle 1e-15 to 2e-15, the vector kernel's 5e-15 and more.
+// the products 560 at the rate of a large binary64 matrix product.
 struct MfPlan64 {
     int P;          // powers in binary64 products: 2, 3 or 4
     int nt;         // P = 2: sample tiles of 16 per block, 2 or 1
@@ -3244,7 +3248,8 @@ template <int MT, int T>
 struct MfTerms64 {
     int idx[8 * MT][32 * T];            // n + 16 T; -1: no term
     unsigned m01[4 * MT], m2[4 * MT], m3[4 * MT];   // largest |b_p| per row pair (binary32 bits)
-    float un[4 * MT];                   // 2^E of the fp16 values
+    float un[4 * MT];                   // 2^E of the fp16 values b_2 (E that of b_2, b_3)
+    float rat[4 * MT];                  // 2^E of b_3 over it
 };
 
 // Cubic in u -> cubic in v = 2 u - 1.
@@ -3331,12 +3336,23 @@ __device__ __forceinline__ void mf64_stage(const SumJob &jb, int iv, int kp, int
         if (wave + q * kMfWaves >= kTasks) continue;
         const int task = wave + q * kMfWaves, mt = task / (2 * T), ta = task % (2 * T);
         const int r = lane >> 3, a = 8 * ta + (lane & 7), t = ta >> 1;
-        const float mx = __uint_as_float(max(M.m2[4 * mt + (r >> 1)], M.m3[4 * mt + (r >> 1)]));
-        int e = 0;
+        // scales of b_2 (that of the larger of b_2 and b_3) and of b_3 (its own: in
+        // that of b_2 a b_3 of 2^-7 b_2 keeps only 17 bits, and three powers in
+        // binary64 were off by 1.2e-14 of |h| near their limit, now 2.5e-15)
+        const float m3 = __uint_as_float(M.m3[4 * mt + (r >> 1)]);
+        const float mx = fmaxf(__uint_as_float(M.m2[4 * mt + (r >> 1)]), m3);
+        int e = 0, e3 = 0;
         if (mx > 0.0f && mx < INFINITY) frexpf(mx, &e);
-        e = min(max(e, -126), 127);
-        const double sc = ldexp(1.0, -e);
-        if ((lane & 15) == 0) M.un[4 * mt + (r >> 1)] = ldexpf(1.0f, e);
+        e = e3 = min(max(e, -126), 127);
+        if (m3 > 0.0f && m3 < INFINITY) {
+            frexpf(m3, &e3);
+            e3 = min(max(e3, -126), e);
+        }
+        const double sc[2] = {ldexp(1.0, -e), ldexp(1.0, -e3)};
+        if ((lane & 15) == 0) {
+            M.un[4 * mt + (r >> 1)] = ldexpf(1.0f, e);
+            M.rat[4 * mt + (r >> 1)] = ldexpf(1.0f, e3 - e);
+        }
         // columns per power: (Re P + Re Q, Im Q - Im P) of row component 0,
         // (Im P + Im Q, Re P - Re Q) of component 1
         const double2 *P = v[q], *Q = v[q] + 4;
@@ -3361,7 +3377,7 @@ __device__ __forceinline__ void mf64_stage(const SumJob &jb, int iv, int kp, int
 #pragma unroll
             for (int p = 2; p < 4; ++p) {
                 unsigned hi, lo;
-                split_pair((float)(o[c][0][p] * sc), (float)(o[c][1][p] * sc), hi, lo);
+                split_pair((float)(o[c][0][p] * sc[p - 2]), (float)(o[c][1][p] * sc[p - 2]), hi, lo);
                 unsigned *f = rest + (((mt * 2 + p - 2) * T + t) * 128 + 2 * r + c + 16 * g) * 4 + j;
                 f[0] = hi;
                 f[256] = lo;
@@ -3481,9 +3497,9 @@ __device__ __forceinline__ void mf64_rows(const R (&c)[4][4], R er, R ei, R *yr,
 // The rest of a round, sum of d^(P-2).. b_p f^a over fp16 operands, without its factor
 // d^2 (P = 2) or d^3 (P = 3): this lane's sample.
 template <int MT, int T, int P>
-__device__ __forceinline__ void mf64_rest(const uint4 *rest, const float *un, bool lo3, float fr,
-                                          float fi, float vq, float er, float ei, float e8r,
-                                          float e8i, float *yr, float *yi) {
+__device__ __forceinline__ void mf64_rest(const uint4 *rest, const float *un, const float *rat,
+                                          bool lo3, float fr, float fi, float vq, float er,
+                                          float ei, float e8r, float e8i, float *yr, float *yi) {
     const int lane = threadIdx.x & (kWave - 1), col = lane & 15, g = lane >> 4;
     mf_u4 bh[4][T], bl[4][T];
     float vv[4];
@@ -3506,13 +3522,16 @@ __device__ __forceinline__ void mf64_rest(const uint4 *rest, const float *un, bo
         };
 #pragma unroll
         for (int nt = 0; nt < 4; ++nt) s[nt] = mf_float4{0.0f, 0.0f, 0.0f, 0.0f};
+        const float r = rat[4 * mt + g];
 #pragma unroll
         for (int p = 3; p >= P; --p) {
             if (p == 2) {
 #pragma unroll
-                for (int nt = 0; nt < 4; ++nt)
+                for (int nt = 0; nt < 4; ++nt) {
+                    const float vr = vv[nt] * r;
 #pragma unroll
-                    for (int i = 0; i < 4; ++i) s[nt][i] = s[nt][i] * vv[nt];
+                    for (int i = 0; i < 4; ++i) s[nt][i] = s[nt][i] * vr;
+                }
             }
 #pragma unroll
             for (int t = 0; t < T; ++t) {
@@ -3525,7 +3544,7 @@ __device__ __forceinline__ void mf64_rest(const uint4 *rest, const float *un, bo
                 prod(ah, bh, t);
             }
         }
-        const float u = un[4 * mt + g];
+        const float u = P == 2 ? un[4 * mt + g] : un[4 * mt + g] * r;
         float c[4][4];
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
@@ -3549,7 +3568,8 @@ template <bool INNER, int MT, int T, bool KERR, int P, int NT>
 __device__ __forceinline__ double2 mf64_round(const SumJob &jb, int iv, double ti, double inv_h2,
                                               bool lo3, long long wbase, long long e, int ns,
                                               const double *base, const uint4 *rest,
-                                              const float *un, const MfPolar64 &po) {
+                                              const float *un, const float *rat,
+                                              const MfPolar64 &po) {
     const int lane = threadIdx.x & (kWave - 1), col = lane & 15, g = lane >> 4;
     const FEW_AS4 double *pc = cptr(jb.pcoef) + (size_t)iv * (KERR ? 24 : 16);
     const long long jo = wbase + lane;
@@ -3612,7 +3632,7 @@ __device__ __forceinline__ double2 mf64_round(const SumJob &jb, int iv, double t
     }
     float yr = 0.0f, yi = 0.0f;
     if constexpr (P < 4)
-        mf64_rest<MT, T, P>(rest, un, lo3, (float)fr, (float)fi, (float)fma(3.0, v0, dl), (float)Er,
+        mf64_rest<MT, T, P>(rest, un, rat, lo3, (float)fr, (float)fi, (float)fma(3.0, v0, dl), (float)Er,
                             (float)Ei, (float)E8r, (float)E8i, &yr, &yi);
     double sr = 0.0, si = 0.0;
 #pragma unroll 1
@@ -3769,7 +3789,7 @@ __device__ void mf_range_f64(const SumJob &jb, long long lo, long long hi, doubl
                         if constexpr (KERR) po.hp = hp + (r - ca) * kMfSPW;
                         const double2 v = mf64_round<INNER, MT, T, KERR, decltype(P)::value, decltype(NT)::value>(
                             jb, iv, ti, inv_h2, I.lo3, a + (long long)r * kMfSPW, e, ns, base,
-                            (const uint4 *)rest, M.un, po);
+                            (const uint4 *)rest, M.un, M.rat, po);
                         if constexpr (INNER) {
                             double2 s = iacc[threadIdx.x];
                             s.x = s.x + v.x;

@@ -1,9 +1,12 @@
 """Binary64 matrix-core summation where its blocks of samples meet the knot grid:
-intervals of fewer samples than a block, down to none.
+intervals of fewer samples than a block, down to none, and amplitudes whose
+curvature lies just below what the fp16 products of the rest may carry.
 
-Bar: 1e-13 of the largest |h| (the phases' rounding, 2^-53 pi (|m| + |n| + |k|),
-stays below 1.5e-14), or twice the vector path's error where the fit of two
-close knots itself is worse.
+Bars: in short intervals 1e-13 of the largest |h| (the phases' rounding, 2^-53 pi
+(|m| + |n| + |k|), stays below 1.5e-14), or twice the vector path's error where
+the fit of two close knots itself is worse; for the rest (|m| + |n| + |k| + 8)
+2^-52: one rounding of the harmonics per unit of the indices and eight for the
+cubic and the sums, against 2^-52 that the rest may add.
 """
 import numpy as np
 import pytest
@@ -24,7 +27,7 @@ def env():
     return native, torch, torch.device("cuda:0")
 
 
-def build(seed, l_max, n_max, n, knots, k_max=None, noise=0.0):
+def build(seed, l_max, n_max, n, knots, k_max=None, noise=0.0, flat=False):
     """Cubic amplitudes in t / T on the given knots ((n samples, 10 s) -> times)."""
     rng = np.random.default_rng(seed)
     T = 10.0 * n
@@ -33,8 +36,9 @@ def build(seed, l_max, n_max, n, knots, k_max=None, noise=0.0):
         w = synth.draw_waveform(rng, synth.mode_list(2, l_max, n_max), T, len(t), 10.0)
     else:
         w = synth.draw_kerr(rng, synth.mode_list_kerr(2, l_max, k_max, n_max), T, len(t), 10.0)
+    poly = rng.standard_normal(w.amp_poly.shape) if flat else w.amp_poly
     s = t / T
-    w.amp = np.einsum("pk,mpc->kmc", np.stack([s ** p for p in range(4)]), w.amp_poly)
+    w.amp = np.einsum("pk,mpc->kmc", np.stack([s ** p for p in range(4)]), poly)
     w.amp = np.ascontiguousarray(w.amp * (1.0 + noise * rng.standard_normal(w.amp.shape)))
     w.t_knots = t
     w.phi_phi = synth.chirp_phase(t, w.f0, w.tc)
@@ -109,3 +113,31 @@ def test_short_intervals(env, case):
     assert not np.array_equal(got, vec)             # (two paths round differently)
     assert err <= max(SHORT_BAR, 2.0 * base)
     assert oracle.max_rel_error(got, vec) <= max(SHORT_BAR, 2.0 * base)
+
+
+def log_spaced(K):
+    return lambda T: synth.knot_times(T, K, 1.2 * T)
+
+
+# modes of one size, cubics in t / T: M_3 w^3 is 2^-31 M_0 for the 20000 samples
+NEAR = [(f"{l_max} {n_max} {n} on {K} knots, seed {s}",
+         dict(seed=s, l_max=l_max, n_max=n_max, n=n, knots=log_spaced(K), k_max=k_max, flat=True))
+        for l_max, n_max, n, K, k_max in ((5, 15, 20_000, 60, 2), (11, 12, 20_000, 60, 2),
+                                          (5, 15, 30_000, 60, 2), (5, 15, 40_000, 60, 2),
+                                          (10, 30, 270_000, 60, None))
+        for s in (0, 1, 2)]
+
+
+@pytest.mark.parametrize("case", NEAR, ids=[c[0] for c in NEAR])
+def test_rest_near_its_limit(env, case):
+    w = build(**case[1])
+    idx, got, vec, _ = sums(env, w)
+    idx = np.arange(w.n_samples - 7 * 2_800, w.n_samples, 7)
+    idx = idx[idx >= 0]
+    ref = oracle.mode_sum_waveform(w, idx=idx)
+    size = np.max(np.abs(vec))
+    err, base = (float(np.max(np.abs(a[idx] - ref)) / size) for a in (got, vec))
+    bar = (w.lmn[:, 1:].max(axis=0).sum() + 8) * 2.0 ** -52
+    print(f"    {case[0]}: max_rel_err={err:.2e} (vector path {base:.2e}, bar {bar:.1e})", flush=True)
+    assert not np.array_equal(got, vec)
+    assert err <= bar
