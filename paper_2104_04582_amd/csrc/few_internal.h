@@ -349,6 +349,16 @@ struct TermLayout {
 // them share its persistent launch, and a second launch of few workgroups at
 // work each costs more than it saves (6 of up to 10 days, binary32, 111 / 127
 // us; 6 of up to 30 days, binary64, 430 / 465).
+// Binary32, accuracy: the matrix kernel forms f^n as a power of the sample's
+// rounded f, an error that grows with |n|; the vector kernel seeds a segment with its
+// exact phase and then walks it, an error that grows with the segment's length
+// (and with the rows whose seeds are chained).  Lists that lie far from n = 0
+// stay on the vector kernel: 21 rows, n in [a, b], 3 million samples, largest
+// error of matrix-core / vector (mean of 10 draws; modes of one size and
+// decaying ones): [20, 31] 1.3e-6 / 7.1e-7 and 9.5e-7 / 4.7e-7, [12, 31] 9.9e-7 / 1.0e-6
+// and 7.6e-7 / 6.6e-7, [2, 12] 7.3e-7 / 7.0e-7 and 5.4e-7 / 4.4e-7; on the other side of
+// the line [5, 31] 1.0e-6 / 1.5e-6 and 6.7e-7 / 7.4e-7, [0, 20] 7.8e-7 / 9.9e-7 and
+// 5.4e-7 / 7.1e-7, [-3, 3] 6.8e-7 / 1.1e-6 and 5.3e-7 / 7.7e-7.
 // (The fold table, its size and its launches are the same either way.)
 inline bool mf_terms_path(const TermLayout &L, long long n, bool fp32) {
     if (L.mf_terms == 0) return false;
@@ -356,6 +366,7 @@ inline bool mf_terms_path(const TermLayout &L, long long n, bool fp32) {
     const int shape = mt == 1 && t == 1 ? 0 : mt <= 2 && t == 1 ? 1 : mt <= 2 ? 2 : 3;
     const int nk = L.k_max - L.k_min + 1;
     if (nk == 1 && n < 262144) return false;
+    if (fp32 && 10 * (L.max_seg_terms - 1) < 7 * std::max(-L.n_min, L.n_max) + 39) return false;
     if (!fp32) {
         const int steps = (L.n_max > -L.n_min ? L.n_max : -L.n_min) / 2 + 1;
         const int cells = 8 * (shape == 0 ? 1 : shape == 3 ? 3 : 2) * 4 * steps;
