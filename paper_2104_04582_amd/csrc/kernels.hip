@@ -3147,19 +3147,40 @@ __device__ __forceinline__ void mf_share_w(const float *wl, long long total, lon
     *hi = a + (e - a) * (j + 1) / S;
 }
 
+// Sums from the fold table are shared out in units: an interval counts its
+// samples and a gap before them (mf_gap), so that a workgroup's share holds
+// fewer samples where it has more intervals to form operands for.  Unit u -> sample.
+__device__ __forceinline__ long long mf_unit_sample(const SumJob &jb, long long u, long long gap) {
+    const FEW_AS4 long long *st = cptr(jb.starts);
+    int iv = 0, top = jb.K - 2;
+    while (iv < top) {
+        const int mid = (iv + top + 1) >> 1;
+        if (st[mid] + gap * mid <= u) iv = mid; else top = mid - 1;
+    }
+    const long long a = st[iv], r = u - a - gap * iv;
+    return r <= gap ? a : min(jb.n, a + r - gap);
+}
+
 // A single-request launch: this workgroup's share of the samples through
 // range(lo, hi), its time reported, and (INNER) its sums of iacc in partial.
+// gap: of mf_unit_sample.
 template <bool INNER, typename Range>
-__device__ __forceinline__ void mf_single(const SumJob &jb, double2 *iacc, Range range) {
+__device__ __forceinline__ void mf_single(const SumJob &jb, double2 *iacc, long long gap,
+                                          Range range) {
     if constexpr (INNER) iacc[threadIdx.x] = make_double2(0.0, 0.0);
     long long lo, hi;
     // the inner-product launch keeps the equal split (its binary64 sums
     // then do not depend on the weights)
     const unsigned long long t0 = wall_clock64();
+    const long long units = jb.n + gap * (jb.K - 1);
     if (!INNER && mf_balanced(jb))
-        mf_share_w(jb.bw, jb.n, &lo, &hi);
+        mf_share_w(jb.bw, units, &lo, &hi);
     else
-        mf_share(jb.n, &lo, &hi);
+        mf_share(units, &lo, &hi);
+    if (gap > 0) {
+        lo = mf_unit_sample(jb, lo, gap);
+        hi = mf_unit_sample(jb, hi, gap);
+    }
     range(lo, hi);
     if (!INNER && jb.btime != nullptr && (int)blockIdx.x < kMfBalanceWG) {
         __syncthreads();
@@ -3184,9 +3205,9 @@ __device__ __forceinline__ void mf_single(const SumJob &jb, double2 *iacc, Range
     }
 }
 
-// A batched launch: the jobs' samples, cost(job) units each, laid end to end
-// (job j from unit sample_base_j), split into equal shares; range(job, a, e).
-template <typename Cost, typename Range>
+// A batched launch: the jobs' units (samples and, with GAPS, gaps), cost(job) each,
+// laid end to end (job j from sample_base_j), split into equal shares; range(job, a, e).
+template <bool GAPS, typename Cost, typename Range>
 __device__ __forceinline__ void mf_batch(const SumJob *jobs, int n_jobs, long long total,
                                          Cost cost, Range range) {
     long long lo, hi;
@@ -3202,8 +3223,14 @@ __device__ __forceinline__ void mf_batch(const SumJob *jobs, int n_jobs, long lo
         const SumJob jb = load_uniform(jobs + j);
         // (a share's end and the next one's start round to the same sample)
         const long long c = cost(jb);
-        const long long a = (max(lo, b0) - b0 + c - 1) / c;
-        const long long e = (min(hi, b0 + jb.n * c) - b0 + c - 1) / c;
+        const long long gap = GAPS ? mf_gap(jb.n, jb.mf_f64) : 0;
+        const long long units = jb.n + gap * (jb.K - 1);
+        long long a = (max(lo, b0) - b0 + c - 1) / c;
+        long long e = (min(hi, b0 + units * c) - b0 + c - 1) / c;
+        if (GAPS) {
+            a = mf_unit_sample(jb, a, gap);
+            e = mf_unit_sample(jb, e, gap);
+        }
         if (a < e) range(jb, a, e);
     }
 }
@@ -3819,7 +3846,7 @@ __global__ __launch_bounds__(64 * kMfWaves) void sum_mfma_kernel(SumJob jb) {
     __shared__ float msc[kMfRows / 2];
     __shared__ int mm[kMfRows];
     __shared__ double2 iacc[INNER ? 64 * kMfWaves : 1];
-    mf_single<INNER>(jb, iacc, [&](long long lo, long long hi) {
+    mf_single<INNER>(jb, iacc, 0, [&](long long lo, long long hi) {
         mf_range<INNER, CONSEC>(jb, lo, hi, mf_lds, msc, mm, iacc);
     });
 }
@@ -3831,7 +3858,7 @@ __global__ __launch_bounds__(64 * kMfWaves) void sum_mfma_batch_kernel(const Sum
     __shared__ float msc[kMfRows / 2];
     __shared__ int mm[kMfRows];
     auto one = [](const SumJob &) { return 1ll; };
-    mf_batch(jobs, n_jobs, total, one, [&](const SumJob &jb, long long a, long long e) {
+    mf_batch<false>(jobs, n_jobs, total, one, [&](const SumJob &jb, long long a, long long e) {
         mf_range<false, CONSEC>(jb, a, e, mf_lds, msc, mm, nullptr);
     });
 }
@@ -3840,7 +3867,7 @@ template <bool INNER, int MT, int T, bool KERR>
 __global__ __launch_bounds__(64 * kMfWaves) void sum_mfma_terms_kernel(SumJob jb) {
     extern __shared__ float4 mf_lds[];
     __shared__ double2 iacc[INNER ? 64 * kMfWaves : 1];
-    mf_single<INNER>(jb, iacc, [&](long long lo, long long hi) {
+    mf_single<INNER>(jb, iacc, mf_gap(jb.n, false), [&](long long lo, long long hi) {
         mf_range_terms<INNER, MT, T, KERR>(jb, lo, hi, mf_lds, iacc);
     });
 }
@@ -3849,7 +3876,7 @@ template <bool INNER, int MT, int T, bool KERR>
 __global__ __launch_bounds__(64 * kMfWaves) void sum_mfma_f64_kernel(SumJob jb) {
     extern __shared__ float4 mf_lds[];
     __shared__ double2 iacc[INNER ? 64 * kMfWaves : 1];
-    mf_single<INNER>(jb, iacc, [&](long long lo, long long hi) {
+    mf_single<INNER>(jb, iacc, mf_gap(jb.n, true), [&](long long lo, long long hi) {
         mf_range_f64<INNER, MT, T, KERR>(jb, lo, hi, (double *)mf_lds, iacc);
     });
 }
@@ -3879,7 +3906,7 @@ __global__ __launch_bounds__(64 * kMfWaves) void sum_mfma_terms_batch_kernel(con
     auto cost = [](const SumJob &jb) {
         return (long long)mf_terms_cost(jb.mf_terms, jb.mf_ns, F64);
     };
-    mf_batch(jobs, n_jobs, total, cost, [&](const SumJob &jb, long long a, long long e) {
+    mf_batch<true>(jobs, n_jobs, total, cost, [&](const SumJob &jb, long long a, long long e) {
         auto run = [&](auto MT, auto T) {
             constexpr int mt = decltype(MT)::value, t = decltype(T)::value;
             if constexpr (F64)
