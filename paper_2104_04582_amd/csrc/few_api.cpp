@@ -227,7 +227,10 @@ class PinnedPool {
 };
 
 // Sums from the fold table take part in the XCD split weights from this many
-// samples on (below, their times are those of forming the operands).
+// samples on.  Below, a workgroup's time is that of forming its operands, and the
+// weights cost 0.6 us (270000 samples 23.0 -> 23.6 us); above, they make no
+// difference on a card whose XCDs run alike (800000 samples 30.8 / 31.4 us without /
+// with, 3.16 million 62.5 / 63.0) and even out one whose XCDs do not.
 constexpr long long kMfSplitMin = 786432;
 
 enum Stage { ST_FIT = 0, ST_PREP = 1, ST_SUM = 2 };
@@ -244,7 +247,7 @@ struct HostReq {
     bool mfma = false;         // binary32 sums of this request run on the matrix-core path
     bool terms_ok = false;     // .. from its fold table, where mf_terms_path says so
     bool fp32 = false;
-    bool mf_terms(long long n) const { return terms_ok && mf_terms_path(terms, n, fp32); }
+    bool mf_terms(long long n) const { return terms_ok && mf_terms_path(terms, n, K, fp32); }
     ~HostReq() { free_term_layout(&terms); }
 };
 

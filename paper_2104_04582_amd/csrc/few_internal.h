@@ -317,33 +317,48 @@ struct TermLayout {
     int m_min = 0, k_min = 0, k_max = 0;
 };
 
-// Whether a sum over n samples of this layout (mf_terms != 0, not mfma) runs on
-// the matrix cores.  Their cost per sample depends on the shape alone (rows,
-// |n|), the vector kernel's on the terms, and each workgroup first forms its
-// operands (6 to 10 us per interval and polar index), which only many samples
-// repay; short generic-Kerr sums are split over the terms by the vector kernel.
-// Where the two meet, in terms per polar index, measured as whole requests
-// (60 knots, 10 s cadence; vector / matrix-core, us):
-//   365 days: 7 rows, |n| <= 3, 49 terms 80.5 / 76.5; 11 rows, |n| <= 3, 77 terms
-//     103.5 / 87.6; 17 rows, |n| <= 4, 153 terms 158 / 130; Kerr |k| <= 2, 7 rows,
-//     |n| <= 3, 49 terms 258 / 292, |n| <= 5, 77 terms 340 / 293
-//   100 days: 7 rows, |n| <= 5, 77 terms 54.0 / 51.4; 11 rows, |n| <= 3, 77 terms 58.0 /
-//     57.4; 9 rows, |n| <= 20, 369 terms 108 / 66; 17 rows, |n| <= 4, 153 terms
-//     77.2 / 78.5; Kerr |k| <= 2, 21 rows, |n| <= 20, 861 terms 880 / 291
-//   30 days: 7 rows, |n| <= 8, 119 terms 43.8 / 43.1; 11 rows, |n| <= 5, 121
-//     terms 46.6 / 47.7; 7 rows, |n| <= 17, 245 terms 54.6 / 49.9; 17 rows,
-//     |n| <= 7, 255 terms 62.0 / 60.3 and Kerr 154.8 / 169.6
-//   1 day, Kerr: 11 rows, |n| <= 8, 187 terms 111 / 91; 9 rows, |n| <= 20, 369
-//     terms 95.8 / 105; 17 rows, |n| <= 12, 425 terms 115 / 140 and 21 rows,
-//     |n| <= 20, 861 terms 201 / 172
+// Whether a sum over n samples on K knots of this layout (mf_terms != 0, not mfma)
+// runs on the matrix cores.  Their cost per sample depends on the shape alone
+// (rows, |n|), the vector kernel's on the terms, and each workgroup first forms
+// its operands (with one round of samples 6 us for 16 rows and |n| < 16 to 12 us for
+// 24 rows and |n| < 32 in binary32, 11 to 38 us in binary64; per interval and polar
+// index), which only many samples repay; short generic-Kerr sums are split over the terms
+// by the vector kernel.  Measured as sums of a kept spline, fold included (10 s
+// cadence, log-spaced knots; vector / matrix-core on smooth amplitudes / on
+// amplitudes with 10 % noise at every knot, us):
+//   3.16 million samples, 60 knots: 7 rows, |n| <= 5, 77 terms 81 / 54 / 62; 11 rows,
+//     |n| <= 3, 77 terms 90 / 64 / 94; 17 rows, |n| <= 4, 153 terms 145 / 102 / 123;
+//     on 1000 knots 125 / 97 / 103, 126 / 109 / 128, 196 / 165 / 197
+//   1 million samples, 60 knots: 36 / 30 / 32, 41 / 36 / 41, 17 rows, |n| <= 8, 289
+//     terms 103 / 55 / 58; on 1000 knots 70 / 72 / 73, 75 / 80 / 85, 141 / 115 / 124
+//   262144 samples, 60 knots: 7 rows, |n| <= 8, 119 terms 23 / 20 / 21; 11 rows, |n| <= 6,
+//     143 terms 27 / 23 / 24; 7 rows, |n| <= 17, 245 terms 33 / 24 / 25; 17 rows,
+//     |n| <= 8 44 / 33 / 33; on 1000 knots 65 / 60 / 63, 76 / 67 / 70, 91 / 72 / 76, 111 / 92 / 95
+//   Kerr, 8640 samples, 60 knots, terms per polar index: 3 x 147 45 / 25 / 25, 5 x 187
+//     88 / 39 / 40, 5 x 1281 209 / 73 / 75; 1000 samples on 900 knots 79 / 100 / 102,
+//     125 / 156 / 163, 624 / 449 / 462
+// (The lines for short Kerr sums are cautious: sums that would gain lie below them,
+// 8640 samples, 5 x 341 terms 67 / 41, 5 x 425 85 / 62.)
 // Binary64: both kernels are bound by the binary64 unit, the vector one with
 // its terms, the matrix one with the cells (row, n) that its products cover,
-// empty ones too; at 3.15 million samples (365 days, 10 s) 46 + 1.07 terms against
-// 125 + 0.5 cells us (full 3843-mode list, 1281 terms of 1536 cells 1460 / 934;
-// 217 of 256 308 / 293; 861 of 1056 1015 / 717; selected lists, 351 of 768
-// 513 / 570 and 870 of 1536 1080 / 927).  Below one round per SIMD the vector
-// kernel's serial walk over the terms is what a call waits for: one day, Kerr
-// 5 x 99 terms 148 / 127 (at 3 days 150 / 154), 3 x 341 terms 233 / 130.
+// empty ones too, and with the powers of the cubic that take binary64 products:
+// two on smooth amplitudes, three or four on noise, which the rule cannot know.
+// Vector / matrix-core smooth / 10 % noise, us, terms of cells:
+//   100 knots: 3.16 million samples 1281 of 1536 1605 / 954 / 1187, 1037 of 1536 1306 / 936 /
+//     1264, 671 of 1024 814 / 670 / 860, 217 of 256 334 / 284 / 317; 0.8 million 491 / 279 /
+//     397, 421 / 277 / 422, 286 / 208 / 282, 110 / 99 / 110; 262144 278 / 169 / 196, 234 /
+//     167 / 193, 150 / 123 / 141, 60 / 54 / 58
+//   1000 knots: 0.8 million samples 615 / 443 / 640, 498 / 436 / 622, 338 / 324 / 443,
+//     146 / 164 / 182; 262144 326 / 321 / 363, 272 / 313 / 351, 188 / 235 / 254, 89 / 114 / 120
+//   so the line rises with the knots; on smooth amplitudes nothing beyond it is slower
+//   than the vector kernel (up to 5 % at 1000 knots), on 10 % noise up to 1.2 times
+//   (0.66 of the cells filled, 150 knots, 1.6 million samples 445 / 363 / 537).
+//   Kerr, 0.4 million samples, 60 knots, five polar indices: 341 of 512 458 / 405 /
+//     481, 425 of 672 583 / 548 / 603, 1281 of 1536 1619 / 912 / 1211
+// Below one round per SIMD the vector kernel's serial walk over the terms is
+// what a call waits for: 8640 samples, 60 knots, Kerr, 5 x 119 terms 134 / 56, 5 x 341
+// 341 / 95; 30000 samples 135 / 75 and 341 / 132; 8640 samples on 400 knots 153 / 114 and
+// 377 / 196.
 // Schwarzschild requests below 262144 samples stay on the vector kernel: alone
 // they would gain (1281 terms over one day, binary64, 265 / 111), but batches of
 // them share its persistent launch, and a second launch of few workgroups at
@@ -360,7 +375,7 @@ struct TermLayout {
 // the line [5, 31] 1.0e-6 / 1.5e-6 and 6.7e-7 / 7.4e-7, [0, 20] 7.8e-7 / 9.9e-7 and
 // 5.4e-7 / 7.1e-7, [-3, 3] 6.8e-7 / 1.1e-6 and 5.3e-7 / 7.7e-7.
 // (The fold table, its size and its launches are the same either way.)
-inline bool mf_terms_path(const TermLayout &L, long long n, bool fp32) {
+inline bool mf_terms_path(const TermLayout &L, long long n, int K, bool fp32) {
     if (L.mf_terms == 0) return false;
     const int mt = L.mf_terms / 10, t = L.mf_terms % 10;
     const int shape = mt == 1 && t == 1 ? 0 : mt <= 2 && t == 1 ? 1 : mt <= 2 ? 2 : 3;
@@ -370,7 +385,8 @@ inline bool mf_terms_path(const TermLayout &L, long long n, bool fp32) {
     if (!fp32) {
         const int steps = (L.n_max > -L.n_min ? L.n_max : -L.n_min) / 2 + 1;
         const int cells = 8 * (shape == 0 ? 1 : shape == 3 ? 3 : 2) * 4 * steps;
-        long long least = n >= 262144 ? 74 + cells / 2 : 150 + cells * 11 / 20;
+        long long least = n < 262144 ? 150 + cells * 11 / 20
+                                     : 74 + cells * (nk > 1 ? 6 : 5) / 10 + (long long)cells * K / 4000;
         const long long brief = n >= 16384 ? 120 : 72;
         if (n < 65536 && least > brief) least = brief;
         return L.n_terms >= least * nk;
@@ -381,10 +397,10 @@ inline bool mf_terms_path(const TermLayout &L, long long n, bool fp32) {
     // over the samples (terms x 10^6 samples)
     static const int kRate[4] = {37, 44, 92, 94}, kStage[4] = {24, 31, 50, 60};
     // (196608 samples: 1.5 rounds of every wave of 256 workgroups)
-    const int brief = (nk > 1 && n < 196608 ? kShortKerr : kShort)[shape];
+    const int brief = nk > 1 && n < 196608 ? kShortKerr[shape] + K / 30 : kShort[shape];
     long long least = brief;
     if (n >= 196608)
-        least = std::min<long long>(brief, kRate[shape] + (nk > 1 ? 16 : 0) +
+        least = std::min<long long>(brief, kRate[shape] + K / 60 + (nk > 1 ? 16 : 0) +
                                                kStage[shape] * 1000000ll / n);
     return L.n_terms >= least * nk;
 }

@@ -3034,7 +3034,7 @@ __device__ void mf_range(const SumJob &jb, long long lo, long long hi, float4 *l
 // prepare_kernel (rows of consecutive m): short mode lists, whose operand
 // table would not fit the space of their fold table, and generic Kerr, one
 // polar index k after the other.  Each workgroup forms the operand values of
-// its intervals itself (5 to 8 us per interval and k, all latency).  In Kerr
+// its intervals itself (latency; what a visit costs is stated at mf_terms_path).  In Kerr
 // the waves' running sums of 12 rounds at a time stay in LDS, so a (interval,
 // k) is staged once per 6144 samples.  Measured against the vector kernel:
 // 225 terms on 1.26 million samples 86 -> 46 us (shape 2 x 2), 34587 Kerr
