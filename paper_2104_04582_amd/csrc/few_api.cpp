@@ -1521,9 +1521,9 @@ int launch_batch(few_plan p, Batch *b, hipStream_t s, unsigned *counter) {
                         Tiling{1, 0});
         if (set > 0) {
             sj[k].sample_base = mf_total[set];
-            const long long ns = r->r.n_samples;
-            mf_total[set] += set > 1 ? ns : (ns + mf_gap(ns, !fp32) * (r->h.K - 1)) *
-                                                mf_terms_cost(sj[k].mf_terms, sj[k].mf_ns, !fp32);
+            const long long gap = mf_gap(r->r.n_samples, set == 1 && fp32 ? kMfGapTerms : kMfGap);
+            mf_total[set] += (r->r.n_samples + gap * (r->h.K - 1)) *
+                             (set == 1 ? mf_terms_cost(sj[k].mf_terms, sj[k].mf_ns, !fp32) : 1);
         } else {
             sj[k].wave_base = (int)waves;
             waves += tile_upper_bound(r->r.n_samples, r->h.K, tile);

@@ -123,7 +123,10 @@ struct MfInfo {
     unsigned short top[kMfMT * 4 * kMfT];   // [mt][p][t]
 };
 static_assert(sizeof(MfInfo) == 96, "4-byte granularity, no padding");
-constexpr int kMfMinTerms = 480;            // below this the vector kernel is cheaper
+// From this many folded terms on a binary32 list is folded straight into the
+// operand table, whatever its length; shorter lists go through the fold table, and
+// mf_terms_path decides.
+constexpr int kMfMinTerms = 480;
 
 // ---------------------------------------------------------------------------
 // Device-side job descriptors.  Pointers are device addresses in the plan
@@ -413,17 +416,20 @@ __host__ __device__ inline int mf_terms_cost(int shape, int ns, bool f64) {
     return f64 ? 8 + tiles * ns : tiles == 1 ? 5 : tiles == 3 ? 10 : t == 1 ? 6 : 8;
 }
 
-// The gap of an interval in such a sum's split between workgroups: the samples
-// that forming its operands (and the round that its last samples leave part
-// empty) is worth, at most two shares' samples.  Without it a workgroup at the
-// dense end of a grid visits several intervals while others sum, and a short
-// request's shares run across interval starts, two visits in place of one:
-// binary64, 1281 terms, 262144 samples on 1000 knots 642 -> 321 us, 5 x 171 Kerr terms,
-// 8640 samples on 60 knots 131 -> 73 us, binary32, 5 x 187, 100000 samples on 900 knots
-// 326 -> 171 us.  Twice these gaps gave the same or less (1000 knots, binary64,
-// 400000 samples: 0.89 of the time without gaps against 0.79).
-__host__ __device__ inline long long mf_gap(long long n, bool f64) {
-    const long long most = f64 ? 512 : 1024, two = n / 128;
+// The gap of an interval in a matrix-core sum's split between workgroups: the
+// samples that its operands (formed, or staged from the operand table, and the
+// round that its last samples leave part empty) are worth, at most two shares'
+// samples.  Without it a workgroup at the dense end of a grid visits several
+// intervals while others sum, and a short request's shares run across interval
+// starts, two visits in place of one: binary64, 1281 terms, 262144 samples on 1000
+// knots 642 -> 321 us, 5 x 171 Kerr terms, 8640 samples on 60 knots 131 -> 73 us, binary32
+// from the fold table, 5 x 187, 100000 samples on 900 knots 326 -> 171 us, from operand
+// tables, 1281 terms, 8640 samples 27.5 -> 22.9 us and 400000 on 1000 knots 116 -> 108 us.
+// Twice these gaps gave the same or less (1000 knots, binary64, 400000 samples:
+// 0.89 of the time without gaps against 0.79), half of them less.
+constexpr int kMfGapTerms = 1024, kMfGap = 512;     // binary32 from the fold table, others
+__host__ __device__ inline long long mf_gap(long long n, int most) {
+    const long long two = n / 128;
     return two < most ? two : most;
 }
 

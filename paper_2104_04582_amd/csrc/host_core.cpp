@@ -53,13 +53,13 @@ void free_term_layout(TermLayout *t) {
     *t = TermLayout{};
 }
 
+// k of a segment's m + 256 k (|m| <= kMaxL)
+static int seg_polar(int mk) { return (mk + 128 + 256 * 1024) / 256 - 1024; }
+
 // Eq. (9): every listed mode (l, m >= 0, k, n) contributes A Y_lm to the
 // signed term (m, k, n); for m > 0 its mirror contributes
 // (-1)^{l+k} conj(A) Y_{l,-m} to the term (-m, -k, -n).  For fixed viewing
 // angles the l-sum then folds into one complex cubic per signed (m, k, n).
-// k of a segment's m + 256 k (|m| <= kMaxL)
-static int seg_polar(int mk) { return (mk + 128 + 256 * 1024) / 256 - 1024; }
-
 // width 3: modes (l, m, n) with k = 0 (Schwarzschild); width 4: (l, m, k, n).
 int build_term_layout(int M, const int32_t *modes, int width, int max_gap, TermLayout *out) {
     *out = TermLayout{};

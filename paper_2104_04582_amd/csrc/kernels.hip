@@ -26,7 +26,8 @@
 //                  of the interval (three); rows combined with e^{-i m Phi_phi}.
 //  sum_mfma_terms_kernel  the same from prepare_kernel's terms (middle lists,
 //                  generic Kerr), operands formed by each workgroup.
-//  sum_mfma_f64_kernel  the same in binary64 (v_mfma_f64_16x16x4_f64).
+//  sum_mfma_f64_kernel  the same in binary64 (v_mfma_f64_16x16x4_f64; small
+//                  curvature from fp16 hi/lo parts with fp32 accumulation).
 //  sum_wg_kernel   binary32 on the vector units (few terms, or few samples):
 //                  one workgroup of 4 waves = one
 //                  tile of consecutive samples inside one knot interval; the
@@ -38,7 +39,7 @@
 //                  m or k), Kahan-compensated within four term groups whose
 //                  values are added in order; the end of a launch uses
 //                  term-split tiles (the four waves take one group each).
-//  sum_kernel      binary64 on the vector units (sparse lists): one wave = one
+//  sum_kernel      binary64 on the vector units (sparse lists, short sums): one wave = one
 //                  tile; phases in double-double; coefficients read by scalar
 //                  loads into SGPR operands.
 //  select_kernel   the mode selector of Sec. III D: per knot a radix select
@@ -1850,8 +1851,8 @@ __global__ __launch_bounds__(256) void sum_wg_persistent_kernel(const SumJob *jo
 // coefficient matrix (rows: the real and imaginary part of each signed m;
 // columns: (n, re/im)) with the matrix of harmonics (Re f^|n|, Im f^|n|) over
 // the samples, f = e^{-i Phi_r}, on fp16 hi/lo operands with fp32
-// accumulation; the sum over p is a Horner recurrence in u on the
-// accumulators, and the rows are combined with e^{-i m Phi_phi}.
+// accumulation; the sum over p is a Horner recurrence in v = 2 u - 1 (or one
+// step within a block of samples) on the accumulators, and the rows are combined with e^{-i m Phi_phi}.
 // ===========================================================================
 typedef _Float16 mf_half8 __attribute__((ext_vector_type(8)));
 typedef float mf_float4 __attribute__((ext_vector_type(4)));
@@ -2243,8 +2244,13 @@ __device__ __forceinline__ double uniform_f64(double v) { return lane_value(v, 0
 // approximations), which is off by at most (|b_2| + 3 |b_3|) w^2 / 2 + |b_3|
 // w^3 / 4.  Blocks are as long as keeps that below kMfBlockRest = 2^-25 S and
 // |T_1| below kMfBlockSlope = 2^-11 S in every fragment; T_1 then needs one
-// product (what is left out stays below 2^-23 S |s|), so a block takes 4
-// products and one Horner step in place of 8 to 12 and 3.  The launch is
+// product, so a block takes 4 products and one Horner step in place of 8 to 12
+// and 3.  (Its rounding to fp16 and the missing lo part of the columns are
+// 2^-23 S each, 2^-22 S |s| together.  Neither this nor the products left out of
+// static tables shows in the result, whose error is that of the binary32
+// harmonics: over 96 full lists, smooth, decaying and noisy, of 0.4 and 3 million
+// samples, the rms and the largest error are within 1 % of those with static
+// tables and all three products, and of those with blocks a fourth as wide.)  The launch is
 // limited by power, which goes with the products (one set of them cost 28.5 us
 // on 12.6 million samples, everything else 270 us).  The 72 registers of
 // T_0 (hi, lo) and T_1 stay in the wave, which forms them from the interval's
@@ -2278,6 +2284,31 @@ __device__ __forceinline__ void mf_stage(const float *tab, float4 *lds) {
         lds[(v & ~127) | (v & 1) << 6 | ((v >> 1) & 63)] = ((const float4 *)tab)[v];
 }
 
+// fp16 parts of a lane's 8 operand values of one fragment, stored as in a static
+// table (d: the fragment's hi part of this lane).
+__device__ __forceinline__ void mf_store_parts(float4 a, float4 b, float4 *d) {
+    unsigned hi[4], lo[4];
+    split_pair(a.x, a.y, hi[0], lo[0]);
+    split_pair(a.z, a.w, hi[1], lo[1]);
+    split_pair(b.x, b.y, hi[2], lo[2]);
+    split_pair(b.z, b.w, hi[3], lo[3]);
+    ((uint4 *)d)[0] = make_uint4(hi[0], hi[1], hi[2], hi[3]);
+    ((uint4 *)d)[64] = make_uint4(lo[0], lo[1], lo[2], lo[3]);
+}
+
+// The operand values of fold_pack staged as a static table.
+__device__ __forceinline__ void mf_stage_static(const float *tab, float4 *lds) {
+    int tid = threadIdx.x;
+    asm volatile("" : "+v"(tid));
+#pragma unroll
+    for (int it = 0; it < (int)(kMfIntervalFloats / 8); it += 64 * kMfWaves) {
+        const int x = it + tid;
+        const float4 *v = (const float4 *)tab + 2 * x;
+        mf_store_parts(v[0], v[1], lds + (x >> 6) * 128 + (x & 63));
+    }
+}
+static_assert(kMfIntervalFloats / 8 % (64 * kMfWaves) == 0, "whole turns");
+
 // Staged values -> static table, in place (each lane rewrites what it read).
 template <int MT, int T>
 __device__ __forceinline__ void mf_convert(float4 *lds) {
@@ -2286,13 +2317,7 @@ __device__ __forceinline__ void mf_convert(float4 *lds) {
     for (int it = tid; it < MT * 4 * T * 64; it += 64 * kMfWaves) {
         float4 *d = lds + (it >> 6) * 128 + (it & 63);
         const float4 a = d[0], b = d[64];
-        unsigned hi[4], lo[4];
-        split_pair(a.x, a.y, hi[0], lo[0]);
-        split_pair(a.z, a.w, hi[1], lo[1]);
-        split_pair(b.x, b.y, hi[2], lo[2]);
-        split_pair(b.z, b.w, hi[3], lo[3]);
-        ((uint4 *)d)[0] = make_uint4(hi[0], hi[1], hi[2], hi[3]);
-        ((uint4 *)d)[64] = make_uint4(lo[0], lo[1], lo[2], lo[3]);
+        mf_store_parts(a, b, d);
     }
 }
 
@@ -2879,29 +2904,6 @@ __device__ __forceinline__ double2 mf_round_block(const SumJob &jb, int iv, doub
     return mf_finish<INNER, KERR>(jb, qr, qi, own, sa, jo, jo < e, dv, po);
 }
 
-// Interval of sample j: the largest i <= K - 2 with starts[i] <= j.
-__device__ __forceinline__ int mf_interval_of(const SumJob &jb, long long j) {
-    const FEW_AS4 long long *st = cptr(jb.starts);
-    int iv = 0, top = jb.K - 2;
-    while (iv < top) {
-        const int mid = (iv + top + 1) >> 1;
-        if (st[mid] <= j) iv = mid; else top = mid - 1;
-    }
-    return iv;
-}
-
-// Share boundary j moved up to the grid of rounds (64 samples from the first
-// sample of its interval), so that every round belongs to one workgroup and a
-// sample's block does not depend on how the samples are shared out.
-__device__ __forceinline__ long long mf_align(const SumJob &jb, long long j) {
-    if (j <= 0) return 0;
-    if (j >= jb.n) return jb.n;
-    const FEW_AS4 long long *st = cptr(jb.starts);
-    const int iv = mf_interval_of(jb, j);
-    const long long a = st[iv];
-    return min((long long)st[iv + 1], a + (j - a + kMfSPW - 1) / kMfSPW * kMfSPW);
-}
-
 // The constants of interval iv and which products it takes, from mx(f), the
 // largest |scaled value| of fragment f = (mt 4 + p) T + t (every wave forms
 // the same).
@@ -2968,17 +2970,15 @@ __device__ __forceinline__ void mf_blocks(const SumJob &jb, int iv, const MfInte
     }
 }
 
-// Samples [lo, hi) of one job (matrix-core path), interval by interval.  Every
+// Samples [lo, hi) of one job (matrix-core path), from interval `first` on.  Every
 // lane of the workgroup runs the same loops over intervals (lo, hi uniform).
 // INNER: each lane's binary64 sums accumulate in its LDS slot
 // iacc[threadIdx.x] (zeroed by the caller), which keeps them out of the
 // registers of the product loop.
 template <bool INNER, bool CONSEC>
-__device__ void mf_range(const SumJob &jb, long long lo, long long hi, float4 *lds,
+__device__ void mf_range(const SumJob &jb, long long lo, long long hi, int first, float4 *lds,
                          float *msc, int *mm, double2 *iacc) {
     constexpr int MT = kMfMT, T = kMfT;
-    lo = mf_align(jb, lo);
-    hi = mf_align(jb, hi);
     if (lo >= hi) return;
     // the waves' sample areas follow the tables in LDS
     const int wave = threadIdx.x / kWave;
@@ -3000,7 +3000,7 @@ __device__ void mf_range(const SumJob &jb, long long lo, long long hi, float4 *l
             iacc[threadIdx.x] = a;
         }
     };
-    for (int iv = mf_interval_of(jb, lo); iv <= jb.K - 2 && lo < hi; ++iv) {
+    for (int iv = first; iv <= jb.K - 2 && lo < hi; ++iv) {
         const long long a = st[iv], end = st[iv + 1], e = min(hi, end);
         if (e <= lo) continue;
         const unsigned short *top = jb.minfo[iv].top;
@@ -3008,11 +3008,13 @@ __device__ void mf_range(const SumJob &jb, long long lo, long long hi, float4 *l
             jb, iv, [&](int f) { return __uint_as_float((unsigned)top[f] << 16); });
         __syncthreads();                            // previous interval no longer read
         if ((int)threadIdx.x < kMfRows / 2) msc[threadIdx.x] = jb.minfo[iv].scale[threadIdx.x];
-        mf_stage(jb.mtab + (size_t)iv * kMfIntervalFloats, lds);
+        const float *tab = jb.mtab + (size_t)iv * kMfIntervalFloats;
+        if (I.block == 0)
+            mf_stage_static(tab, lds);
+        else
+            mf_stage(tab, lds);
         __syncthreads();
         if (I.block == 0) {
-            mf_convert<MT, T>(lds);
-            __syncthreads();
             // (a wave whose samples of a round all lie past the end skips it)
             for (long long base = lo + (long long)wave * kMfSPW; base < e; base += kMfRound)
                 add(mf_round_static<INNER, CONSEC, MT, T, false>(jb, iv, I, base, e, lds, msc, mm,
@@ -3041,10 +3043,8 @@ __device__ void mf_range(const SumJob &jb, long long lo, long long hi, float4 *l
 // modes (9 x 1281 terms) on 3.16 million 7230 -> 1000 us (3 x 2); the error
 // against binary64 falls too, 8.1e-7 -> 2.6e-7 and 1.6e-6 -> 4.6e-7.
 template <bool INNER, int MT, int T, bool KERR>
-__device__ void mf_range_terms(const SumJob &jb, long long lo, long long hi, float4 *lds,
-                               double2 *iacc) {
-    lo = mf_align(jb, lo);
-    hi = mf_align(jb, hi);
+__device__ void mf_range_terms(const SumJob &jb, long long lo, long long hi, int first,
+                               float4 *lds, double2 *iacc) {
     if (lo >= hi) return;
     __shared__ MfTerms<MT, T> M;
     const int wave = threadIdx.x / kWave;
@@ -3075,7 +3075,7 @@ __device__ void mf_range_terms(const SumJob &jb, long long lo, long long hi, flo
         }
         return I;
     };
-    for (int iv = mf_interval_of(jb, lo); iv <= jb.K - 2 && lo < hi; ++iv) {
+    for (int iv = first; iv <= jb.K - 2 && lo < hi; ++iv) {
         const long long a = st[iv], end = st[iv + 1], e = min(hi, end);
         if (e <= lo) continue;
         // the waves take equal contiguous runs of rounds
@@ -3147,41 +3147,51 @@ __device__ __forceinline__ void mf_share_w(const float *wl, long long total, lon
     *hi = a + (e - a) * (j + 1) / S;
 }
 
-// Sums from the fold table are shared out in units: an interval counts its
-// samples and a gap before them (mf_gap), so that a workgroup's share holds
-// fewer samples where it has more intervals to form operands for.  Unit u -> sample.
-__device__ __forceinline__ long long mf_unit_sample(const SumJob &jb, long long u, long long gap) {
+// A job is shared out in units: an interval counts its samples and a gap before
+// them (mf_gap), so that a share holds fewer samples where it has more
+// intervals to form operands for.  Units [u0, u1) -> samples [lo, hi), both moved
+// up to the grid of rounds (64 samples from the first one of their interval), so
+// that every round belongs to one workgroup and a sample's block does not depend
+// on how the samples are shared out; iv: the interval of lo (or the one before
+// it).  Both searches run in step: a chain of scalar loads is what a short
+// launch waits for.
+__device__ __forceinline__ void mf_units(const SumJob &jb, long long u0, long long u1,
+                                         long long gap, long long *lo, long long *hi, int *iv) {
     const FEW_AS4 long long *st = cptr(jb.starts);
-    int iv = 0, top = jb.K - 2;
-    while (iv < top) {
-        const int mid = (iv + top + 1) >> 1;
-        if (st[mid] + gap * mid <= u) iv = mid; else top = mid - 1;
+    int a0 = 0, a1 = 0;
+    for (int step = 512; step > 0; step >>= 1) {    // (K <= 1024)
+        const int q0 = min(a0 + step, jb.K - 2), q1 = min(a1 + step, jb.K - 2);
+        if (st[q0] + gap * q0 <= u0) a0 = q0;
+        if (st[q1] + gap * q1 <= u1) a1 = q1;
     }
-    const long long a = st[iv], r = u - a - gap * iv;
-    return r <= gap ? a : min(jb.n, a + r - gap);
+    auto sample = [&](int i, long long u) {
+        const long long a = st[i], r = max(u - gap * (i + 1) - a, 0ll);
+        return min((long long)st[i + 1], a + (r + kMfSPW - 1) / kMfSPW * kMfSPW);
+    };
+    *lo = sample(a0, u0);
+    *hi = sample(a1, u1);
+    *iv = a0;
 }
 
 // A single-request launch: this workgroup's share of the samples through
-// range(lo, hi), its time reported, and (INNER) its sums of iacc in partial.
-// gap: of mf_unit_sample.
+// range(lo, hi, first interval), its time reported, and (INNER) its sums of iacc in
+// partial.  gap: of mf_units.
 template <bool INNER, typename Range>
 __device__ __forceinline__ void mf_single(const SumJob &jb, double2 *iacc, long long gap,
                                           Range range) {
     if constexpr (INNER) iacc[threadIdx.x] = make_double2(0.0, 0.0);
-    long long lo, hi;
+    long long lo, hi, u0, u1;
+    int iv;
     // the inner-product launch keeps the equal split (its binary64 sums
     // then do not depend on the weights)
     const unsigned long long t0 = wall_clock64();
     const long long units = jb.n + gap * (jb.K - 1);
     if (!INNER && mf_balanced(jb))
-        mf_share_w(jb.bw, units, &lo, &hi);
+        mf_share_w(jb.bw, units, &u0, &u1);
     else
-        mf_share(units, &lo, &hi);
-    if (gap > 0) {
-        lo = mf_unit_sample(jb, lo, gap);
-        hi = mf_unit_sample(jb, hi, gap);
-    }
-    range(lo, hi);
+        mf_share(units, &u0, &u1);
+    mf_units(jb, u0, u1, gap, &lo, &hi, &iv);
+    range(lo, hi, iv);
     if (!INNER && jb.btime != nullptr && (int)blockIdx.x < kMfBalanceWG) {
         __syncthreads();
         if (threadIdx.x == 0) {
@@ -3205,10 +3215,11 @@ __device__ __forceinline__ void mf_single(const SumJob &jb, double2 *iacc, long 
     }
 }
 
-// A batched launch: the jobs' units (samples and, with GAPS, gaps), cost(job) each,
-// laid end to end (job j from sample_base_j), split into equal shares; range(job, a, e).
-template <bool GAPS, typename Cost, typename Range>
-__device__ __forceinline__ void mf_batch(const SumJob *jobs, int n_jobs, long long total,
+// A batched launch: the jobs' units, cost(job) each, laid end to end (job j from
+// sample_base_j), split into equal shares; range(job, lo, hi, first interval).
+// most: of the gaps.
+template <typename Cost, typename Range>
+__device__ __forceinline__ void mf_batch(const SumJob *jobs, int n_jobs, long long total, int most,
                                          Cost cost, Range range) {
     long long lo, hi;
     mf_share(total, &lo, &hi);
@@ -3221,17 +3232,15 @@ __device__ __forceinline__ void mf_batch(const SumJob *jobs, int n_jobs, long lo
         const long long b0 = *cptr(&jobs[j].sample_base);
         if (b0 >= hi) break;
         const SumJob jb = load_uniform(jobs + j);
-        // (a share's end and the next one's start round to the same sample)
+        const long long gap = mf_gap(jb.n, most), units = jb.n + gap * (jb.K - 1);
+        // (a share's end and the next one's start round to the same unit)
         const long long c = cost(jb);
-        const long long gap = GAPS ? mf_gap(jb.n, jb.mf_f64) : 0;
-        const long long units = jb.n + gap * (jb.K - 1);
-        long long a = (max(lo, b0) - b0 + c - 1) / c;
-        long long e = (min(hi, b0 + units * c) - b0 + c - 1) / c;
-        if (GAPS) {
-            a = mf_unit_sample(jb, a, gap);
-            e = mf_unit_sample(jb, e, gap);
-        }
-        if (a < e) range(jb, a, e);
+        const long long u0 = (max(lo, b0) - b0 + c - 1) / c;
+        const long long u1 = (min(hi, b0 + units * c) - b0 + c - 1) / c;
+        long long a, e;
+        int iv;
+        mf_units(jb, u0, u1, gap, &a, &e, &iv);
+        if (a < e) range(jb, a, e, iv);
     }
 }
 
@@ -3781,13 +3790,11 @@ __device__ __forceinline__ double2 mf64_round(const SumJob &jb, int iv, double t
 
 constexpr int kMfKerrRounds64 = 3;
 
-// Samples [lo, hi) of one job, interval by interval (mf_range_terms in
+// Samples [lo, hi) of one job, from interval `first` on (mf_range_terms in
 // binary64).
 template <bool INNER, int MT, int T, bool KERR>
-__device__ void mf_range_f64(const SumJob &jb, long long lo, long long hi, double *base,
-                             double2 *iacc) {
-    lo = mf_align(jb, lo);
-    hi = mf_align(jb, hi);
+__device__ void mf_range_f64(const SumJob &jb, long long lo, long long hi, int first,
+                             double *base, double2 *iacc) {
     if (lo >= hi) return;
     __shared__ MfTerms64<MT, T> M;
     const int wave = threadIdx.x / kWave, ns = jb.mf_ns;
@@ -3795,7 +3802,7 @@ __device__ void mf_range_f64(const SumJob &jb, long long lo, long long hi, doubl
     double2 *hp = (double2 *)((char *)rest + mf64_rest_bytes(MT, T)) + wave * kMfKerrRounds64 * kMfSPW;
     const FEW_AS4 long long *st = cptr(jb.starts);
     for (int x = threadIdx.x; x < 8 * MT * 32 * T; x += 64 * kMfWaves) (&M.idx[0][0])[x] = -1;
-    for (int iv = mf_interval_of(jb, lo); iv <= jb.K - 2 && lo < hi; ++iv) {
+    for (int iv = first; iv <= jb.K - 2 && lo < hi; ++iv) {
         const long long a = st[iv], end = st[iv + 1], e = min(hi, end);
         if (e <= lo) continue;
         const double ti = uniform_f64(jb.t[iv]);
@@ -3846,8 +3853,8 @@ __global__ __launch_bounds__(64 * kMfWaves) void sum_mfma_kernel(SumJob jb) {
     __shared__ float msc[kMfRows / 2];
     __shared__ int mm[kMfRows];
     __shared__ double2 iacc[INNER ? 64 * kMfWaves : 1];
-    mf_single<INNER>(jb, iacc, 0, [&](long long lo, long long hi) {
-        mf_range<INNER, CONSEC>(jb, lo, hi, mf_lds, msc, mm, iacc);
+    mf_single<INNER>(jb, iacc, mf_gap(jb.n, kMfGap), [&](long long lo, long long hi, int iv) {
+        mf_range<INNER, CONSEC>(jb, lo, hi, iv, mf_lds, msc, mm, iacc);
     });
 }
 
@@ -3858,8 +3865,8 @@ __global__ __launch_bounds__(64 * kMfWaves) void sum_mfma_batch_kernel(const Sum
     __shared__ float msc[kMfRows / 2];
     __shared__ int mm[kMfRows];
     auto one = [](const SumJob &) { return 1ll; };
-    mf_batch<false>(jobs, n_jobs, total, one, [&](const SumJob &jb, long long a, long long e) {
-        mf_range<false, CONSEC>(jb, a, e, mf_lds, msc, mm, nullptr);
+    mf_batch(jobs, n_jobs, total, kMfGap, one, [&](const SumJob &jb, long long a, long long e, int iv) {
+        mf_range<false, CONSEC>(jb, a, e, iv, mf_lds, msc, mm, nullptr);
     });
 }
 
@@ -3867,8 +3874,8 @@ template <bool INNER, int MT, int T, bool KERR>
 __global__ __launch_bounds__(64 * kMfWaves) void sum_mfma_terms_kernel(SumJob jb) {
     extern __shared__ float4 mf_lds[];
     __shared__ double2 iacc[INNER ? 64 * kMfWaves : 1];
-    mf_single<INNER>(jb, iacc, mf_gap(jb.n, false), [&](long long lo, long long hi) {
-        mf_range_terms<INNER, MT, T, KERR>(jb, lo, hi, mf_lds, iacc);
+    mf_single<INNER>(jb, iacc, mf_gap(jb.n, kMfGapTerms), [&](long long lo, long long hi, int iv) {
+        mf_range_terms<INNER, MT, T, KERR>(jb, lo, hi, iv, mf_lds, iacc);
     });
 }
 
@@ -3876,8 +3883,8 @@ template <bool INNER, int MT, int T, bool KERR>
 __global__ __launch_bounds__(64 * kMfWaves) void sum_mfma_f64_kernel(SumJob jb) {
     extern __shared__ float4 mf_lds[];
     __shared__ double2 iacc[INNER ? 64 * kMfWaves : 1];
-    mf_single<INNER>(jb, iacc, mf_gap(jb.n, true), [&](long long lo, long long hi) {
-        mf_range_f64<INNER, MT, T, KERR>(jb, lo, hi, (double *)mf_lds, iacc);
+    mf_single<INNER>(jb, iacc, mf_gap(jb.n, kMfGap), [&](long long lo, long long hi, int iv) {
+        mf_range_f64<INNER, MT, T, KERR>(jb, lo, hi, iv, (double *)mf_lds, iacc);
     });
 }
 
@@ -3906,13 +3913,14 @@ __global__ __launch_bounds__(64 * kMfWaves) void sum_mfma_terms_batch_kernel(con
     auto cost = [](const SumJob &jb) {
         return (long long)mf_terms_cost(jb.mf_terms, jb.mf_ns, F64);
     };
-    mf_batch<true>(jobs, n_jobs, total, cost, [&](const SumJob &jb, long long a, long long e) {
+    mf_batch(jobs, n_jobs, total, F64 ? kMfGap : kMfGapTerms, cost,
+             [&](const SumJob &jb, long long a, long long e, int iv) {
         auto run = [&](auto MT, auto T) {
             constexpr int mt = decltype(MT)::value, t = decltype(T)::value;
             if constexpr (F64)
-                mf_range_f64<false, mt, t, false>(jb, a, e, (double *)mf_lds, nullptr);
+                mf_range_f64<false, mt, t, false>(jb, a, e, iv, (double *)mf_lds, nullptr);
             else
-                mf_range_terms<false, mt, t, false>(jb, a, e, mf_lds, nullptr);
+                mf_range_terms<false, mt, t, false>(jb, a, e, iv, mf_lds, nullptr);
         };
         mf_with_shape(jb.mf_terms / 10, jb.mf_terms % 10, run);
     });

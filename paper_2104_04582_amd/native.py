@@ -193,8 +193,8 @@ class Plan:
     timing: False, True (HIP events around every launch, FEW_FLAG_TIMING),
     "sum" (around summation launches only, FEW_FLAG_TIMING_SUM) or "sum_sparse"
     (around every 8th summation launch, FEW_FLAG_TIMING_SUM | _SPARSE).
-    vector_only: mixed precision without the matrix-core summation
-    (FEW_FLAG_VECTOR_ONLY).
+    vector_only: sums on the vector units only (FEW_FLAG_VECTOR_ONLY), in binary64
+    every step in binary64.
     select_sorted: the mode selector sorts every knot (FEW_FLAG_SELECT_SORTED)."""
 
     def __init__(self, device: int = 0, precision: str = "fp64", stream: Optional[int] = None,

@@ -56,7 +56,13 @@ LONG = [("fp64", dict(seed=1, l_max=7, n_max=31, n=262_144, K=1000)),
         ("mixed", dict(seed=4, l_max=3, n_max=31, n=262_144, K=1000)),
         ("mixed", dict(seed=5, l_max=6, n_max=16, n=300_007, K=700, grid="ends")),
         ("mixed", dict(seed=6, l_max=5, n_max=15, n=900_001, K=513, grid="random", t0=0.1)),
-        ("mixed", dict(seed=7, l_max=8, n_max=12, n=262_144, K=5))]
+        ("mixed", dict(seed=7, l_max=8, n_max=12, n=262_144, K=5)),
+        # operand tables (480 terms and more), whatever the length
+        ("mixed", dict(seed=8, l_max=10, n_max=30, n=8_640, K=40)),
+        ("mixed", dict(seed=9, l_max=7, n_max=31, n=129, K=300, grid="random")),
+        ("mixed", dict(seed=10, l_max=6, n_max=31, n=300_000, K=1000, grid="ends", t0=0.1)),
+        ("mixed", dict(seed=11, l_max=8, n_max=20, n=1, K=4)),
+        ("mixed", dict(seed=12, l_max=9, n_max=25, n=100_000, K=150))]
 KERR = [(p, dict(seed=20 + i, l_max=5, n_max=15, n=n, K=K, k_max=1, grid=grid))
         for p in ("fp64", "mixed")
         for i, (n, K, grid) in enumerate(((1, 5, "log"), (127, 40, "log"), (128, 300, "random"),
