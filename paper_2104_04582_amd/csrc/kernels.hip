@@ -3261,9 +3261,8 @@ __device__ __forceinline__ void mf_batch(const SumJob *jobs, int n_jobs, long lo
 // T_0 and T_1 formed in binary64 from the staged b_p for each use (6 operations of
 // 4 cycles against 4 or 2 products of 64).  The rest is small: |d| <= w, half the
 // block's width in v.  Where (M_2 + 4 M_3) w^2 <= 2^-30 M_0 (M_p the largest |b_p| of the
-// interval, M_0 of p <= 1) it is summed from fp16 hi + lo operands (22 bits, b_2 and
-// b_3 each in their own scale) with binary32 harmonics and accumulation, at 1/16 of
-// the binary64 products' cost: 4 binary64 operations per term in all.  The
+// interval, M_0 of p <= 1) it is summed from fp16 hi + lo operands (22 bits) with
+// binary32 harmonics and accumulation, at 1/16 of the binary64 products' cost: 4 binary64 operations per term in all.  The
 // harmonics f^a and E^row are binary32 power chains of up to 31 and 24 steps, so
 // a term's rest is good to 2^-19 at worst and adds up to 2^-49 M_0; the vector kernel's
 // Horner recurrence rounds at 2^-53 of its running sum once per term it walks.
@@ -3284,8 +3283,7 @@ template <int MT, int T>
 struct MfTerms64 {
     int idx[8 * MT][32 * T];            // n + 16 T; -1: no term
     unsigned m01[4 * MT], m2[4 * MT], m3[4 * MT];   // largest |b_p| per row pair (binary32 bits)
-    float un[4 * MT];                   // 2^E of the fp16 values b_2 (E that of b_2, b_3)
-    float rat[4 * MT];                  // 2^E of b_3 over it
+    float un[4 * MT];                   // 2^E of the fp16 values
 };
 
 // Cubic in u -> cubic in v = 2 u - 1.
@@ -3301,14 +3299,50 @@ __device__ __forceinline__ void mf_recentre(double a0, double a1, double a2, dou
 static constexpr size_t mf64_base_bytes(int MT, int ns) { return (size_t)MT * ns * 2048; }
 static constexpr size_t mf64_rest_bytes(int MT, int T) { return (size_t)MT * 2 * T * 2048; }
 
+// How the interval's rounds are summed (every wave forms the same).
+template <int MT, int T>
+__device__ __forceinline__ MfPlan64 mf64_plan(const SumJob &jb, double inv_h2,
+                                              const MfTerms64<MT, T> &M) {
+    unsigned b01 = 0, b2 = 0, b3 = 0;
+#pragma unroll
+    for (int i = 0; i < 4 * MT; ++i) {
+        b01 = max(b01, M.m01[i]);
+        b2 = max(b2, M.m2[i]);
+        b3 = max(b3, M.m3[i]);
+    }
+    const float M0 = uniform_f32(__uint_as_float(b01)), M2 = uniform_f32(__uint_as_float(b2)),
+                M3 = uniform_f32(__uint_as_float(b3));
+    // half width of a block of 32 samples.  Blocks do not end with the interval:
+    // v0 lies up to 1 + w, and |3 v0 + d| = |3 v - 2 d| <= 3 + 2 w for |v| <= 1.  In
+    // an interval of less than 64 samples (w > 1/2) the rest, small there for the
+    // interval's sake alone, would be multiplied up again by d^2 and 3 v0 + d (an
+    // interval of 8 samples: error 9e-13, of 1.5 samples 2e-9): no blocks.
+    const float w = uniform_f32((float)(16.0 * jb.dt * inv_h2));
+    MfPlan64 I{4, 1, true};
+    // (NaN, infinite and tiny values: all in binary64)
+    if (w <= 0.5f && M0 > 1e-30f && M0 < 1e30f && M2 < 1e30f && M3 < 1e30f) {
+        const float lim = 0x1p-30f * M0, q = (M2 + 4.0f * M3) * w * w;
+        if (q <= 4.0f * lim) {
+            I.P = 2;
+            I.nt = q <= lim ? 2 : 1;
+        } else if (M3 * w * w * w <= lim) {
+            I.P = 3;
+        }
+        const float u = I.nt == 2 ? w : 0.5f * w;
+        I.lo3 = !(I.P == 2 && (M2 + 8192.0f * M3) * u * u <= lim);
+    }
+    return I;
+}
+
 // Operand values of interval iv and polar index kp: mf_terms_stage in binary64.
 // Lane 16 k + rho of a product's left operand holds row rho = 4 i + g of (signed m
 // 2 g + i / 2, component i % 2) and column k = 2 (a % 2) + component, so that a
 // result lane (16 g + sample) holds both components of rows 2 g and 2 g + 1, as
 // the fp16 products' does.
 template <int MT, int T>
-__device__ __forceinline__ void mf64_stage(const SumJob &jb, int iv, int kp, int ns,
-                                           MfTerms64<MT, T> &M, double *base, unsigned *rest) {
+__device__ __forceinline__ MfPlan64 mf64_stage(const SumJob &jb, int iv, int kp, int ns,
+                                               double inv_h2, MfTerms64<MT, T> &M, double *base,
+                                               unsigned *rest) {
     int tid = threadIdx.x;
     asm volatile("" : "+v"(tid));       // (addresses formed here, not kept through the rounds)
     const int lane = tid & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(tid / kWave);
@@ -3367,28 +3401,22 @@ __device__ __forceinline__ void mf64_stage(const SumJob &jb, int iv, int kp, int
         }
     }
     __syncthreads();
+    const MfPlan64 I = mf64_plan<MT, T>(jb, inv_h2, M);
 #pragma unroll
     for (int q = 0; q < kTurns; ++q) {
         if (wave + q * kMfWaves >= kTasks) continue;
         const int task = wave + q * kMfWaves, mt = task / (2 * T), ta = task % (2 * T);
         const int r = lane >> 3, a = 8 * ta + (lane & 7), t = ta >> 1;
-        // scales of b_2 (that of the larger of b_2 and b_3) and of b_3 (its own: in
+        // scale of the larger of b_2 and b_3, or of b_3 where it is summed alone (in
         // that of b_2 a b_3 of 2^-7 b_2 keeps only 17 bits, and three powers in
         // binary64 were off by 1.2e-14 of |h| near their limit, now 2.5e-15)
         const float m3 = __uint_as_float(M.m3[4 * mt + (r >> 1)]);
-        const float mx = fmaxf(__uint_as_float(M.m2[4 * mt + (r >> 1)]), m3);
-        int e = 0, e3 = 0;
+        const float mx = I.P == 3 ? m3 : fmaxf(__uint_as_float(M.m2[4 * mt + (r >> 1)]), m3);
+        int e = 0;
         if (mx > 0.0f && mx < INFINITY) frexpf(mx, &e);
-        e = e3 = min(max(e, -126), 127);
-        if (m3 > 0.0f && m3 < INFINITY) {
-            frexpf(m3, &e3);
-            e3 = min(max(e3, -126), e);
-        }
-        const double sc[2] = {ldexp(1.0, -e), ldexp(1.0, -e3)};
-        if ((lane & 15) == 0) {
-            M.un[4 * mt + (r >> 1)] = ldexpf(1.0f, e);
-            M.rat[4 * mt + (r >> 1)] = ldexpf(1.0f, e3 - e);
-        }
+        e = min(max(e, -126), 127);
+        const double sc = ldexp(1.0, -e);
+        if ((lane & 15) == 0) M.un[4 * mt + (r >> 1)] = ldexpf(1.0f, e);
         // columns per power: (Re P + Re Q, Im Q - Im P) of row component 0,
         // (Im P + Im Q, Re P - Re Q) of component 1
         const double2 *P = v[q], *Q = v[q] + 4;
@@ -3413,7 +3441,7 @@ __device__ __forceinline__ void mf64_stage(const SumJob &jb, int iv, int kp, int
 #pragma unroll
             for (int p = 2; p < 4; ++p) {
                 unsigned hi, lo;
-                split_pair((float)(o[c][0][p] * sc[p - 2]), (float)(o[c][1][p] * sc[p - 2]), hi, lo);
+                split_pair((float)(o[c][0][p] * sc), (float)(o[c][1][p] * sc), hi, lo);
                 unsigned *f = rest + (((mt * 2 + p - 2) * T + t) * 128 + 2 * r + c + 16 * g) * 4 + j;
                 f[0] = hi;
                 f[256] = lo;
@@ -3421,40 +3449,6 @@ __device__ __forceinline__ void mf64_stage(const SumJob &jb, int iv, int kp, int
         }
     }
     __syncthreads();
-}
-
-// How the interval's rounds are summed (every wave forms the same).
-template <int MT, int T>
-__device__ __forceinline__ MfPlan64 mf64_plan(const SumJob &jb, double inv_h2,
-                                              const MfTerms64<MT, T> &M) {
-    unsigned b01 = 0, b2 = 0, b3 = 0;
-#pragma unroll
-    for (int i = 0; i < 4 * MT; ++i) {
-        b01 = max(b01, M.m01[i]);
-        b2 = max(b2, M.m2[i]);
-        b3 = max(b3, M.m3[i]);
-    }
-    const float M0 = uniform_f32(__uint_as_float(b01)), M2 = uniform_f32(__uint_as_float(b2)),
-                M3 = uniform_f32(__uint_as_float(b3));
-    // half width of a block of 32 samples.  Blocks do not end with the interval:
-    // v0 lies up to 1 + w, and |3 v0 + d| = |3 v - 2 d| <= 3 + 2 w for |v| <= 1.  In
-    // an interval of less than 64 samples (w > 1/2) the rest, small there for the
-    // interval's sake alone, would be multiplied up again by d^2 and 3 v0 + d (an
-    // interval of 8 samples: error 9e-13, of 1.5 samples 2e-9): no blocks.
-    const float w = uniform_f32((float)(16.0 * jb.dt * inv_h2));
-    MfPlan64 I{4, 1, true};
-    // (NaN, infinite and tiny values: all in binary64)
-    if (w <= 0.5f && M0 > 1e-30f && M0 < 1e30f && M2 < 1e30f && M3 < 1e30f) {
-        const float lim = 0x1p-30f * M0, q = (M2 + 4.0f * M3) * w * w;
-        if (q <= 4.0f * lim) {
-            I.P = 2;
-            I.nt = q <= lim ? 2 : 1;
-        } else if (M3 * w * w * w <= lim) {
-            I.P = 3;
-        }
-        const float u = I.nt == 2 ? w : 0.5f * w;
-        I.lo3 = !(I.P == 2 && (M2 + 8192.0f * M3) * u * u <= lim);
-    }
     return I;
 }
 
@@ -3533,9 +3527,9 @@ __device__ __forceinline__ void mf64_rows(const R (&c)[4][4], R er, R ei, R *yr,
 // The rest of a round, sum of d^(P-2).. b_p f^a over fp16 operands, without its factor
 // d^2 (P = 2) or d^3 (P = 3): this lane's sample.
 template <int MT, int T, int P>
-__device__ __forceinline__ void mf64_rest(const uint4 *rest, const float *un, const float *rat,
-                                          bool lo3, float fr, float fi, float vq, float er,
-                                          float ei, float e8r, float e8i, float *yr, float *yi) {
+__device__ __forceinline__ void mf64_rest(const uint4 *rest, const float *un, bool lo3, float fr,
+                                          float fi, float vq, float er, float ei, float e8r,
+                                          float e8i, float *yr, float *yi) {
     const int lane = threadIdx.x & (kWave - 1), col = lane & 15, g = lane >> 4;
     mf_u4 bh[4][T], bl[4][T];
     float vv[4];
@@ -3558,16 +3552,13 @@ __device__ __forceinline__ void mf64_rest(const uint4 *rest, const float *un, co
         };
 #pragma unroll
         for (int nt = 0; nt < 4; ++nt) s[nt] = mf_float4{0.0f, 0.0f, 0.0f, 0.0f};
-        const float r = rat[4 * mt + g];
 #pragma unroll
         for (int p = 3; p >= P; --p) {
             if (p == 2) {
 #pragma unroll
-                for (int nt = 0; nt < 4; ++nt) {
-                    const float vr = vv[nt] * r;
+                for (int nt = 0; nt < 4; ++nt)
 #pragma unroll
-                    for (int i = 0; i < 4; ++i) s[nt][i] = s[nt][i] * vr;
-                }
+                    for (int i = 0; i < 4; ++i) s[nt][i] = s[nt][i] * vv[nt];
             }
 #pragma unroll
             for (int t = 0; t < T; ++t) {
@@ -3580,7 +3571,7 @@ __device__ __forceinline__ void mf64_rest(const uint4 *rest, const float *un, co
                 prod(ah, bh, t);
             }
         }
-        const float u = P == 2 ? un[4 * mt + g] : un[4 * mt + g] * r;
+        const float u = un[4 * mt + g];
         float c[4][4];
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
@@ -3604,8 +3595,7 @@ template <bool INNER, int MT, int T, bool KERR, int P, int NT>
 __device__ __forceinline__ double2 mf64_round(const SumJob &jb, int iv, double ti, double inv_h2,
                                               bool lo3, long long wbase, long long e, int ns,
                                               const double *base, const uint4 *rest,
-                                              const float *un, const float *rat,
-                                              const MfPolar64 &po) {
+                                              const float *un, const MfPolar64 &po) {
     const int lane = threadIdx.x & (kWave - 1), col = lane & 15, g = lane >> 4;
     const FEW_AS4 double *pc = cptr(jb.pcoef) + (size_t)iv * (KERR ? 24 : 16);
     const long long jo = wbase + lane;
@@ -3668,7 +3658,7 @@ __device__ __forceinline__ double2 mf64_round(const SumJob &jb, int iv, double t
     }
     float yr = 0.0f, yi = 0.0f;
     if constexpr (P < 4)
-        mf64_rest<MT, T, P>(rest, un, rat, lo3, (float)fr, (float)fi, (float)fma(3.0, v0, dl), (float)Er,
+        mf64_rest<MT, T, P>(rest, un, lo3, (float)fr, (float)fi, (float)fma(3.0, v0, dl), (float)Er,
                             (float)Ei, (float)E8r, (float)E8i, &yr, &yi);
     double sr = 0.0, si = 0.0;
 #pragma unroll 1
@@ -3815,15 +3805,14 @@ __device__ void mf_range_f64(const SumJob &jb, long long lo, long long hi, int f
         for (int c = 0; c < most; c += step) {      // uniform per workgroup
             const int ca = min(rb, ra + c), cb = min(rb, ca + step);
             for (int q = KERR ? jb.mf_nk - 1 : 0; q >= 0; --q) {
-                mf64_stage<MT, T>(jb, iv, jb.mf_k0 + q, ns, M, base, rest);
-                const MfPlan64 I = mf64_plan<MT, T>(jb, inv_h2, M);
+                const MfPlan64 I = mf64_stage<MT, T>(jb, iv, jb.mf_k0 + q, ns, inv_h2, M, base, rest);
                 MfPolar64 po{hp, !KERR || q == jb.mf_nk - 1, !KERR || q == 0, jb.mf_k0};
                 auto run = [&](auto P, auto NT) {
                     for (int r = ca; r < cb; ++r) {
                         if constexpr (KERR) po.hp = hp + (r - ca) * kMfSPW;
                         const double2 v = mf64_round<INNER, MT, T, KERR, decltype(P)::value, decltype(NT)::value>(
                             jb, iv, ti, inv_h2, I.lo3, a + (long long)r * kMfSPW, e, ns, base,
-                            (const uint4 *)rest, M.un, M.rat, po);
+                            (const uint4 *)rest, M.un, po);
                         if constexpr (INNER) {
                             double2 s = iacc[threadIdx.x];
                             s.x = s.x + v.x;
