@@ -78,10 +78,18 @@ typedef enum {
 } few_status;
 
 typedef enum {
-    FEW_FP64 = 0,   /* every step in binary64 (phases in double-double) */
+    FEW_FP64 = 0,   /* binary64 (phases in double-double).  Sums on the matrix cores take
+                       the curvature of the amplitudes within a block of 16 or 32
+                       samples from fp16 hi/lo operands with binary32 accumulation
+                       where it is below 2^-30 of the largest coefficient (at most 2^-49
+                       of it per term; the measured error is no larger than that of the
+                       vector units).  FEW_FLAG_VECTOR_ONLY: every step in binary64 */
     FEW_MIXED = 1   /* binary64 spline solve, phases and mod-2pi reduction;
-                       binary32 amplitude evaluation, harmonics and products,
-                       compensated binary32 accumulation; complex64 output */
+                       binary32 amplitude evaluation and harmonics; complex64 output.
+                       Products and sums: on the matrix cores fp16 hi/lo operands
+                       (about 22 bits) with binary32 accumulation, on the vector units
+                       (lists far from n = 0, few terms or samples, FEW_FLAG_VECTOR_ONLY)
+                       binary32 with compensated accumulation */
 } few_precision;
 
 enum {
@@ -209,6 +217,10 @@ int32_t few_spline_coefs(few_spline spline, int32_t which, void *dst);
  * mirror with -2Y_lm(theta, phi), sum over modes and write
  *   out[j] = h(t_j) = h_plus - i h_cross
  * as interleaved complex128 (FEW_FP64) or complex64 (FEW_MIXED) device memory.
+ * The summation kernel follows from the mode list, K and n_samples, and the
+ * matrix cores sum blocks of samples counted from the first one of each
+ * interval: the same sample summed as part of another range agrees to rounding,
+ * not bit for bit.
  * Requires t_0 <= t_start and t_start + (n_samples-1) dt <= t_{K-1}.
  * Enqueued on the plan stream; returns before the kernels finish.
  */
@@ -333,7 +345,7 @@ int32_t few_wait(few_plan plan, uint64_t ticket);
 /*
  * Request log of the server (few_submit): with a path, the scheduler appends
  * one JSON line per request when it retires -- ticket, status, knots, modes,
- * samples, path ("mfma", "vector" or "fp64"), batch number and size, and the
+ * samples, path ("mfma", "vector" or, for both kernels of FEW_FP64 plans, "fp64"), batch number and size, and the
  * times in microseconds since plan creation (host steady clock) at which it
  * arrived (few_submit), was admitted into a batch and was seen complete
  * (admit_us is -1 for a request that was never admitted).  The file is
@@ -410,7 +422,7 @@ uint64_t few_host_request_bytes(int32_t precision, int32_t K, int32_t M,
  * matrix operands and summed on the matrix cores whatever its length (unless
  * the plan sets FEW_FLAG_VECTOR_ONLY), 0 if it is folded into a term table,
  * which the matrix cores take for longer sums and the vector units for
- * shorter ones, or a negative few_status for an invalid list.  few_host_mfma_shape
+ * shorter ones, dense knot grids and lists far from n = 0, or a negative few_status for an invalid list.  few_host_mfma_shape
  * writes the launch shape: out8 = (waves per workgroup, 16-sample tiles per
  * wave, 16-row tiles, 32-column steps per sign of n, most MFMA instructions
  * per tile and round (about a third of them where the cubic is written about
