@@ -329,39 +329,39 @@ struct TermLayout {
 // by the vector kernel.  Measured as sums of a kept spline, fold included (10 s
 // cadence, log-spaced knots; vector / matrix-core on smooth amplitudes / on
 // amplitudes with 10 % noise at every knot, us):
-//   3.16 million samples, 60 knots: 7 rows, |n| <= 5, 77 terms 81 / 54 / 62; 11 rows,
-//     |n| <= 3, 77 terms 90 / 64 / 94; 17 rows, |n| <= 4, 153 terms 145 / 102 / 123;
-//     on 1000 knots 125 / 97 / 103, 126 / 109 / 128, 196 / 165 / 197
-//   1 million samples, 60 knots: 36 / 30 / 32, 41 / 36 / 41, 17 rows, |n| <= 8, 289
-//     terms 103 / 55 / 58; on 1000 knots 70 / 72 / 73, 75 / 80 / 85, 141 / 115 / 124
-//   262144 samples, 60 knots: 7 rows, |n| <= 8, 119 terms 23 / 20 / 21; 11 rows, |n| <= 6,
-//     143 terms 27 / 23 / 24; 7 rows, |n| <= 17, 245 terms 33 / 24 / 25; 17 rows,
-//     |n| <= 8 44 / 33 / 33; on 1000 knots 65 / 60 / 63, 76 / 67 / 70, 91 / 72 / 76, 111 / 92 / 95
-//   Kerr, 8640 samples, 60 knots, terms per polar index: 3 x 147 45 / 25 / 25, 5 x 187
-//     88 / 39 / 40, 5 x 1281 209 / 73 / 75; 1000 samples on 900 knots 79 / 100 / 102,
-//     125 / 156 / 163, 624 / 449 / 462
+//   3.16 million samples, 60 knots: 7 rows, |n| <= 5, 77 terms 90 / 57 / 66; 11 rows,
+//     |n| <= 3, 77 terms 96 / 67 / 85; 17 rows, |n| <= 4, 153 terms 156 / 106 / 135;
+//     on 1000 knots 122 / 94 / 103, 129 / 106 / 126, 198 / 163 / 192
+//   1 million samples, 60 knots: 39 / 30 / 33, 40 / 34 / 41, 17 rows, |n| <= 8, 289
+//     terms 93 / 51 / 59; on 1000 knots 70 / 69 / 70, 73 / 76 / 82, 145 / 112 / 114
+//   262144 samples, 60 knots: 7 rows, |n| <= 8, 119 terms 23 / 20 / 20; 11 rows, |n| <= 6,
+//     143 terms 26 / 22 / 22; 7 rows, |n| <= 17, 245 terms 36 / 24 / 25; 17 rows,
+//     |n| <= 8 44 / 31 / 32; on 1000 knots 65 / 58 / 59, 73 / 65 / 67, 93 / 71 / 73, 110 / 89 / 92
+//   Kerr, 8640 samples, 60 knots, terms per polar index: 3 x 147 45 / 24 / 25, 5 x 187
+//     87 / 39 / 39, 5 x 1281 210 / 72 / 75; 1000 samples on 900 knots 78 / 98 / 98,
+//     124 / 154 / 159, 628 / 447 / 462
 // (The lines for short Kerr sums are cautious: sums that would gain lie below them,
-// 8640 samples, 5 x 341 terms 67 / 41, 5 x 425 85 / 62.)
+// 8640 samples, 5 x 341 terms 67 / 40, 5 x 425 85 / 62.)
 // Binary64: both kernels are bound by the binary64 unit, the vector one with
 // its terms, the matrix one with the cells (row, n) that its products cover,
 // empty ones too, and with the powers of the cubic that take binary64 products:
 // two on smooth amplitudes, three or four on noise, which the rule cannot know.
 // Vector / matrix-core smooth / 10 % noise, us, terms of cells:
-//   100 knots: 3.16 million samples 1281 of 1536 1605 / 954 / 1187, 1037 of 1536 1306 / 936 /
-//     1264, 671 of 1024 814 / 670 / 860, 217 of 256 334 / 284 / 317; 0.8 million 491 / 279 /
-//     397, 421 / 277 / 422, 286 / 208 / 282, 110 / 99 / 110; 262144 278 / 169 / 196, 234 /
-//     167 / 193, 150 / 123 / 141, 60 / 54 / 58
-//   1000 knots: 0.8 million samples 615 / 443 / 640, 498 / 436 / 622, 338 / 324 / 443,
-//     146 / 164 / 182; 262144 326 / 321 / 363, 272 / 313 / 351, 188 / 235 / 254, 89 / 114 / 120
+//   100 knots: 3.16 million samples 1281 of 1536 1539 / 916 / 1183, 1037 of 1536 1258 / 919 /
+//     1178, 671 of 1024 824 / 668 / 856, 217 of 256 314 / 273 / 316; 0.8 million 496 / 277 /
+//     397, 430 / 277 / 417, 268 / 204 / 282, 106 / 95 / 109; 262144 277 / 167 / 188, 226 /
+//     165 / 186, 148 / 122 / 133, 62 / 53 / 57
+//   1000 knots: 0.8 million samples 617 / 442 / 627, 497 / 433 / 610, 348 / 322 / 438,
+//     142 / 159 / 182; 262144 327 / 319 / 353, 268 / 312 / 345, 186 / 233 / 252, 87 / 110 / 118
 //   so the line rises with the knots; on smooth amplitudes nothing beyond it is slower
-//   than the vector kernel (up to 5 % at 1000 knots), on 10 % noise up to 1.2 times
-//   (0.66 of the cells filled, 150 knots, 1.6 million samples 445 / 363 / 537).
-//   Kerr, 0.4 million samples, 60 knots, five polar indices: 341 of 512 458 / 405 /
-//     481, 425 of 672 583 / 548 / 603, 1281 of 1536 1619 / 912 / 1211
+//   than the vector kernel (up to 2 % at 1000 knots), on 10 % noise up to 1.2 times
+//   (0.66 of the cells filled, 150 knots, 3.16 million samples 842 / 688 / 1002).
+//   Kerr, 0.4 million samples, 60 knots, five polar indices: 341 of 512 460 / 402 /
+//     499, 425 of 672 592 / 547 / 601, 1281 of 1536 1603 / 911 / 1151
 // Below one round per SIMD the vector kernel's serial walk over the terms is
 // what a call waits for: 8640 samples, 60 knots, Kerr, 5 x 119 terms 134 / 56, 5 x 341
-// 341 / 95; 30000 samples 135 / 75 and 341 / 132; 8640 samples on 400 knots 153 / 114 and
-// 377 / 196.
+// 340 / 94; 30000 samples 135 / 74 and 341 / 132; 8640 samples on 400 knots 152 / 114 and
+// 376 / 194.
 // Schwarzschild requests below 262144 samples stay on the vector kernel: alone
 // they would gain (1281 terms over one day, binary64, 265 / 111), but batches of
 // them share its persistent launch, and a second launch of few workgroups at
@@ -424,7 +424,7 @@ __host__ __device__ inline int mf_terms_cost(int shape, int ns, bool f64) {
 // starts, two visits in place of one: binary64, 1281 terms, 262144 samples on 1000
 // knots 642 -> 321 us, 5 x 171 Kerr terms, 8640 samples on 60 knots 131 -> 73 us, binary32
 // from the fold table, 5 x 187, 100000 samples on 900 knots 326 -> 171 us, from operand
-// tables, 1281 terms, 8640 samples 27.5 -> 22.9 us and 400000 on 1000 knots 116 -> 108 us.
+// tables, 1281 terms, 8640 samples 25.7 -> 20.9 us and 400000 on 1000 knots 109 -> 104 us.
 // Twice these gaps gave the same or less (1000 knots, binary64, 400000 samples:
 // 0.89 of the time without gaps against 0.79), half of them less.
 constexpr int kMfGapTerms = 1024, kMfGap = 512;     // binary32 from the fold table, others
